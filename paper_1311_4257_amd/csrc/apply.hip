@@ -24,6 +24,7 @@
 #include <utility>
 
 #include "internal.hpp"
+#include "split_mfma.hpp"
 
 namespace dfmm {
 
@@ -238,8 +239,6 @@ __global__ void __launch_bounds__(S2M_BS) k_s2m(const int* __restrict__ lstart, 
   }
 }
 
-typedef float v4f __attribute__((ext_vector_type(4)));  // an MFMA accumulator tile
-
 // S2M for many right-hand sides as a complex GEMM on MFMA: per leaf, the
 // outgoing check potentials are V^T (R x points) times the leaf's densities
 // (points x rhs).  A workgroup takes (leaf, 16 NCT right-hand sides); the
@@ -305,482 +304,18 @@ __global__ void __launch_bounds__(64 * S2M_MT_NW) k_s2m_mfma(const int* __restri
   }
 }
 
-// ---- grouped gather GEMM on MFMA: Y[vdst] = A[op] X[vsrc] ------------------------
-// The complex product y = A x is done as a real product on interleaved data:
-// real row 2q (re) of A is (Re A[q][p], -Im A[q][p]) per column pair (2p, 2p+1)
-// and row 2q+1 (im) is (Im, Re); x and y stay in their natural interleaved
-// layout.  One workgroup (NW = 2 or 4 waves) handles NT*16 vector columns of
-// one group (one operator).  The 16-row M-tiles m of the group go to the waves
-// as m = wave + NW (slice + slices t), t = 0, 1, ... (slice = blockIdx.y), and each
-// wave walks its tiles one after the other, so a group's own M_g sets the work
-// and no MFMA runs on an empty tile.  The K dimension of a tile is split into
-// four quarters, one per group of 16 lanes (MFMA k index): a lane reads four
-// consecutive k values of its quarter with one 16-byte load from LDS (B) and
-// from the fragment-ordered operator (A).  The column block sits in LDS,
-// [column][k] with a row stride S = 4 (mod 32) floats.  The (tile, k-step)
-// sequence of a wave is one flat loop; the operator loads of the next few step
-// pairs are in flight in a register ring, and a load is issued for every step
-// pair (past the end it repeats the last address) so that each wait is for the
-// oldest load only.
-
-__host__ __device__ inline int gg_stride(int K) {
-  int s = 2 * K;
-  return s + ((4 - (s % 32)) + 32) % 32;
-}
-
-// operator loads in flight per lane (each covers two k-steps)
-template <int NT>
-struct GgDepth {
-  static constexpr int value = NT == 1 ? 4 : (NT == 2 ? 4 : 3);
-};
-
-// the float4 of the neighbouring lane (lane ^ 1), by DPP quad permutation [1, 0, 3, 2]
-__device__ __forceinline__ float4 swap_pair(const float4 v) {
-  auto sw = [](float x) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xF, 0xF, false));
-  };
-  return make_float4(sw(v.x), sw(v.y), sw(v.z), sw(v.w));
-}
-
-// ---- split 16-bit products (FP16X3 / BF16X3 plans) -----------------------------------
-// A 32-bit word holds two 16-bit values, the first in the low half.  x = hi + lo
-// with hi the 16-bit rounding of x and lo that of the (exact) remainder.
-typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-constexpr int PREC_F16 = 1, PREC_BF16 = 2;
-
-template <int PREC>
-__device__ __forceinline__ void split_pair(float a, float b, unsigned& hi, unsigned& lo) {
-  if constexpr (PREC == PREC_F16) {
-    const _Float16 ha = _Float16(a), hb = _Float16(b);
-    const _Float16 la = _Float16(a - float(ha)), lb = _Float16(b - float(hb));
-    hi = unsigned(__builtin_bit_cast(unsigned short, ha)) | (unsigned(__builtin_bit_cast(unsigned short, hb)) << 16);
-    lo = unsigned(__builtin_bit_cast(unsigned short, la)) | (unsigned(__builtin_bit_cast(unsigned short, lb)) << 16);
-  } else {
-    auto rne = [](float x) {  // bfloat16 bits, round to nearest even
-      const unsigned u = __float_as_uint(x);
-      return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-    };
-    const unsigned ha = rne(a), hb = rne(b);
-    hi = ha | (hb << 16);
-    lo = rne(a - __uint_as_float(ha << 16)) | (rne(b - __uint_as_float(hb << 16)) << 16);
-  }
-}
-
-// (x, y) -> (y, x) of a word's two halves
-__device__ __forceinline__ unsigned rot16(unsigned x) { return __builtin_amdgcn_alignbit(x, x, 16); }
-
-template <int PREC>
-__device__ __forceinline__ v4f mfma16(v4u a, v4u b, v4f c) {
-  if constexpr (PREC == PREC_F16)
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0);
-  else
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0,
-                                                   0);
-}
-
-// ALDS: stage the workgroup's operator tiles in LDS first.  ACC64: every two
-// k-steps (32 real products per output) the float32 MFMA sums are added into
-// float64 partial sums, so the rounding of long float32 dot products (which
-// grows with their length) stays at that of 32 terms.
-template <int NT, bool ALDS, bool ACC64, int NW, int PREC>
-__device__ __forceinline__ void ggemm_tile(const float4* __restrict__ A, const int64_t* __restrict__ aoff,
-                                           const int* __restrict__ aexp,
-                                           const int* __restrict__ gmk, int M, int K, int split,
-                                           const int* __restrict__ gops, const int* __restrict__ gv0,
-                                           const int* __restrict__ vsrc, const int* __restrict__ vdst,
-                                           const int* __restrict__ chunk_grp, const int* __restrict__ chunk_c0,
-                                           int nrhs, const float2* __restrict__ X, float2* __restrict__ Y,
-                                           int chunk, int slice, int nslices) {
-  static_assert(!(ACC64 && PREC), "split 16-bit products are for fast plans");
-  extern __shared__ float4 xs[];
-  constexpr int NC = NT * 16;
-  constexpr int PD = GgDepth<NT>::value;
-  constexpr int BS = 64 * NW;
-  // 16-bit plans: operators packed with K_g padded to 16 (two k-steps per MFMA)
-  auto kp = [](int k) { return PREC ? (k + 15) / 16 * 16 : k; };
-  const int S4 = gg_stride(split * kp(K)) / 4;  // float4 per LDS column (split K >= every K_g)
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int j = lane & 15, kr = lane >> 4;
-  const bool odd = (j & 1) != 0;
-  const int g = chunk_grp[chunk];
-  const int Mg = gmk[2 * g], Kr = gmk[2 * g + 1];  // this group's operator size
-  const int Kg = kp(Kr);                 // packed K (Kr + zero columns in 16-bit plans)
-  const int Q4 = Kg / 8;                 // k-steps per tile (K_g / 2 real k per quarter, 4 per step)
-  const int nM = Mg / 8, nMall = M / 8;  // 16-row real M-tiles with data / in the vector stride
-  const int m0 = wave + NW * slice, mstep = NW * nslices;
-  const int mcnt = m0 < nM ? (nM - m0 + mstep - 1) / mstep : 0;
-  const int64_t c0 = chunk_c0[chunk];
-  const int vbeg = gv0[g];
-  const int64_t ncol = int64_t(gv0[g + 1] - vbeg) * nrhs;
-  const int nc = int(min<int64_t>(NC, ncol - c0));
-
-  // stage the source vectors: column c -> X[(src * nrhs + k) * K], its first K_g
-  // complex entries.  The column sources go through a small LDS table (one
-  // division per column); each thread then walks its elements (q4 fastest, so
-  // a wave reads long contiguous runs) with incremental indices, issuing a
-  // batch of loads before storing them.
-  const int per_col = Kg / 2;  // float4 per column
-  const int pcs = per_col / split;  // float4 per source vector (split = 2: each read twice)
-  const int preal = Kr / 2;         // float4 of the column that the vector holds (rest: zero padding)
-  const float4* Aop = A + aoff[gops[g]];
-  const int tile4 = Q4 * 32;  // float4 per M-tile in the fragment order
-  float4* as = xs + NC * S4;  // ALDS: the tiles of this slice, [t][wave][tile4]
-
-  // operator fragment stream of this wave: flat step i = (t, s) reads tile base
-  // + s * 32 + this lane's offset.  The two lanes of a row pair (j, j ^ 1) need
-  // the same 16 bytes, so one load serves two steps: the even lane fetches step
-  // i and the odd lane step i + 1, and a lane swap gives each both.  From global
-  // memory the first loads are issued before the column staging, so their
-  // latency overlaps it.
-  const int total = mcnt * Q4;  // flat (tile, k-step) sequence of this wave
-  const int lofs = (j >> 1) * 4 + kr;
-  // Offsets are 32-bit (one operator holds far fewer than 2^31 float4) and
-  // strictly increase along the sequence (every advance adds at least 32), so
-  // clamping to the last step's offset repeats it past the end.  The loop
-  // bookkeeping is scalar work that competes with the MFMAs for issue slots,
-  // hence no branches and no 64-bit arithmetic here.
-  const int tbase0 = ALDS ? wave * tile4 : m0 * tile4;
-  const int tjump = ALDS ? NW * tile4 : mstep * tile4;
-  const float4* abase = (ALDS ? static_cast<const float4*>(as) : Aop) + lofs;
-  const int last = tbase0 + (mcnt - 1) * tjump + (Q4 - 1) * 32;
-  const int pwrap = tjump - (Q4 - 1) * 32;  // from a tile's last k-step to the next tile's first
-  int ps = 0;                 // k-step of the next prefetch within its tile
-  int pofs = tbase0;          // its offset
-  auto advance = [&]() {
-    const bool wrap = ++ps == Q4;
-    ps = wrap ? 0 : ps;
-    pofs += wrap ? pwrap : 32;
-  };
-  auto fetch = [&]() -> float4 {  // the next two steps: the even lane's, then the odd lane's
-    const int o0 = min(pofs, last);
-    advance();
-    const int o1 = min(pofs, last);
-    advance();
-    return abase[odd ? o1 : o0];
-  };
-  float4 ring[PD];
-  if (!ALDS && total > 0) {
-#pragma unroll
-    for (int p = 0; p < PD; ++p) ring[p] = fetch();
-  }
-  __shared__ const float4* colsrc[NC];
-  if (threadIdx.x < NC) {
-    const int col = threadIdx.x;
-    const float4* p = nullptr;
-    if (col < nc) {
-      const int64_t cc = c0 + col;
-      const int src = vsrc[vbeg + int(cc / nrhs)];
-      if (src >= 0) p = reinterpret_cast<const float4*>(X + (int64_t(src) * nrhs + int(cc % nrhs)) * K);
-    }
-    colsrc[col] = p;
-  }
-  __syncthreads();
-  {
-    constexpr int UB = 4;  // loads in flight per thread
-    const int nel = NC * per_col;
-    const int dcol = BS / per_col, dq = BS % per_col;
-    int col = int(threadIdx.x) / per_col, q4 = int(threadIdx.x) % per_col;
-    for (int base = int(threadIdx.x); base < nel; base += UB * BS) {
-      float4 v[UB];
-      int dst[UB];
-#pragma unroll
-      for (int u = 0; u < UB; ++u) {
-        v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        dst[u] = -1;
-        if (base + u * BS < nel) {
-          const float4* p = colsrc[col];
-          if (p && (!PREC || q4 < preal)) v[u] = p[q4 < pcs ? q4 : q4 - pcs];
-          dst[u] = col * S4 + q4;
-        }
-        col += dcol;
-        q4 += dq;
-        if (q4 >= per_col) {
-          q4 -= per_col;
-          ++col;
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < UB; ++u)
-        if (dst[u] >= 0) xs[dst[u]] = v[u];
-    }
-  }
-  __shared__ int cexp[NC];  // 16-bit plans: power-of-two scale exponent of each column
-  if constexpr (PREC != 0) {
-    __syncthreads();  // the float32 columns are staged
-    if (threadIdx.x < NC) {
-      int e = 0;
-      if constexpr (PREC == PREC_F16) {  // largest column entry below 2^14 after scaling
-        float mx = 0.f;
-        const float4* c = xs + threadIdx.x * S4;
-        for (int q = 0; q < per_col; ++q) {
-          const float4 v = c[q];
-          mx = fmaxf(mx, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
-        }
-        if (mx > 0.f) {
-          int E;
-          (void)frexpf(mx, &E);
-          e = 14 - E;
-        }
-      }
-      cexp[threadIdx.x] = e;
-    }
-    __syncthreads();
-    for (int idx = int(threadIdx.x); idx < NC * per_col; idx += BS) {
-      const int col = idx / per_col, q = idx - col * per_col;
-      float4 v = xs[col * S4 + q];
-      if constexpr (PREC == PREC_F16) {
-        const int e = cexp[col];
-        v = make_float4(ldexpf(v.x, e), ldexpf(v.y, e), ldexpf(v.z, e), ldexpf(v.w, e));
-      }
-      unsigned h0, l0, h1, l1;
-      split_pair<PREC>(v.x, v.y, h0, l0);
-      split_pair<PREC>(v.z, v.w, h1, l1);
-      xs[col * S4 + q] = make_float4(__uint_as_float(h0), __uint_as_float(h1), __uint_as_float(l0), __uint_as_float(l1));
-    }
-  }
-  if (ALDS) {
-    const int tmax = nM > NW * slice ? (nM - NW * slice + mstep - 1) / mstep : 0;
-    const int nel = 4 * tmax * tile4;
-    const int dblk = BS / tile4, doff = BS % tile4;
-    int blk = int(threadIdx.x) / tile4, off = int(threadIdx.x) % tile4;
-    for (int idx = int(threadIdx.x); idx < nel; idx += BS) {
-      const int m = (blk % NW) + NW * slice + mstep * (blk / NW);
-      as[idx] = m < nM ? Aop[int64_t(m) * tile4 + off] : make_float4(0.f, 0.f, 0.f, 0.f);
-      blk += dblk;
-      off += doff;
-      if (off >= tile4) {
-        off -= tile4;
-        ++blk;
-      }
-    }
-  }
-  __syncthreads();
-  if (ALDS && total > 0) {
-#pragma unroll
-    for (int p = 0; p < PD; ++p) ring[p] = fetch();
-  }
-
-  // this lane's output columns
-  float2* yp[NT];
-#pragma unroll
-  for (int n = 0; n < NT; ++n) {
-    const int col = n * 16 + j;
-    yp[n] = nullptr;
-    if (col < nc) {
-      const int64_t cc = c0 + col;
-      const int vv = vbeg + int(cc / nrhs);
-      yp[n] = Y + (int64_t(vdst[vv]) * nrhs + int(cc % nrhs)) * M;
-    }
-  }
-
-  if constexpr (PREC != 0) {
-    if (total > 0) {
-      // operator scale of the group and column scales: the sums are unscaled at the write
-      const int ea = PREC == PREC_F16 ? aexp[gops[g]] : 0;
-      float osc[NT];
-#pragma unroll
-      for (int n = 0; n < NT; ++n) osc[n] = ldexpf(1.0f, -(ea + cexp[n * 16 + j]));
-      v4f acc[NT];
-#pragma unroll
-      for (int n = 0; n < NT; ++n) acc[n] = v4f{0.f, 0.f, 0.f, 0.f};
-      const float4* bcol = xs + j * S4 + kr * Q4;
-      float4 b0[NT], b1[NT];  // steps s, s + 1 of every column tile (hi, hi, lo, lo words)
-#pragma unroll
-      for (int n = 0; n < NT; ++n) {
-        b0[n] = bcol[n * 16 * S4];
-        b1[n] = bcol[n * 16 * S4 + 1];
-      }
-      int s = 0, t = 0;
-      constexpr unsigned SG = 0x80000000u;  // sign of a word's high half
-      // one ring slot = two k-steps = one 16x16x32 MFMA per product term; the
-      // even row of a complex row pair is (Re, -Im), the odd row (Im, Re)
-      auto dstep = [&](const float4 vf, const float4 wf) {
-        const unsigned vx = __float_as_uint(vf.x), vy = __float_as_uint(vf.y), vz = __float_as_uint(vf.z),
-                       vw = __float_as_uint(vf.w), wx = __float_as_uint(wf.x), wy = __float_as_uint(wf.y),
-                       wz = __float_as_uint(wf.z), ww = __float_as_uint(wf.w);
-        const v4u ah = odd ? v4u{rot16(wx), rot16(wy), rot16(vx), rot16(vy)} : v4u{vx ^ SG, vy ^ SG, wx ^ SG, wy ^ SG};
-        const v4u al = odd ? v4u{rot16(wz), rot16(ww), rot16(vz), rot16(vw)} : v4u{vz ^ SG, vw ^ SG, wz ^ SG, ww ^ SG};
-#pragma unroll
-        for (int n = 0; n < NT; ++n) {
-          const v4u bh = {__float_as_uint(b0[n].x), __float_as_uint(b0[n].y), __float_as_uint(b1[n].x),
-                          __float_as_uint(b1[n].y)};
-          const v4u bl = {__float_as_uint(b0[n].z), __float_as_uint(b0[n].w), __float_as_uint(b1[n].z),
-                          __float_as_uint(b1[n].w)};
-          acc[n] = mfma16<PREC>(ah, bh, acc[n]);
-          acc[n] = mfma16<PREC>(ah, bl, acc[n]);
-          acc[n] = mfma16<PREC>(al, bh, acc[n]);
-        }
-        s += 2;
-        const int s2 = s == Q4 ? 0 : s;  // the next step pair (the column is the same for every M-tile)
-#pragma unroll
-        for (int n = 0; n < NT; ++n) {
-          b0[n] = bcol[n * 16 * S4 + s2];
-          b1[n] = bcol[n * 16 * S4 + s2 + 1];
-        }
-        if (s == Q4) {  // tile done: lane holds real rows 4kr .. 4kr+3 = complex rows 2kr, 2kr+1
-          const int m = m0 + mstep * t;
-#pragma unroll
-          for (int n = 0; n < NT; ++n) {
-            const v4f a = acc[n];
-            const float4 o = make_float4(a[0] * osc[n], a[1] * osc[n], a[2] * osc[n], a[3] * osc[n]);
-            if (yp[n]) reinterpret_cast<float4*>(yp[n] + 8 * m + 2 * kr)[0] = o;
-            acc[n] = v4f{0.f, 0.f, 0.f, 0.f};
-          }
-          s = 0;
-          ++t;
-        }
-      };
-      int i0 = 0;  // total is even: Q4 is even in 16-bit plans
-      for (; i0 + 2 * PD <= total; i0 += 2 * PD) {
-#pragma unroll
-        for (int p = 0; p < PD; ++p) {
-          const float4 v = ring[p], w = swap_pair(v);
-          dstep(v, w);
-          ring[p] = fetch();
-        }
-      }
-#pragma unroll
-      for (int p = 0; p < PD; ++p) {
-        if (i0 + 2 * p >= total) break;
-        const float4 v = ring[p], w = swap_pair(v);
-        dstep(v, w);
-      }
-    }
-  } else if (total > 0) {
-    v4f acc[NT];  // consecutive MFMAs on one accumulator chain through its C operand
-    double a64[ACC64 ? NT : 1][4];
-#pragma unroll
-    for (int n = 0; n < NT; ++n) acc[n] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int n = 0; n < (ACC64 ? NT : 1); ++n)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) a64[n][r] = 0.0;
-    int s = 0, t = 0;
-    // B fragments: a ring of two steps (slot p & 1 of the unrolled loop)
-    const float4* bcol = xs + j * S4 + kr * Q4;
-    const int s1 = Q4 > 1 ? 1 : 0;
-    float4 bq[2][NT];
-#pragma unroll
-    for (int n = 0; n < NT; ++n) {
-      bq[0][n] = bcol[n * 16 * S4];
-      bq[1][n] = bcol[n * 16 * S4 + s1];
-    }
-    // the complex A fragments of a step pair as real rows (even row: Re, -Im;
-    // odd row: Im, Re): v is this lane's load, w its neighbour's
-    auto frag0 = [&](const float4 v, const float4 w, float (&av)[4]) {  // step i
-      av[0] = odd ? w.y : v.x;
-      av[1] = odd ? w.x : -v.y;
-      av[2] = odd ? w.w : v.z;
-      av[3] = odd ? w.z : -v.w;
-    };
-    auto frag1 = [&](const float4 v, const float4 w, float (&av)[4]) {  // step i + 1
-      av[0] = odd ? v.y : w.x;
-      av[1] = odd ? v.x : -w.y;
-      av[2] = odd ? v.w : w.z;
-      av[3] = odd ? v.z : -w.w;
-    };
-    int s2 = 2 % Q4;  // the k-step two ahead of s, within its tile
-    auto step = [&](const float (&av)[4], float4 (&b)[NT]) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int n = 0; n < NT; ++n) {
-          const float bv = u == 0 ? b[n].x : (u == 1 ? b[n].y : (u == 2 ? b[n].z : b[n].w));
-          acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], bv, acc[n], 0, 0, 0);
-        }
-#pragma unroll
-      for (int n = 0; n < NT; ++n) b[n] = bcol[n * 16 * S4 + s2];
-      s2 = s2 + 1 == Q4 ? 0 : s2 + 1;  // s advances by one step, cyclically within the tile
-      if constexpr (ACC64) {
-        if ((s & 1) || s + 1 == Q4) {
-#pragma unroll
-          for (int n = 0; n < NT; ++n) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) a64[n][r] += double(acc[n][r]);
-            acc[n] = v4f{0.f, 0.f, 0.f, 0.f};
-          }
-        }
-      }
-      if (++s == Q4) {  // tile done: lane holds real rows 4kr .. 4kr+3 = complex rows 2kr, 2kr+1
-        const int m = m0 + mstep * t;
-#pragma unroll
-        for (int n = 0; n < NT; ++n) {
-          float4 o;
-          if constexpr (ACC64) {
-            o = make_float4(float(a64[n][0]), float(a64[n][1]), float(a64[n][2]), float(a64[n][3]));
-#pragma unroll
-            for (int r = 0; r < 4; ++r) a64[n][r] = 0.0;
-          } else {
-            const v4f a = acc[n];
-            o = make_float4(a[0], a[1], a[2], a[3]);
-          }
-          if (yp[n]) reinterpret_cast<float4*>(yp[n] + 8 * m + 2 * kr)[0] = o;
-          acc[n] = v4f{0.f, 0.f, 0.f, 0.f};
-        }
-        s = 0;
-        ++t;
-      }
-    };
-    // each load's register is refilled after its two steps have consumed it
-    int i0 = 0;
-    float av0[4], av1[4];
-    for (; i0 + 2 * PD <= total; i0 += 2 * PD) {
-#pragma unroll
-      for (int p = 0; p < PD; ++p) {
-        const float4 v = ring[p], w = swap_pair(v);
-        frag0(v, w, av0);
-        frag1(v, w, av1);
-        step(av0, bq[0]);
-        step(av1, bq[1]);
-        ring[p] = fetch();
-      }
-    }
-#pragma unroll
-    for (int p = 0; p < PD; ++p) {
-      if (i0 + 2 * p >= total) break;
-      const float4 v = ring[p], w = swap_pair(v);
-      frag0(v, w, av0);
-      frag1(v, w, av1);
-      step(av0, bq[0]);
-      if (i0 + 2 * p + 1 < total) step(av1, bq[1]);
-    }
-  }
-  // tiles between the group's M_g and the vector stride M hold zeros
-  for (int m = m0 + mstep * mcnt; m < nMall; m += mstep)
-#pragma unroll
-    for (int n = 0; n < NT; ++n)
-      if (yp[n]) reinterpret_cast<float4*>(yp[n] + 8 * m + 2 * kr)[0] = make_float4(0.f, 0.f, 0.f, 0.f);
-}
-
-#define DFMM_GG_PARAMS                                                                                       \
-  const float4 *__restrict__ A, const int64_t *__restrict__ aoff, const int *__restrict__ aexp,               \
-      const int *__restrict__ gmk, int M, int K,                                                               \
-      int split, const int *__restrict__ gops, const int *__restrict__ gv0, const int *__restrict__ vsrc,      \
-      const int *__restrict__ vdst, const int *__restrict__ chunk_grp, const int *__restrict__ chunk_c0,       \
-      int nrhs, const float2 *__restrict__ X, float2 *__restrict__ Y
-#define DFMM_GG_ARGS A, aoff, aexp, gmk, M, K, split, gops, gv0, vsrc, vdst, chunk_grp, chunk_c0, nrhs, X, Y
-
-// The same tile engine under two names, so that kernel traces separate the
-// translations (M2L of Algorithm 1) from the pair-form tree transfers (M2M and L2L).
-template <int NT, bool ALDS, bool ACC64, int NW, int PREC>
-__global__ void __launch_bounds__(64 * NW) k_m2l(DFMM_GG_PARAMS) {
-  ggemm_tile<NT, ALDS, ACC64, NW, PREC>(DFMM_GG_ARGS, int(blockIdx.x), int(blockIdx.y), int(gridDim.y));
-}
-template <int NT, bool ALDS, bool ACC64, int NW, int PREC>
-__global__ void __launch_bounds__(64 * NW) k_transfer(DFMM_GG_PARAMS) {
-  ggemm_tile<NT, ALDS, ACC64, NW, PREC>(DFMM_GG_ARGS, int(blockIdx.x), int(blockIdx.y), int(gridDim.y));
-}
-
-// All M2L launches of an apply (every HF level and the leaf level) in one
-// launch: they read only the upward pass's outputs, so their chunks can share
-// the GPU (the HBM-bound HF chunks beside the compute-bound leaf-level ones).
-// A chunk names its problem and M-slice; each problem writes its own pair
-// scratch, reduced afterwards in the order of the separate launches.
-constexpr int kMaxProbs = 8;
-struct GgProb {
+// ---- grouped gather GEMM on MFMA: Y[v] = A[op] X[vsrc] ---------------------------
+// One workgroup handles NT*16 vector columns of one group (one operator); pair
+// output v of a group is vector v of Y.  The columns are staged in LDS once, in
+// their 16-bit planes (split_mfma.hpp); a wave stages whole columns, so that
+// a column's 16-bit scale needs no other wave.  The tiles of 16 complex rows go
+// to the waves as m = wave + waves (slice + slices t), t = 0, 1, ... (slice =
+// blockIdx.y), and each wave walks its (tile, step) sequence with the operator
+// rows of the next step in flight; the first are issued before the staging.
+// ACC64 (precise plans): every step's float32 sums (64 products per output)
+// are added into float64 partial sums, so the rounding of long float32 dot
+// products, which grows with their length, stays at that of one step.
+struct GgArgs {
   const float4* A;
   const int64_t* aoff;
   const int* aexp;
@@ -788,44 +323,209 @@ struct GgProb {
   const int* gops;
   const int* gv0;
   const int* vsrc;
-  const int* vdst;
   const float2* X;
   float2* Y;
-  int M, K, split, slices;
+  int M, K;  // row strides of the Y and X vectors
+  int half;  // 8 columns per chunk instead of 16 (operators too long for LDS with 16; 16-column launches only)
 };
-struct GgProbs {
-  GgProb p[kMaxProbs];
-};
-template <int NT, int NW, int PREC>
-__global__ void __launch_bounds__(64 * NW) k_m2l_fused(const GgProbs P, const int* __restrict__ chunk_ps,
-                                                        const int* __restrict__ chunk_grp,
-                                                        const int* __restrict__ chunk_c0, int nrhs) {
-  const int c = int(blockIdx.x);
-  const int ps = chunk_ps[c];  // problem | slice << 4
-  const GgProb& q = P.p[ps & 15];
-  ggemm_tile<NT, false, false, NW, PREC>(q.A, q.aoff, q.aexp, q.gmk, q.M, q.K, q.split, q.gops, q.gv0, q.vsrc,
-                                         q.vdst, chunk_grp, chunk_c0, nrhs, q.X, q.Y, c, ps >> 4, q.slices);
+
+template <int NT, bool ACC64, int OP>
+__device__ __forceinline__ void ggemm_tile(const GgArgs& a, const int* __restrict__ chunk_grp,
+                                           const int* __restrict__ chunk_c0, int nrhs, int chunk, int slice,
+                                           int nslices) {
+  extern __shared__ float4 xs4[];
+  __shared__ int cexp[16 * NT];  // FP16X3: power-of-two scale exponent of each column
+  constexpr int NC = NT * 16, AW = OpForm<OP>::AW;
+  v4u* xs = reinterpret_cast<v4u*>(xs4);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  const int nw = int(blockDim.x) >> 6;
+  const int g = chunk_grp[chunk];
+  const int Mg = a.gmk[2 * g], Kg = a.gmk[2 * g + 1];  // this group's operator size
+  const OpRows o(Kg, lane);
+  const int cs = col_units(Kg, OpForm<OP>::PB);
+  const int nM = (Mg + 15) / 16, nMall = (a.M + 15) / 16;  // row tiles with data / in the vector stride
+  const int m0 = wave + nw * slice, mstep = nw * nslices;
+  const int mcnt = m0 < nM ? (nM - m0 + mstep - 1) / mstep : 0;
+  const int c0 = chunk_c0[chunk];
+  const int vbeg = a.gv0[g];
+  const int64_t ncol = int64_t(a.gv0[g + 1] - vbeg) * nrhs;
+  const int ncmax = NT == 1 && a.half ? 8 : NC;
+  const int nc = int(min<int64_t>(ncmax, ncol - c0));
+  const int op = a.gops[g];
+  const float4* Aop = a.A + a.aoff[op];
+  const int tile4 = 2 * Kg * AW;  // float4 of a full row tile
+  float4 raw[AW];
+  auto tile = [&](int m) { return OpTile<OP>(o, Aop + m * tile4, min(16, Mg - 16 * m)); };
+  if (mcnt > 0) load_first<OP>(tile(m0), raw);
+  {
+    // lane c holds column c's source vector; its wave reads it lane by lane
+    int src = -1;
+    if (lane < nc) {
+      const int cc = c0 + lane, v = cc / nrhs;
+      const int s = a.vsrc[vbeg + v];
+      if (s >= 0) src = s * nrhs + (cc - v * nrhs);
+    }
+    constexpr int UB = 4;  // columns in flight
+    const int per_col = Kg / 2;            // float4 per column
+    const int pad_col = 4 * col_chunks(Kg);  // and with the chunk of zeros
+    auto at = [&](int col, int q) -> float4 {
+      const int s = __builtin_amdgcn_readlane(src, col);
+      if (s < 0 || q >= per_col) return make_float4(0.f, 0.f, 0.f, 0.f);
+      return reinterpret_cast<const float4*>(a.X + int64_t(s) * a.K)[q];
+    };
+    for (int cb = wave; cb < ncmax; cb += UB * nw) {
+      float4 v[UB];
+      int e[UB];
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        const int col = cb + u * nw;
+        e[u] = 0;
+        v[u] = col < ncmax ? at(col, lane) : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+      if constexpr (OP == OP_F16) {  // largest column entry below 2^14 after scaling
+#pragma unroll
+        for (int u = 0; u < UB; ++u) {
+          const int col = cb + u * nw;
+          if (col >= ncmax) break;
+          float mx = 0.f;
+          for (int q = lane;;) {
+            const float4 w = q == lane ? v[u] : at(col, q);
+            mx = fmaxf(mx, fmaxf(fmaxf(fabsf(w.x), fabsf(w.y)), fmaxf(fabsf(w.z), fabsf(w.w))));
+            q += 64;
+            if (q - lane >= per_col) break;
+          }
+          mx = wave_max(mx);
+          if (mx > 0.f) {
+            int E;
+            (void)frexpf(mx, &E);
+            e[u] = 14 - E;
+          }
+          if (lane == 0) cexp[col] = e[u];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        const int col = cb + u * nw;
+        if (col >= ncmax) break;
+        unsigned* xc = reinterpret_cast<unsigned*>(xs + col * cs);
+        for (int q0 = 0; q0 < pad_col; q0 += 64) {
+          float4 w = q0 == 0 ? v[u] : at(col, q0 + lane);
+          if constexpr (OP == OP_F16)
+            w = make_float4(ldexpf(w.x, e[u]), ldexpf(w.y, e[u]), ldexpf(w.z, e[u]), ldexpf(w.w, e[u]));
+          if (q0 + lane < pad_col) stage_pair<OP>(xc, q0 + lane, w);
+        }
+      }
+    }
+  }
+  __syncthreads();
+
+  float osc[NT];
+  if constexpr (OP == OP_F16) {
+    // operator scale of the group and column scales: the sums are unscaled at the write
+    const int ea = a.aexp[op];
+#pragma unroll
+    for (int n = 0; n < NT; ++n) osc[n] = ldexpf(1.0f, -(ea + cexp[n * 16 + (ncmax < 16 ? o.j & 7 : o.j)]));
+  }
+  float2* yb = a.Y + (int64_t(vbeg) * nrhs + c0) * a.M + 4 * o.kr;  // lane: rows 4 kr .. 4 kr + 3 of a tile
+  const int jcol = ncmax < 16 ? o.j & 7 : o.j;
+  using Acc = typename std::conditional<ACC64, double, float>::type;
+  Acc re[NT][4], im[NT][4];
+  for (int m = m0; m < nM; m += mstep) {
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) re[n][r] = im[n][r] = Acc(0);
+    const int mn = m + mstep < nM ? m + mstep : m;  // past the last tile: its rows again
+    tile_product<OP, NT>(o, tile(m), tile(mn), xs + jcol * cs, cs, raw, [&](int n, const StepSums& t, auto merged) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        re[n][r] += Acc(t.p[r]);
+        if constexpr (!decltype(merged)::value) re[n][r] -= Acc(t.q[r]);
+        im[n][r] += Acc(t.i[r]);
+      }
+    });
+    // rows past M_g are zeros up to the vector stride
+    const int row = 16 * m + 4 * o.kr;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      float v[8];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        float x = float(re[n][r]), y = float(im[n][r]);
+        if constexpr (OP == OP_F16) {
+          x *= osc[n];
+          y *= osc[n];
+        }
+        v[2 * r] = row < Mg ? x : 0.f;
+        v[2 * r + 1] = row < Mg ? y : 0.f;
+      }
+      if (n * 16 + o.j < nc && row < a.M) {
+        float4* y = reinterpret_cast<float4*>(yb + int64_t(n * 16 + o.j) * a.M + 16 * m);
+        y[0] = make_float4(v[0], v[1], v[2], v[3]);
+        y[1] = make_float4(v[4], v[5], v[6], v[7]);
+      }
+    }
+  }
+  // tiles between the group's M_g and the vector stride M hold zeros
+  for (int m = m0 + mstep * mcnt; m < nMall; m += mstep)
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+      if (n * 16 + o.j < nc && 16 * m + 4 * o.kr < a.M) {
+        float4* y = reinterpret_cast<float4*>(yb + int64_t(n * 16 + o.j) * a.M + 16 * m);
+        y[0] = y[1] = make_float4(0.f, 0.f, 0.f, 0.f);
+      }
 }
-#undef DFMM_GG_PARAMS
-#undef DFMM_GG_ARGS
+
+// The same tile engine under two names, so that kernel traces separate the
+// translations (M2L of Algorithm 1) from the pair-form tree transfers (M2M and L2L).
+constexpr int GG_MINW = 2, GG_MAXW = 8;  // waves per workgroup
+// Waves per SIMD that the registers have to allow: 4 for up to 32 columns.
+#define DFMM_GG_BOUNDS(NT, OP) __launch_bounds__(64 * GG_MAXW, OP == OP_P4 ? 2 : 4)
+template <int NT, bool ACC64, int OP>
+__global__ void DFMM_GG_BOUNDS(NT, (ACC64 ? OP_P4 : OP)) k_m2l(const GgArgs a, const int* __restrict__ chunk_grp,
+                                                      const int* __restrict__ chunk_c0, int nrhs) {
+  ggemm_tile<NT, ACC64, OP>(a, chunk_grp, chunk_c0, nrhs, int(blockIdx.x), int(blockIdx.y), int(gridDim.y));
+}
+template <int NT, bool ACC64, int OP>
+__global__ void DFMM_GG_BOUNDS(NT, (ACC64 ? OP_P4 : OP)) k_transfer(const GgArgs a, const int* __restrict__ chunk_grp,
+                                                           const int* __restrict__ chunk_c0, int nrhs) {
+  ggemm_tile<NT, ACC64, OP>(a, chunk_grp, chunk_c0, nrhs, int(blockIdx.x), int(blockIdx.y), int(gridDim.y));
+}
+// All M2L launches of an apply (every HF level and the leaf level) in one
+// launch: they read only the upward pass's outputs, so their chunks can share
+// the GPU (the HBM-bound HF chunks beside the compute-bound leaf-level ones).
+// A chunk names its problem; each problem writes its own pair scratch, reduced
+// afterwards in the order of the separate launches.
+constexpr int kMaxProbs = 8;
+struct GgProbs {
+  GgArgs p[kMaxProbs];
+};
+template <int NT, int OP>
+__global__ void DFMM_GG_BOUNDS(NT, OP) k_m2l_fused(const GgProbs P, const int* __restrict__ chunk_ps,
+                                                   const int* __restrict__ chunk_grp,
+                                                   const int* __restrict__ chunk_c0, int nrhs) {
+  const int c = int(blockIdx.x);
+  ggemm_tile<NT, false, OP>(P.p[chunk_ps[c]], chunk_grp, chunk_c0, nrhs, c, 0, 1);
+}
 
 // ---- slot-form GEMM: every output slot sums its terms in registers ---------------
 // A workgroup owns one output vector (a slot, 16 NT of its right-hand sides)
-// and one wave per 16-row M-tile of it.  It walks the slot's terms in their
-// fixed order: each term's source columns are staged in LDS (double-buffered:
-// the next term's columns are loaded into registers while this term's
-// products run, and stored after them), and each wave holds the whole tile of
-// the term's operator in registers, loaded one term ahead.  A term's products
-// accumulate in float32 MFMA chains (one operator row against the column, as
-// in the pair form) and are added into float64 sums across terms, so the slot's
+// and one wave per tile of 16 rows.  It walks the slot's terms in their fixed
+// order: each term's source columns are staged in LDS in their 16-bit planes,
+// then each wave multiplies its operator rows, whose next step (or the next
+// term's first) is in flight.  A term's products accumulate in float32 (as in
+// the pair form) and are added into float64 sums across terms, so the slot's
 // sum has the rounding of the pair form's fixed-order reduction without its
 // stored pair outputs.  The terms of a launch are of two kinds with their own
-// operator and source arrays (a level's M2L pairs and its L2L terms).
+// operator and source arrays (a level's M2L pairs and its L2L terms).  One
+// workgroup stages while another one multiplies: one column buffer, and two
+// workgroups per CU.
 struct SlotArgs {
   const int* order;   // launch order of the groups
   const int* t0;      // term range of each group
   const int* gm;      // padded rows of each group's operators
-  const int4* terms;  // (operator float4 offset, source vector, K | split << 12 | kind << 14, 0)
+  const int4* terms;  // (operator float4 offset, source vector, K | kind << 14, 0)
   const float4* A0;
   const float4* A1;
   const float2* X0;
@@ -833,213 +533,113 @@ struct SlotArgs {
   int KX0, KX1;       // row strides of the two kinds' source vectors
   int M;              // row stride of the output vectors
   int cpg;            // column chunks per group
-  int S4;             // LDS column stride in float4
-  int waves;          // waves per workgroup (M-tiles per slice)
+  int cu;             // LDS units of the column block
+  int waves;          // waves per workgroup (row tiles per slice)
   const int* gdst;    // output vector of each group (null: the group's own index)
 };
-constexpr int SLOT_UB = 2;  // staged float4 per thread and term
-// s_waitcnt immediate for vmcnt(0) alone (gfx9 encoding: vmcnt bits 3:0 and
-// 15:14, expcnt 6:4 and lgkmcnt 11:8 left at their maxima)
-constexpr int kWaitVm0 = 0x0F70;
 
-// f(std::integral_constant<int, q>) for the runtime q in 1 .. QMAX (nothing
-// for any other q): one branch-free body per term length
-template <int QMAX, typename F, int... I>
-__device__ __forceinline__ void slot_dispatch_seq(int q, F&& f, std::integer_sequence<int, I...>) {
-  (void)((q == I + 1 && (f(std::integral_constant<int, I + 1>{}), true)) || ...);
-}
-template <int QMAX, typename F>
-__device__ __forceinline__ void slot_dispatch(int q, F&& f) {
-  slot_dispatch_seq<QMAX>(q, static_cast<F&&>(f), std::make_integer_sequence<int, QMAX>{});
-}
-
-template <int NT, int PMAX>
+template <int NT>
 __device__ __forceinline__ void slot_gemm(const SlotArgs& a, int nrhs, float2* __restrict__ Y) {
-  constexpr int NC = NT * 16;
-  extern __shared__ float4 xs[];  // two buffers of NC columns, S4 float4 each, then the group's terms
-  const int BS = 64 * a.waves;
+  constexpr int NC = NT * 16, OP = OP_F32, AW = OpForm<OP>::AW, PB = OpForm<OP>::PB;
+  extern __shared__ float4 xs4[];  // the term's columns, then the group's terms
+  v4u* xs = reinterpret_cast<v4u*>(xs4);
+  int4* tl = reinterpret_cast<int4*>(xs4 + a.cu);
   const int tid = int(threadIdx.x);
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int j = lane & 15, kr = lane >> 4;
-  const bool odd = (j & 1) != 0;
   const int chunk = int(blockIdx.x);
   const int g = a.order[chunk / a.cpg];
   const int c0 = (chunk % a.cpg) * NC;
   const int nc = min(NC, nrhs - c0);
   const int tb = a.t0[g], te = a.t0[g + 1];
-  const int nM = a.gm[g] / 8;
+  const int Mg = a.gm[g];
   const int m = int(blockIdx.y) * a.waves + wave;
-  const bool act = m < nM;  // wave-uniform: this wave's tile has operator rows
-  const int S4 = a.S4;
-  const int lofs = (j >> 1) * 4 + kr;
+  const bool act = 16 * m < Mg;  // wave-uniform: this wave's tile has operator rows
+  const int rows = min(16, Mg - 16 * m);
 
   struct Tm {
     const float4* A;
     const float2* X;  // column c0 of the source slot
-    int KX, Kg, split, mg;
+    int KX, Kg;
   };
   auto decode = [&](int4 e) {  // e: the term's table entry (wave-uniform)
     e.x = __builtin_amdgcn_readfirstlane(e.x);
     e.y = __builtin_amdgcn_readfirstlane(e.y);
     e.z = __builtin_amdgcn_readfirstlane(e.z);
-    e.w = __builtin_amdgcn_readfirstlane(e.w);
     const int kind = (e.z >> 14) & 1;
     Tm r;
     r.KX = kind ? a.KX1 : a.KX0;
     r.A = (kind ? a.A1 : a.A0) + e.x;
     r.X = (kind ? a.X1 : a.X0) + (int64_t(e.y) * nrhs + c0) * r.KX;
     r.Kg = e.z & 0xFFF;
-    r.split = (e.z >> 12) & 3;
-    r.mg = e.w;
     return r;
   };
-  float4 xv[SLOT_UB];
-  // thread index idx < 2^11 as (column, float4 of the column): idx / (Kg / 2) by
-  // the term's multiplier
-  auto x_load = [&](const Tm& T) {  // this thread's share of the term's columns
-    const int per_col = T.Kg / 2, pcs = per_col / T.split, nel = NC * per_col;
-#pragma unroll
-    for (int u = 0; u < SLOT_UB; ++u) {
-      const int idx = tid + u * BS;
-      xv[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (idx < nel) {
-        const int col = int(__umul24(unsigned(idx), unsigned(T.mg)) >> 23), q4 = idx - col * per_col;
-        if (col < nc)
-          xv[u] = reinterpret_cast<const float4*>(T.X + int64_t(col) * T.KX)[q4 < pcs ? q4 : q4 - pcs];
-      }
-    }
-  };
-  auto x_store = [&](int buf, const Tm& T) {
-    const int per_col = T.Kg / 2, nel = NC * per_col;
-    float4* xb = xs + buf * NC * S4;
-#pragma unroll
-    for (int u = 0; u < SLOT_UB; ++u) {
-      const int idx = tid + u * BS;
-      if (idx < nel) {
-        const int col = int(__umul24(unsigned(idx), unsigned(T.mg)) >> 23), q4 = idx - col * per_col;
-        xb[col * S4 + q4] = xv[u];
-      }
-    }
-  };
-  // this wave's tile of a term's operator (Q4 k-steps from base): pair p holds
-  // k-steps 2p (even lane) and 2p + 1 (odd lane); pairs past the end repeat the
-  // last step, so every load stays inside the tile
-  auto op_pair = [&](const float4* base, int Q4, int p) { return base[min(2 * p + (odd ? 1 : 0), Q4 - 1) * 32]; };
-  double a64[NT][4];
+  double dre[NT][4], dim_[NT][4];
 #pragma unroll
   for (int n = 0; n < NT; ++n)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) a64[n][q] = 0.0;
-  // The products of one term of Q4 k-steps (a compile-time count, so the body
-  // has no branches).  The operator tile lives in one set of registers: as soon
-  // as pair p has been turned into MFMA fragments, the next term's pair p is
-  // loaded into it (a term of Q4n steps from base rn), so that load has a whole
-  // term of products to land.
-  auto compute = [&](auto q4c, float4 (&r)[PMAX], int buf, const float4* rn, int Q4n) {
-    constexpr int Q4 = decltype(q4c)::value;
-    // kr made opaque for each term: otherwise the compiler hoists kr * Q4 for
-    // every length out of the term loop and spills the fourteen offsets
-    int kro = kr;
-    asm volatile("" : "+v"(kro));
-    const float4* bcol = xs + buf * NC * S4 + j * S4 + kro * Q4;
-    v4f acc[NT];
-#pragma unroll
-    for (int n = 0; n < NT; ++n) acc[n] = v4f{0.f, 0.f, 0.f, 0.f};
-    // The workgroup barrier keeps a SIMD's waves in step, so they reach their
-    // staging work (term decode, column loads and stores) together and the
-    // matrix core idles meanwhile; a wave in its products takes issue
-    // priority over one that is staging.
-    __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-    for (int p = 0; p < (Q4 + 1) / 2; ++p) {
-      const float4 v = r[p], w = swap_pair(v);
-      // the complex A fragments as real rows (even row: Re, -Im; odd row: Im, Re)
-      const float a0[4] = {odd ? w.y : v.x, odd ? w.x : -v.y, odd ? w.w : v.z, odd ? w.z : -v.w};
-      const float a1[4] = {odd ? v.y : w.x, odd ? v.x : -w.y, odd ? v.w : w.z, odd ? v.z : -w.w};
-      r[p] = op_pair(rn, Q4n, p);
-      // the scheduler would otherwise move the reload down to the end of the
-      // term, where it can no longer land during the products
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int n = 0; n < NT; ++n) {
-        const float4 b = bcol[n * 16 * S4 + 2 * p];
-        acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[0], b.x, acc[n], 0, 0, 0);
-        acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[1], b.y, acc[n], 0, 0, 0);
-        acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[2], b.z, acc[n], 0, 0, 0);
-        acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[3], b.w, acc[n], 0, 0, 0);
-      }
-      if (2 * p + 1 < Q4) {
-#pragma unroll
-        for (int n = 0; n < NT; ++n) {
-          const float4 b = bcol[n * 16 * S4 + 2 * p + 1];
-          acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[0], b.x, acc[n], 0, 0, 0);
-          acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[1], b.y, acc[n], 0, 0, 0);
-          acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[2], b.z, acc[n], 0, 0, 0);
-          acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[3], b.w, acc[n], 0, 0, 0);
-        }
-      }
-    }
-    __builtin_amdgcn_s_setprio(0);
-    // the next term is longer than this one
-#pragma unroll
-    for (int p = (Q4 + 1) / 2; p < PMAX; ++p) r[p] = op_pair(rn, Q4n, p);
-#pragma unroll
-    for (int n = 0; n < NT; ++n)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) a64[n][q] += double(acc[n][q]);
-  };
-
+    for (int q = 0; q < 4; ++q) dre[n][q] = dim_[n][q] = 0.0;
   if (tb < te) {
     // the group's term table in LDS (decoding a term is then one broadcast read)
-    int4* tl = reinterpret_cast<int4*>(xs + 2 * NC * S4);
-    for (int i = tid; i < te - tb; i += BS) tl[i] = a.terms[tb + i];
+    for (int i = tid; i < te - tb; i += 64 * a.waves) tl[i] = a.terms[tb + i];
     __syncthreads();
-    float4 r[PMAX];
     Tm T = decode(tl[0]);
-    if (act) {
-      const float4* base = T.A + m * (T.Kg / 8 * 32) + lofs;
+    float4 raw[AW];
+    auto tile = [&](const Tm& q) { return OpTile<OP>(OpRows(q.Kg, lane), q.A + m * (2 * q.Kg * AW), rows); };
+    if (act) load_first<OP>(tile(T), raw);
+    for (int t = tb; t < te; ++t) {
+      const Tm Tn = t + 1 < te ? decode(tl[t + 1 - tb]) : T;
+      const int per_col = T.Kg / 2, pad_col = 4 * col_chunks(T.Kg), cs = col_units(T.Kg, PB);
+      __syncthreads();  // the previous term's columns are consumed
+      constexpr int UB = NT == 2 ? 6 : 3;  // columns in flight (6 or more waves stage 32 in one round)
+      for (int q = lane; q < pad_col; q += 64)
+        for (int cb = wave; cb < NC; cb += UB * a.waves) {
+          float4 v[UB];
 #pragma unroll
-      for (int p = 0; p < PMAX; ++p) r[p] = op_pair(base, T.Kg / 8, p);
-    }
-    x_load(T);
-    x_store(0, T);
-    __syncthreads();
-    // Each term first retires every load in flight (its operator tile, loaded
-    // during the previous term) and only then issues the next term's column
-    // loads: without this wait the compiler waits for the prefetch itself
-    // before the first product.  The last term reloads its own tile (a
-    // harmless repeat) so that the body is the same for every term.
-    for (int t = tb, buf = 0;; ++t, buf ^= 1) {
-      const bool more = t + 1 < te;
-      Tm Tn = T;
-      __builtin_amdgcn_s_waitcnt(kWaitVm0);
-      if (more) {
-        Tn = decode(tl[t + 1 - tb]);
-        x_load(Tn);
-      }
-      if (act) {
-        const int Q4n = Tn.Kg / 8;
-        const float4* rn = Tn.A + m * (Q4n * 32) + lofs;
-        slot_dispatch<2 * PMAX>(T.Kg / 8, [&](auto q4c) { compute(q4c, r, buf, rn, Q4n); });
-      }
-      if (more) x_store(buf ^ 1, Tn);
+          for (int u = 0; u < UB; ++u) {
+            const int col = cb + u * a.waves;
+            v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (col < nc && q < per_col) v[u] = reinterpret_cast<const float4*>(T.X + int64_t(col) * T.KX)[q];
+          }
+#pragma unroll
+          for (int u = 0; u < UB; ++u) {
+            const int col = cb + u * a.waves;
+            if (col < NC) stage_pair<OP>(reinterpret_cast<unsigned*>(xs + col * cs), q, v[u]);
+          }
+        }
       __syncthreads();
-      if (!more) break;
+      if (act) {
+        const OpRows o(T.Kg, lane);
+        tile_product<OP, NT>(o, tile(T), tile(Tn), xs + o.j * cs, cs, raw, [&](int n, const StepSums& s, auto merged) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            if constexpr (decltype(merged)::value) dre[n][q] += double(s.p[q]);
+            else dre[n][q] += double(s.p[q] - s.q[q]);
+            dim_[n][q] += double(s.i[q]);
+          }
+        });
+      }
       T = Tn;
     }
   }
-  // lane (j, kr) holds real rows 4 kr .. 4 kr + 3 (complex rows 2 kr, 2 kr + 1) of
-  // tile m for column j of each column tile; tiles past M_g are written as zeros
+  // lane (j, kr) holds rows 4 kr .. 4 kr + 3 of tile m for column j of each column
+  // tile; rows past M_g are written as zeros up to the vector stride
   const int gy = a.gdst ? a.gdst[g] : g;
-  if (m < a.M / 8) {
+  const int row = 16 * m + 4 * (lane >> 4);
+  if (row < a.M) {
+    const bool has = row < Mg;
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
-      const int col = n * 16 + j;
+      const int col = n * 16 + (lane & 15);
       if (col < nc) {
-        float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (act) o = make_float4(float(a64[n][0]), float(a64[n][1]), float(a64[n][2]), float(a64[n][3]));
-        reinterpret_cast<float4*>(Y + (int64_t(gy) * nrhs + c0 + col) * a.M + 8 * m + 2 * kr)[0] = o;
+        float4 w0 = make_float4(0.f, 0.f, 0.f, 0.f), w1 = w0;
+        if (has) {
+          w0 = make_float4(float(dre[n][0]), float(dim_[n][0]), float(dre[n][1]), float(dim_[n][1]));
+          w1 = make_float4(float(dre[n][2]), float(dim_[n][2]), float(dre[n][3]), float(dim_[n][3]));
+        }
+        float4* y = reinterpret_cast<float4*>(Y + (int64_t(gy) * nrhs + c0 + col) * a.M + row);
+        y[0] = w0;
+        y[1] = w1;
       }
     }
   }
@@ -1047,13 +647,14 @@ __device__ __forceinline__ void slot_gemm(const SlotArgs& a, int nrhs, float2* _
 
 // The slot form under two names, so that kernel traces separate the upward
 // transfers (M2M) from the downward pass (M2L pairs and L2L terms of a level).
-template <int NT, int PMAX>
-__global__ void __launch_bounds__(1024) k_m2m_slot(const SlotArgs a, int nrhs, float2* __restrict__ Y) {
-  slot_gemm<NT, PMAX>(a, nrhs, Y);
+constexpr int SLOT_MAXW = 8;  // waves per workgroup
+template <int NT>
+__global__ void __launch_bounds__(64 * SLOT_MAXW, 4) k_m2m_slot(const SlotArgs a, int nrhs, float2* __restrict__ Y) {
+  slot_gemm<NT>(a, nrhs, Y);
 }
-template <int NT, int PMAX>
-__global__ void __launch_bounds__(1024) k_m2l_slot(const SlotArgs a, int nrhs, float2* __restrict__ Y) {
-  slot_gemm<NT, PMAX>(a, nrhs, Y);
+template <int NT>
+__global__ void __launch_bounds__(64 * SLOT_MAXW, 4) k_m2l_slot(const SlotArgs a, int nrhs, float2* __restrict__ Y) {
+  slot_gemm<NT>(a, nrhs, Y);
 }
 
 // ---- U[slot] (+)= sum of Y over the pairs of the slot -------------------------------
@@ -1237,6 +838,9 @@ __global__ void __launch_bounds__(EV_BS) k_leaf_eval(const float4* __restrict__ 
     }
   }
 }
+
+// (x, y) -> (y, x) of a word's two halves
+__device__ __forceinline__ unsigned rot16(unsigned x) { return __builtin_amdgcn_alignbit(x, x, 16); }
 
 // Near field for many right-hand sides (fast plans): per leaf, U[t][k] +=
 // sum_s G(x_t, x_s) F[s][k] as a complex GEMM on MFMA.  A workgroup takes a
@@ -1703,8 +1307,7 @@ struct Launch {        // one grouped-GEMM launch prepared for the current nrhs
   const GGemm* G = nullptr;
   int nt = 4;          // 16-column tiles per workgroup
   int slices = 1;      // M-slices (grid y)
-  int nw = 4;          // waves per workgroup (2 or 4)
-  bool alds = false;   // operator slice staged in LDS (4-wave workgroups)
+  int nw = 4;          // waves per workgroup
   bool m2l = false;    // translation launch (kernel name k_m2l) or tree transfer (k_transfer)
   int64_t nchunks = 0;
   DevBuf grp, col0;
@@ -1714,8 +1317,9 @@ struct Launch {        // one grouped-GEMM launch prepared for the current nrhs
 // tuner finds that faster than the separate launches.
 struct Fused {
   int nt = 0;                 // 16-column tiles per workgroup; 0: separate launches
+  int nw = 4;                 // waves per workgroup
   int64_t nchunks = 0;
-  DevBuf ps, grp, col0;       // per chunk: problem | slice << 4, group, first column
+  DevBuf ps, grp, col0;       // per chunk: problem, group, first column
   std::vector<int64_t> yoff;  // per problem: offset (float2) of its pair outputs in the pair scratch
 };
 
@@ -1725,7 +1329,6 @@ struct SlotLaunch {
   int nt = 1;          // 16-column tiles per workgroup
   int slices = 1;      // M-slices (grid y)
   int waves = 1;       // waves per workgroup
-  int pmax = 8;        // operator pairs per lane held in registers (>= K / 16)
   int cpg = 1;         // column chunks per group
   int64_t nchunks = 0;
 };
@@ -1838,14 +1441,15 @@ static void xcd_order(std::initializer_list<std::vector<int32_t>*> cols) {
   }
 }
 
-// Chunks and grid for one (tile width, M-slices, waves, operator-in-LDS) choice.
-static void prepare_cfg(Launch& L, const GGemm& G, int nrhs, int nt, int slices, int nw = 4, bool alds = false) {
+static bool gg_half(const GGemm& G);
+
+// Chunks and grid for one (tile width, M-slices, waves) choice.
+static void prepare_cfg(Launch& L, const GGemm& G, int nrhs, int nt, int slices, int nw) {
   L.G = &G;
   L.nt = nt;
   L.nw = nw;
-  L.alds = alds;
   std::vector<int32_t> grp, col0;
-  make_chunks(G, nrhs, L.nt * 16, grp, col0);
+  make_chunks(G, nrhs, L.nt == 1 && gg_half(G) ? 8 : L.nt * 16, grp, col0);
   xcd_order({&grp, &col0});
   L.nchunks = int64_t(grp.size());
   L.slices = slices;
@@ -1853,32 +1457,41 @@ static void prepare_cfg(Launch& L, const GGemm& G, int nrhs, int nt, int slices,
   L.col0.upload(col0);
 }
 
+// dynamic LDS limit of the GEMM kernels: 160 KB less 1 KB for their static LDS
+// (the column source table)
+constexpr int kGgDynLds = 159 * 1024;
+
+// operand form of a launch, and its LDS: nt 16-column tiles in their 16-bit planes
+static int gg_form(const GGemm& G) {
+  if (G.prec == DFMM_PREC_FP16X3) return OP_F16;
+  if (G.prec == DFMM_PREC_BF16X3) return OP_BF16;
+  return G.split == 2 ? OP_P4 : OP_F32;
+}
+static size_t gg_lds(const GGemm& G, int nt) {
+  const int pb = gg_form(G) == OP_F32 || gg_form(G) == OP_P4 ? 3 : 2;
+  return size_t(16) * size_t(nt * 16) * size_t(col_units(G.K, pb));
+}
+// 16 columns do not fit LDS (float32 ranks past 846): 8 per chunk
+static bool gg_half(const GGemm& G) { return gg_lds(G, 1) > size_t(kGgDynLds); }
+static size_t gg_lds_used(const GGemm& G, int nt) { return nt == 1 && gg_half(G) ? gg_lds(G, 1) / 2 : gg_lds(G, nt); }
+static bool gg_fits(const GGemm& G, int nt) { return gg_lds_used(G, nt) <= size_t(kGgDynLds); }
+
 // Default choice: narrow tiles when the average group holds few columns; few
 // chunks: split the M-tiles over more workgroups (at least ~4 per CU).
 static void prepare(Launch& L, const GGemm& G, int nrhs) {
   double avg = G.ngroups ? double(G.nvec) * nrhs / double(G.ngroups) : 0.0;
   int nt = avg < 40.0 ? 2 : 4;
+  while (nt > 1 && !gg_fits(G, nt)) nt /= 2;
   int64_t nchunks = 0;
   for (int64_t g = 0; g < G.ngroups; ++g)
     nchunks += (int64_t(G.v0_h[g + 1] - G.v0_h[g]) * nrhs + nt * 16 - 1) / (nt * 16);
-  int nM = G.M / 8;
+  const int nM = (G.M + 15) / 16;
   int max_slices = std::max(1, (nM + 3) / 4);
   int slices = 1;
   while (slices < max_slices && nchunks * slices < 1024) ++slices;
-  prepare_cfg(L, G, nrhs, nt, slices);
+  prepare_cfg(L, G, nrhs, nt, slices, 4);
 }
 
-static size_t gg_lds_bytes(int K, int nt) { return sizeof(float) * size_t(gg_stride(K)) * size_t(nt * 16); }
-static size_t gg_lds_total(int K, int nt, int mt, bool alds) {
-  return gg_lds_bytes(K, nt) + (alds ? size_t(2048) * mt * (K / 8) : 0);  // 4 waves x mt tiles
-}
-
-// dynamic LDS limit of the GEMM kernels: 160 KB less 1 KB for their static LDS
-// (the column source table)
-constexpr int kGgDynLds = 159 * 1024;
-
-// M-tiles per wave of the largest group for a given number of M-slices
-static int gg_mt(const GGemm& G, int slices) { return (G.M / 8 + 4 * slices - 1) / (4 * slices); }
 
 // Raise a GEMM kernel's dynamic LDS limit, once per (kernel, device): the
 // attribute belongs to the device that is current when it is set.
@@ -1893,51 +1506,36 @@ static void ensure_lds_limit(const void* fn) {
   done.insert({fn, dev});
 }
 
-template <int NT, bool ALDS, bool ACC64, int NW, int PREC>
-static void launch_nt_a(const Launch& L, int nrhs, const float2* X, float2* Y, hipStream_t st) {
-  const GGemm& G = *L.G;
-  const size_t lds = gg_lds_total(kpad(G.K, G.prec) * G.split, NT, gg_mt(G, L.slices), ALDS);
-  auto kern = L.m2l ? &k_m2l<NT, ALDS, ACC64, NW, PREC> : &k_transfer<NT, ALDS, ACC64, NW, PREC>;
-  ensure_lds_limit(reinterpret_cast<const void*>(kern));
-  hipLaunchKernelGGL(kern, dim3(unsigned(L.nchunks), unsigned(L.slices)), dim3(64 * NW), lds, st,
-                     G.A.as<float4>(), G.aoff.as<int64_t>(), G.aexp.as<int>(), G.gmk.as<int>(), G.M, G.K, G.split,
-                     G.ops.as<int>(),
-                     G.v0.as<int>(), G.vsrc.as<int>(), G.vdst.as<int>(), L.grp.as<int>(), L.col0.as<int>(), nrhs,
-                     X, Y);
+static GgArgs gg_args(const GGemm& G, const float2* X, float2* Y) {
+  return GgArgs{G.A.as<float4>(), G.aoff.as<int64_t>(), G.aexp.as<int>(), G.gmk.as<int>(), G.ops.as<int>(),
+                G.v0.as<int>(),   G.vsrc.as<int>(),     X,                Y,               G.M,
+                G.K,              gg_half(G) ? 1 : 0};
 }
 
-template <int NT, int PREC>
-static void launch_nt_p(const Launch& L, int nrhs, const float2* X, float2* Y, hipStream_t st) {
-  if (L.nw == 2) launch_nt_a<NT, false, false, 2, PREC>(L, nrhs, X, Y, st);
-  else if (L.alds) launch_nt_a<NT, true, false, 4, PREC>(L, nrhs, X, Y, st);
-  else launch_nt_a<NT, false, false, 4, PREC>(L, nrhs, X, Y, st);
+template <int NT, bool ACC64, int OP>
+static void launch_nt_a(const Launch& L, int nrhs, const float2* X, float2* Y, hipStream_t st) {
+  const GGemm& G = *L.G;
+  auto kern = L.m2l ? &k_m2l<NT, ACC64, OP> : &k_transfer<NT, ACC64, OP>;
+  ensure_lds_limit(reinterpret_cast<const void*>(kern));
+  hipLaunchKernelGGL(kern, dim3(unsigned(L.nchunks), unsigned(L.slices)), dim3(unsigned(64 * L.nw)), gg_lds_used(G, NT), st,
+                     gg_args(G, X, Y), L.grp.as<int>(), L.col0.as<int>(), nrhs);
 }
 
 template <int NT>
 static void launch_nt(const Launch& L, int nrhs, const float2* X, float2* Y, hipStream_t st) {
-  if (L.G->prec == DFMM_PREC_FP16X3) return launch_nt_p<NT, PREC_F16>(L, nrhs, X, Y, st);
-  if (L.G->prec == DFMM_PREC_BF16X3) return launch_nt_p<NT, PREC_BF16>(L, nrhs, X, Y, st);
-  if (L.nw == 2) {
-    if (L.G->acc64) launch_nt_a<NT, false, true, 2, 0>(L, nrhs, X, Y, st);  // precise plans
-    else launch_nt_a<NT, false, false, 2, 0>(L, nrhs, X, Y, st);
-  } else {
-    if (L.G->acc64) launch_nt_a<NT, false, true, 4, 0>(L, nrhs, X, Y, st);
-    else if (L.alds) launch_nt_a<NT, true, false, 4, 0>(L, nrhs, X, Y, st);
-    else launch_nt_a<NT, false, false, 4, 0>(L, nrhs, X, Y, st);
-  }
-}
-
-static bool gg_fits(const GGemm& G, int nt, int slices, bool alds, int nw) {
-  if (alds && (G.acc64 || nw != 4)) return false;
-  return gg_lds_total(kpad(G.K, G.prec) * G.split, nt, gg_mt(G, slices), alds) <= size_t(kGgDynLds);
+  const int op = gg_form(*L.G);
+  if (op == OP_F16) launch_nt_a<NT, false, OP_F16>(L, nrhs, X, Y, st);
+  else if (op == OP_BF16) launch_nt_a<NT, false, OP_BF16>(L, nrhs, X, Y, st);
+  else if (op == OP_P4) launch_nt_a<NT, true, OP_P4>(L, nrhs, X, Y, st);
+  else if (L.G->acc64) launch_nt_a<NT, true, OP_F32>(L, nrhs, X, Y, st);
+  else launch_nt_a<NT, false, OP_F32>(L, nrhs, X, Y, st);
 }
 
 static void launch_gemm(const Launch& L, int nrhs, const float2* X, float2* Y, hipStream_t st) {
   if (L.nchunks == 0) return;
   const GGemm& G = *L.G;
   if (G.T != 1) throw Error{DFMM_EUNSUPPORTED, "grouped GEMM with more than one term per group"};
-  if (!gg_fits(G, L.nt, L.slices, L.alds, L.nw))
-    throw Error{DFMM_EUNSUPPORTED, "skeleton rank too large for the GEMM kernel"};
+  if (!gg_fits(G, L.nt)) throw Error{DFMM_EUNSUPPORTED, "skeleton rank too large for the GEMM kernel"};
   if (L.nt == 4) launch_nt<4>(L, nrhs, X, Y, st);
   else if (L.nt == 3) launch_nt<3>(L, nrhs, X, Y, st);
   else if (L.nt == 2) launch_nt<2>(L, nrhs, X, Y, st);
@@ -1959,27 +1557,24 @@ static bool slot_pays(int nrhs) {
   return 0.92 * padded <= double(nrhs);
 }
 
+// LDS: the column block, then the term table of the longest group
+static size_t slot_col_units(const SlotGemm& S, int nt) { return size_t(nt * 16) * size_t(col_units(S.Kmax, 3)); }
 static size_t slot_lds_bytes(const SlotGemm& S, int nt) {
-  return size_t(2) * size_t(nt * 16) * size_t(gg_stride(S.Kmax)) * sizeof(float) +
-         size_t(S.max_terms) * sizeof(int4);
+  return slot_col_units(S, nt) * 16 + size_t(S.max_terms) * sizeof(int4);
 }
 
-// nt column tiles; one wave per M-tile (at most 16 per workgroup: larger ranks
-// take more M-slices), and enough waves to stage a term's columns
+// nt column tiles; one wave per tile of 16 rows (at most SLOT_MAXW per workgroup:
+// larger ranks take more M-slices)
 static bool prepare_slot(SlotLaunch& L, const SlotGemm& S, int nrhs, int nt) {
   L.S = &S;
   L.nt = nt;
   const int NC = 16 * nt;
   L.cpg = (nrhs + NC - 1) / NC;
   L.nchunks = S.ngroups * L.cpg;
-  const int nMall = std::max(1, S.M / 8);
-  L.slices = (nMall + 15) / 16;
+  const int nMall = std::max(1, (S.M + 15) / 16);
+  L.slices = (nMall + SLOT_MAXW - 1) / SLOT_MAXW;
   L.waves = (nMall + L.slices - 1) / L.slices;
-  const int need = (NC * (S.Kmax / 2) + 64 * SLOT_UB - 1) / (64 * SLOT_UB);
-  L.waves = std::max(L.waves, need);
-  L.pmax = S.Kmax <= 64 ? 4 : (S.Kmax <= 112 ? 7 : 8);
-  return L.waves <= 16 && S.Kmax <= 128 && S.KXmax <= 128 && !S.split2 &&
-         slot_lds_bytes(S, nt) <= size_t(kGgDynLds);
+  return !S.split2 && slot_lds_bytes(S, nt) <= size_t(kGgDynLds);
 }
 
 // The slot form serves fast float32 plans where it pays (DFMM_SLOT=0 forces the
@@ -2008,12 +1603,13 @@ static bool use_slot(const dfmm_plan_s& P, int nrhs) {
   return prepare_slot(tmp, P.lf.down, nrhs, nt);
 }
 
-template <int NT, int PMAX>
+template <int NT>
 static void launch_slot_t(const SlotLaunch& L, const SlotArgs& a, int nrhs, float2* Y, bool m2l, hipStream_t st) {
   const size_t lds = slot_lds_bytes(*L.S, NT);
-  auto kern = m2l ? &k_m2l_slot<NT, PMAX> : &k_m2m_slot<NT, PMAX>;
+  auto kern = m2l ? &k_m2l_slot<NT> : &k_m2m_slot<NT>;
   ensure_lds_limit(reinterpret_cast<const void*>(kern));
-  hipLaunchKernelGGL(kern, dim3(unsigned(L.nchunks), unsigned(L.slices)), dim3(64 * L.waves), lds, st, a, nrhs, Y);
+  hipLaunchKernelGGL(kern, dim3(unsigned(L.nchunks), unsigned(L.slices)), dim3(unsigned(64 * L.waves)), lds, st, a,
+                     nrhs, Y);
 }
 
 // kind 0: operators A0 on source vectors X0 (row stride KX0); kind 1 likewise
@@ -2023,16 +1619,9 @@ static void launch_slot(const SlotLaunch& L, const float4* A0, const float2* X0,
   if (L.nchunks == 0) return;
   const SlotGemm& S = *L.S;
   SlotArgs a{S.order.as<int>(), S.t0.as<int>(), S.gm.as<int>(), S.terms.as<int4>(), A0, A1 ? A1 : A0, X0,
-             X1 ? X1 : X0, KX0, X1 ? KX1 : KX0, S.M, L.cpg, gg_stride(S.Kmax) / 4, L.waves, gdst};
-  if (L.nt == 2) {
-    if (L.pmax == 4) launch_slot_t<2, 4>(L, a, nrhs, Y, m2l, st);
-    else if (L.pmax == 7) launch_slot_t<2, 7>(L, a, nrhs, Y, m2l, st);
-    else launch_slot_t<2, 8>(L, a, nrhs, Y, m2l, st);
-  } else {
-    if (L.pmax == 4) launch_slot_t<1, 4>(L, a, nrhs, Y, m2l, st);
-    else if (L.pmax == 7) launch_slot_t<1, 7>(L, a, nrhs, Y, m2l, st);
-    else launch_slot_t<1, 8>(L, a, nrhs, Y, m2l, st);
-  }
+             X1 ? X1 : X0, KX0, X1 ? KX1 : KX0, S.M, L.cpg, int(slot_col_units(S, L.nt)), L.waves, gdst};
+  if (L.nt == 2) launch_slot_t<2>(L, a, nrhs, Y, m2l, st);
+  else launch_slot_t<1>(L, a, nrhs, Y, m2l, st);
 }
 
 static void prepare_slot_set(const dfmm_plan_s& P, int nrhs, LaunchSet& LS) {
@@ -2058,7 +1647,7 @@ static bool fused_fits(const dfmm_plan_s& P, int nt) {
   const auto probs = m2l_problems(P);
   if (P.precise || probs.size() < 2 || probs.size() > size_t(kMaxProbs)) return false;
   for (const GGemm* G : probs)
-    if (G->T != 1 || !gg_fits(*G, nt, 1, false, 4)) return false;
+    if (G->T != 1 || !gg_fits(*G, nt)) return false;
   return true;
 }
 
@@ -2069,7 +1658,7 @@ static void prepare_fused(const dfmm_plan_s& P, int nrhs, int nt, Fused& F) {
   int64_t off = pair_rows_transfer(P) * nrhs;  // past the transfers' scratch
   for (size_t i = 0; i < probs.size(); ++i) {
     std::vector<int32_t> g1, c1;
-    make_chunks(*probs[i], nrhs, nt * 16, g1, c1);
+    make_chunks(*probs[i], nrhs, nt == 1 && gg_half(*probs[i]) ? 8 : nt * 16, g1, c1);
     for (size_t k = 0; k < g1.size(); ++k) {
       ps.push_back(int32_t(i));
       grp.push_back(g1[k]);
@@ -2080,24 +1669,27 @@ static void prepare_fused(const dfmm_plan_s& P, int nrhs, int nt, Fused& F) {
   }
   xcd_order({&ps, &grp, &col0});
   F.nt = nt;
+  int nM = 1;
+  for (const GGemm* G : probs) nM = std::max(nM, (G->M + 15) / 16);
+  F.nw = std::max(std::min(nM, GG_MAXW), 4);  // a wave per row tile
   F.nchunks = int64_t(ps.size());
   F.ps.upload(ps);
   F.grp.upload(grp);
   F.col0.upload(col0);
 }
 
-template <int NT, int PREC>
+template <int NT, int OP>
 static void launch_fused_t(const GgProbs& pr, size_t lds, const Fused& F, int nrhs, hipStream_t st) {
-  ensure_lds_limit(reinterpret_cast<const void*>(&k_m2l_fused<NT, 4, PREC>));
-  hipLaunchKernelGGL((k_m2l_fused<NT, 4, PREC>), dim3(unsigned(F.nchunks)), dim3(256), lds, st, pr, F.ps.as<int>(),
-                     F.grp.as<int>(), F.col0.as<int>(), nrhs);
+  ensure_lds_limit(reinterpret_cast<const void*>(&k_m2l_fused<NT, OP>));
+  hipLaunchKernelGGL((k_m2l_fused<NT, OP>), dim3(unsigned(F.nchunks)), dim3(unsigned(64 * F.nw)), lds, st, pr,
+                     F.ps.as<int>(), F.grp.as<int>(), F.col0.as<int>(), nrhs);
 }
 
-template <int PREC>
+template <int OP>
 static void launch_fused_p(const GgProbs& pr, size_t lds, const Fused& F, int nrhs, hipStream_t st) {
-  if (F.nt == 4) launch_fused_t<4, PREC>(pr, lds, F, nrhs, st);
-  else if (F.nt == 2) launch_fused_t<2, PREC>(pr, lds, F, nrhs, st);
-  else launch_fused_t<1, PREC>(pr, lds, F, nrhs, st);
+  if (F.nt == 4) launch_fused_t<4, OP>(pr, lds, F, nrhs, st);
+  else if (F.nt == 2) launch_fused_t<2, OP>(pr, lds, F, nrhs, st);
+  else launch_fused_t<1, OP>(pr, lds, F, nrhs, st);
 }
 
 // X of problem i: the level's outgoing potentials (the leaves' for the leaf level)
@@ -2110,55 +1702,51 @@ static void launch_fused(const dfmm_plan_s& P, const Ws& S, const Fused& F, int 
   for (size_t i = 0; i < probs.size(); ++i) {
     const GGemm& G = *probs[i];
     const float2* X = level[i] >= 0 ? S.F[size_t(level[i])].as<float2>() : S.flf.as<float2>();
-    pr.p[i] = GgProb{G.A.as<float4>(), G.aoff.as<int64_t>(), G.aexp.as<int>(), G.gmk.as<int>(), G.ops.as<int>(),
-                     G.v0.as<int>(), G.vsrc.as<int>(), G.vdst.as<int>(), X, S.Y.as<float2>() + F.yoff[i], G.M,
-                     G.K, G.split, 1};
-    lds = std::max(lds, gg_lds_total(kpad(G.K, G.prec) * G.split, F.nt, gg_mt(G, 1), false));
+    pr.p[i] = gg_args(G, X, S.Y.as<float2>() + F.yoff[i]);
+    lds = std::max(lds, gg_lds_used(G, F.nt));
   }
-  if (P.prec == DFMM_PREC_FP16X3) launch_fused_p<PREC_F16>(pr, lds, F, nrhs, st);
-  else if (P.prec == DFMM_PREC_BF16X3) launch_fused_p<PREC_BF16>(pr, lds, F, nrhs, st);
-  else launch_fused_p<0>(pr, lds, F, nrhs, st);
+  if (P.prec == DFMM_PREC_FP16X3) launch_fused_p<OP_F16>(pr, lds, F, nrhs, st);
+  else if (P.prec == DFMM_PREC_BF16X3) launch_fused_p<OP_BF16>(pr, lds, F, nrhs, st);
+  else launch_fused_p<OP_F32>(pr, lds, F, nrhs, st);
 }
 
-// Tile autotuner: time every (tile width, M-slices, waves per workgroup,
-// operator-in-LDS) candidate of one launch on the apply stream (its output goes
-// to the pair scratch Y only) and keep the fastest.  Runs once per plan and nrhs.
+// Tile autotuner: time every (tile width, M-slices, waves per workgroup)
+// candidate of one launch on the apply stream (its output goes to the pair
+// scratch Y only) and keep the fastest.  Runs once per plan and nrhs.
 static void autotune(Launch& L, const GGemm& G, int nrhs, const float2* X, float2* Y, hipStream_t st) {
   prepare(L, G, nrhs);
   if (G.ngroups == 0) return;
   const char* env = std::getenv("DFMM_AUTOTUNE");
   if (env && env[0] == '0') return;
-  const int nM = G.M / 8;
+  const int nM = (G.M + 15) / 16;
   hipEvent_t e0, e1;
   DFMM_HIP(hipEventCreate(&e0));
   DFMM_HIP(hipEventCreate(&e1));
   float best = 1e30f;
   int best_nt = L.nt, best_sl = L.slices, best_nw = L.nw;
-  bool best_alds = false;
-  for (int nw : {4, 2})
-  for (int alds = 0; alds < 2; ++alds)
-  for (int nt : {1, 2, 3, 4})
-    for (int sl = 1; sl <= std::min(std::max(1, (nM + nw - 1) / nw), 4); ++sl) {
-      if (!gg_fits(G, nt, sl, alds != 0, nw)) continue;
-      prepare_cfg(L, G, nrhs, nt, sl, nw, alds != 0);
-      launch_gemm(L, nrhs, X, Y, st);  // warm-up
-      DFMM_HIP(hipEventRecord(e0, st));
-      for (int i = 0; i < 3; ++i) launch_gemm(L, nrhs, X, Y, st);
-      DFMM_HIP(hipEventRecord(e1, st));
-      DFMM_HIP(hipEventSynchronize(e1));
-      float ms = 0.f;
-      DFMM_HIP(hipEventElapsedTime(&ms, e0, e1));
-      if (ms < best) {
-        best = ms;
-        best_nt = nt;
-        best_sl = sl;
-        best_nw = nw;
-        best_alds = alds != 0;
+  for (int nw : {8, 7, 6, 4, 2})
+    for (int nt : {1, 2, 3, 4})
+      for (int sl = 1; sl <= std::min((nM + nw - 1) / nw, 4); ++sl) {
+        if (nw > 4 && nw != std::min(nM, GG_MAXW)) continue;  // 6 to 8 waves: one per row tile
+        if (!gg_fits(G, nt)) continue;
+        prepare_cfg(L, G, nrhs, nt, sl, nw);
+        launch_gemm(L, nrhs, X, Y, st);  // warm-up
+        DFMM_HIP(hipEventRecord(e0, st));
+        for (int i = 0; i < 3; ++i) launch_gemm(L, nrhs, X, Y, st);
+        DFMM_HIP(hipEventRecord(e1, st));
+        DFMM_HIP(hipEventSynchronize(e1));
+        float ms = 0.f;
+        DFMM_HIP(hipEventElapsedTime(&ms, e0, e1));
+        if (ms < best) {
+          best = ms;
+          best_nt = nt;
+          best_sl = sl;
+          best_nw = nw;
+        }
       }
-    }
   DFMM_HIP(hipEventDestroy(e0));
   DFMM_HIP(hipEventDestroy(e1));
-  prepare_cfg(L, G, nrhs, best_nt, best_sl, best_nw, best_alds);
+  prepare_cfg(L, G, nrhs, best_nt, best_sl, best_nw);
 }
 
 // The sizes the workspace of a plan depends on.
@@ -2221,7 +1809,7 @@ static void ensure_workspace(ApplyState& S, size_t bytes) {
   S.buf.alloc(bytes);
 }
 
-// ---- tuning record: the chosen (tile width, M-slices, LDS operator) per launch,
+// ---- tuning record: the chosen (tile width, M-slices, waves) per launch,
 // kept in the plan's cache directory under a key of the launch shapes, nrhs and
 // the device, so that later plans of the same shape skip the trial launches.
 static void fnv(uint64_t& h, const void* p, size_t n) {
@@ -2240,6 +1828,8 @@ static std::string tune_path(const dfmm_plan_s& P, const std::vector<const GGemm
   fnv(h, prop.gcnArchName, std::strlen(prop.gcnArchName));
   fnv(h, &prop.multiProcessorCount, sizeof(prop.multiProcessorCount));
   fnv(h, &nrhs, sizeof(nrhs));
+  const int engine = 2;  // 1: the float32 MFMA engine, whose choices say nothing about this one
+  fnv(h, &engine, sizeof(engine));
   for (const GGemm* g : gs) {
     const int64_t dims[8] = {g->M, g->K, g->T, g->ngroups, g->nvec, g->split, int64_t(g->acc64), g->prec};
     fnv(h, dims, sizeof(dims));
@@ -2259,9 +1849,9 @@ static bool load_tuning(const std::string& path, std::vector<Launch*>& ls, const
   bool ok = std::fscanf(fp, "dfmm-tune 4 %d", &n) == 1 && n == int(ls.size());
   std::vector<int> v(4 * size_t(std::max(n, 0)));
   for (int i = 0; ok && i < n; ++i) {
-    int* c = &v[4 * size_t(i)];  // tile width, M-slices, operator in LDS, waves
+    int* c = &v[4 * size_t(i)];  // tile width, M-slices, (unused), waves
     ok = std::fscanf(fp, "%d %d %d %d", &c[0], &c[1], &c[2], &c[3]) == 4;
-    ok = ok && c[0] >= 1 && c[0] <= 4 && c[1] >= 1 && c[1] <= 64 && (c[3] == 2 || c[3] == 4);
+    ok = ok && c[0] >= 1 && c[0] <= 4 && c[1] >= 1 && c[1] <= 64 && c[3] >= GG_MINW && c[3] <= GG_MAXW;
   }
   ok = ok && std::fscanf(fp, " fused %d", fused_nt) == 1 &&
        (*fused_nt == 0 || *fused_nt == 1 || *fused_nt == 2 || *fused_nt == 4);
@@ -2269,8 +1859,8 @@ static bool load_tuning(const std::string& path, std::vector<Launch*>& ls, const
   if (!ok) return false;
   for (int i = 0; i < n; ++i) {
     const int* c = &v[4 * size_t(i)];
-    if (!gg_fits(*gs[i], c[0], c[1], c[2] != 0, c[3])) return false;
-    prepare_cfg(*ls[i], *gs[i], nrhs, c[0], c[1], c[3], c[2] != 0);
+    if (!gg_fits(*gs[i], c[0])) return false;
+    prepare_cfg(*ls[i], *gs[i], nrhs, c[0], c[1], c[3]);
   }
   return true;
 }
@@ -2281,7 +1871,7 @@ static void save_tuning(const std::string& path, const std::vector<Launch*>& ls,
   FILE* fp = std::fopen(tmp.c_str(), "w");
   if (!fp) return;  // the record is an optimisation only
   std::fprintf(fp, "dfmm-tune 4 %d\n", int(ls.size()));
-  for (const Launch* L : ls) std::fprintf(fp, "%d %d %d %d\n", L->nt, L->slices, L->alds ? 1 : 0, L->nw);
+  for (const Launch* L : ls) std::fprintf(fp, "%d %d 0 %d\n", L->nt, L->slices, L->nw);
   std::fprintf(fp, "fused %d\n", fused_nt);
   const bool ok = std::fclose(fp) == 0;
   if (ok) std::rename(tmp.c_str(), path.c_str());
@@ -2400,7 +1990,7 @@ static void inherit_launches(dfmm_plan_s& P, int nrhs, const LaunchSet& from, La
   LS.l2l.resize(P.hf.size());
   LS.m2l.resize(P.hf.size());
   auto take = [&](Launch& L, const Launch& F, const GGemm& G) {
-    prepare_cfg(L, G, nrhs, F.nt, F.slices, F.nw, F.alds);
+    prepare_cfg(L, G, nrhs, F.nt, F.slices, F.nw);
     L.m2l = F.m2l;
   };
   for (size_t e = 0; e < P.hf.size(); ++e) {

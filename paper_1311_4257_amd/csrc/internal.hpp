@@ -169,24 +169,8 @@ void build_slot_gemm(SlotGemm& S, int M, int64_t ngroups, const std::vector<int3
                      const std::vector<SlotTerm>& terms, const SlotKind kinds[2], int kx_max);
 
 // Pack an M x K complex matrix (row-major, interleaved float64) into the
-// fragment order read by the GEMM kernel.
-void pack_operator(const double* Tc, int M, int K, float* out);
-// pack_operator of T (split = 1) or of [T_hi | T_lo] (split = 2), T_hi the float32
-// rounding of T and T_lo that of the remainder; out holds 2 M K split floats
-void pack_operator_split(const double* Tc, int M, int K, int split, float* out);
-// K of a packed operator: a multiple of 16 for the 16-bit MFMA (two k-steps per instruction)
-inline int kpad(int K, int prec) {
-  return (prec == DFMM_PREC_FP16X3 || prec == DFMM_PREC_BF16X3) ? (K + 15) / 16 * 16 : K;
-}
-// pack_operator in float64: the same fragment order, double4 in place of float4
+// fragment order of the float64 GEMM kernel
 void pack_operator64(const double* Tc, int M, int K, double* out);
-// Convert nops packed float32 operators (stride floats apart) in place to the
-// hi + lo 16-bit format of prec: each float4 slot (re0, im0, re1, im1) becomes
-// four 32-bit words (hi re0 | hi im0), (hi re1 | hi im1), (lo re0 | lo im0),
-// (lo re1 | lo im1), low half first.  FP16X3 first scales operator i by
-// 2^aexp[i] so that its largest entry is below 2^14.
-void to_half_ops(std::vector<float>& A, int64_t nops, int64_t stride, int prec, std::vector<int32_t>& aexp);
-
 // ---- one HF level of the plan -------------------------------------------------
 struct HFLevel {
   int l = 0;      // tree level

@@ -127,23 +127,24 @@ AdaptiveLevels adaptive_levels(const Tree& T, int D, int leaf_max) {
 
 }  // namespace
 
-// Fragment order of an M x K complex operator for the MFMA kernel: for M-tile
-// m (8 complex rows), step s4 (K / 8 of them), row-in-tile ql (8) and K quarter
-// kr (4), one float4 holds the two complex entries (q, p0) and (q, p0 + 1) with
-// q = 8 m + ql and p0 = kr K / 4 + 2 s4.
-void pack_operator(const double* Tc, int M, int K, float* out) {
-  int nm = M / 8, ns = K / 8;
-  for (int m = 0; m < nm; ++m)
-    for (int s4 = 0; s4 < ns; ++s4)
-      for (int ql = 0; ql < 8; ++ql)
-        for (int kr = 0; kr < 4; ++kr) {
-          int q = 8 * m + ql, p0 = kr * (K / 4) + 2 * s4;
-          float* o = out + 4 * ((((size_t(m) * ns + s4) * 8 + ql) * 4) + kr);
-          o[0] = float(Tc[2 * (size_t(q) * K + p0)]);
-          o[1] = float(Tc[2 * (size_t(q) * K + p0) + 1]);
-          o[2] = float(Tc[2 * (size_t(q) * K + p0 + 1)]);
-          o[3] = float(Tc[2 * (size_t(q) * K + p0 + 1) + 1]);
-        }
+// Storage of an M x K complex operator (M, K multiples of 8) for the GEMM kernels:
+// tiles of 16 rows (the last of 8 where M ends on a half tile), each in steps of
+// four chunks of 8 complex k (the last step holds what is left), each step as
+// AW float4 per (row, chunk): float4 t of chunk c of row j at (t nc + c) rows + j,
+// nc chunks in the step, so that a wave's load t is one run over its rows.
+static size_t op_slot(int M, int K, int AW, int q, int c, int t) {
+  const int m = q / 16, rows = std::min(16, M - 16 * m), s = c / 4, nc = std::min(4, K / 8 - 4 * s);
+  return size_t(m) * size_t(2 * K * AW) + size_t(s) * size_t(4 * AW * rows) +
+         (size_t(t) * size_t(nc) + size_t(c - 4 * s)) * size_t(rows) + size_t(q % 16);
+}
+
+// float32: float4 t holds the complex entries 2 t and 2 t + 1 of its chunk
+static void pack_operator(const double* Tc, int M, int K, float* out) {
+  for (int q = 0; q < M; ++q)
+    for (int c = 0; c < K / 8; ++c)
+      for (int t = 0; t < 4; ++t)
+        for (int e = 0; e < 4; ++e)
+          out[4 * op_slot(M, K, 4, q, c, t) + size_t(e)] = float(Tc[2 * (size_t(q) * K + 8 * c + 2 * t) + size_t(e)]);
 }
 
 void pack_operator64(const double* Tc, int M, int K, double* out) {
@@ -159,45 +160,6 @@ void pack_operator64(const double* Tc, int M, int K, double* out) {
           o[2] = Tc[2 * (size_t(q) * K + p0 + 1)];
           o[3] = Tc[2 * (size_t(q) * K + p0 + 1) + 1];
         }
-}
-
-namespace {
-// Packed operators of one launch, float32 (fragment order of the float32 and
-// 16-bit engines) or float64 (float64 plans); entries at the same offsets.
-struct OpStore {
-  bool f64;
-  std::vector<float> f;
-  std::vector<double> d;
-  OpStore(bool f64_, size_t n) : f64(f64_) {
-    if (f64) d.assign(n, 0.0);
-    else f.assign(n, 0.0f);
-  }
-  void pack(const double* T, int M, int K, int split, size_t off) {
-    if (f64) pack_operator64(T, M, K, d.data() + off);
-    else pack_operator_split(T, M, K, split, f.data() + off);
-  }
-  void upload(DevBuf& b) {
-    if (f64) b.upload(d);
-    else b.upload(f);
-  }
-};
-}  // namespace
-
-void pack_operator_split(const double* Tc, int M, int K, int split, float* out) {
-  if (split == 1) {
-    pack_operator(Tc, M, K, out);
-    return;
-  }
-  std::vector<double> T2(size_t(2) * M * 2 * K);
-  for (int q = 0; q < M; ++q)
-    for (int p = 0; p < K; ++p)
-      for (int c = 0; c < 2; ++c) {
-        const double v = Tc[2 * (size_t(q) * K + p) + c];
-        const double hi = double(float(v));
-        T2[2 * (size_t(q) * 2 * K + p) + c] = hi;
-        T2[2 * (size_t(q) * 2 * K + K + p) + c] = v - hi;
-      }
-  pack_operator(T2.data(), M, 2 * K, out);
 }
 
 // float32 -> IEEE binary16 bits, round to nearest even (subnormals kept; the
@@ -249,39 +211,66 @@ static float bf16_to_f32(uint16_t h) {
   return v;
 }
 
-void to_half_ops(std::vector<float>& A, int64_t nops, int64_t stride, int prec, std::vector<int32_t>& aexp) {
-  aexp.assign(size_t(nops), 0);
-  parallel_for(nops, [&](int64_t i) {
-    float* a = A.data() + size_t(i) * size_t(stride);
-    int e = 0;
-    if (prec == DFMM_PREC_FP16X3) {
-      float mx = 0.0f;
-      for (int64_t k = 0; k < stride; ++k) mx = std::max(mx, std::fabs(a[k]));
-      if (mx > 0.0f) {
-        int E = 0;
-        (void)std::frexp(mx, &E);  // mx < 2^E
-        e = 14 - E;
-      }
+// Planes of 16-bit values: unit 2 p + part (Re, Im) of a (row, chunk) holds plane p
+// of its 8 complex entries.  FP16X3 / BF16X3: 2 planes of the float32 operator,
+// FP16X3 scaled by 2^(*aexp) so that its largest entry is below 2^14.  Precise
+// plans (prec FP32): 4 bfloat16 planes (32 bits) of the float64 operator.
+static void pack_operator_planes(const double* Tc, int M, int K, int prec, float* out, int32_t* aexp) {
+  const int P = prec == DFMM_PREC_FP32 ? 4 : 2;
+  int e = 0;
+  if (prec == DFMM_PREC_FP16X3) {
+    float mx = 0.0f;
+    for (size_t k = 0; k < size_t(2) * M * K; ++k) mx = std::max(mx, std::fabs(float(Tc[k])));
+    if (mx > 0.0f) {
+      int E = 0;
+      (void)std::frexp(mx, &E);  // mx < 2^E
+      e = 14 - E;
     }
-    aexp[size_t(i)] = e;
-    for (int64_t k = 0; k < stride; k += 4) {
-      uint16_t hi[4], lo[4];
-      for (int c = 0; c < 4; ++c) {
-        const float v = std::ldexp(a[k + c], e);
-        if (prec == DFMM_PREC_FP16X3) {
-          hi[c] = f32_to_f16(v);
-          lo[c] = f32_to_f16(v - f16_to_f32(hi[c]));
-        } else {
-          hi[c] = f32_to_bf16(v);
-          lo[c] = f32_to_bf16(v - bf16_to_f32(hi[c]));
+  }
+  *aexp = e;
+  uint16_t* h = reinterpret_cast<uint16_t*>(out);
+  for (int q = 0; q < M; ++q)
+    for (int c = 0; c < K / 8; ++c)
+      for (int k = 0; k < 8; ++k)
+        for (int part = 0; part < 2; ++part) {
+          const double x = Tc[2 * (size_t(q) * K + 8 * c + k) + size_t(part)];
+          double v = P == 4 ? x : double(std::ldexp(float(x), e));
+          for (int p = 0; p < P; ++p) {
+            uint16_t w;
+            if (prec == DFMM_PREC_FP16X3) {
+              w = f32_to_f16(float(v));
+              v -= double(f16_to_f32(w));
+            } else {
+              w = f32_to_bf16(float(v));
+              v -= double(bf16_to_f32(w));
+            }
+            h[8 * op_slot(M, K, 2 * P, q, c, 2 * p + part) + size_t(k)] = w;
+          }
         }
-      }
-      const uint32_t w[4] = {uint32_t(hi[0]) | uint32_t(hi[1]) << 16, uint32_t(hi[2]) | uint32_t(hi[3]) << 16,
-                             uint32_t(lo[0]) | uint32_t(lo[1]) << 16, uint32_t(lo[2]) | uint32_t(lo[3]) << 16};
-      std::memcpy(a + k, w, 16);
-    }
-  });
 }
+
+// Packed operators of one launch: float32, 16-bit planes (16-bit plans, and the
+// split operators of precise plans) or float64 (float64 plans).
+struct OpStore {
+  int prec;
+  std::vector<float> f;
+  std::vector<double> d;
+  std::vector<int32_t> aexp;  // FP16X3: scale exponent of each operator
+  OpStore(int prec_, size_t n, int64_t nops) : prec(prec_), aexp(size_t(nops), 0) {
+    if (prec == DFMM_PREC_FP64) d.assign(n, 0.0);
+    else f.assign(n, 0.0f);
+  }
+  void pack(const double* T, int M, int K, int split, size_t off, int64_t op) {
+    if (prec == DFMM_PREC_FP64) pack_operator64(T, M, K, d.data() + off);
+    else if (prec == DFMM_PREC_FP32 && split == 1) pack_operator(T, M, K, f.data() + off);
+    else pack_operator_planes(T, M, K, prec, f.data() + off, &aexp[size_t(op)]);
+  }
+  void upload(GGemm& G) {
+    if (prec == DFMM_PREC_FP64) G.A.upload(d);
+    else G.A.upload(f);
+    if (prec == DFMM_PREC_FP16X3 || prec == DFMM_PREC_BF16X3) G.aexp.upload(aexp);
+  }
+};
 
 void build_slot_gemm(SlotGemm& S, int M, int64_t ngroups, const std::vector<int32_t>& gM,
                      const std::vector<SlotTerm>& terms, const SlotKind kinds[2], int kx_max) {
@@ -311,10 +300,7 @@ void build_slot_gemm(SlotGemm& S, int M, int64_t ngroups, const std::vector<int3
     e[0] = int32_t(aoff);
     e[1] = t.src;
     e[2] = kp | (k.split << 12) | (t.kind << 14);
-    // column staging divides a thread's index (< 2^11) by the term's float4 per
-    // column (kp / 2 < 2^11): the quotient is (idx * e[3]) >> 23 exactly for
-    // e[3] = ceil(2^23 / (kp / 2)), since idx times the rounding excess is < 2^23
-    e[3] = int32_t(((1u << 23) + uint32_t(kp / 2) - 1) / uint32_t(kp / 2));
+    e[3] = 0;
     kmax = std::max(kmax, kp);
     S.split2 = S.split2 || k.split != 1;
     S.flops[t.kind] += k.G->opflops[size_t(t.op)];
@@ -372,7 +358,6 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
   dfmm_info& info = P.info;
   std::memset(&info, 0, sizeof(info));
   const bool fp64 = P.prec == DFMM_PREC_FP64;  // float64 operators and vectors
-  const bool half = P.prec == DFMM_PREC_FP16X3 || P.prec == DFMM_PREC_BF16X3;
   info.N = N;
   info.K = K;
   info.depth = D;
@@ -700,8 +685,7 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
     }
     std::vector<int32_t> vdst(vsrc.size());
     for (size_t i = 0; i < vdst.size(); ++i) vdst[i] = int32_t(i);
-    const int RK = kpad(R, P.prec);  // packed K of every operator of the launch
-    OpStore At(fp64, size_t(2) * R * RK * split * ngroups);
+    OpStore At(P.prec, size_t(2) * R * R * split * ngroups, ngroups);
     std::vector<int32_t> gmk(size_t(2) * ngroups);
     std::vector<int64_t> aoff(ngroups);
     parallel_for(ngroups, [&](int64_t gi) {
@@ -712,10 +696,9 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
              sz = double(std::get<2>(keys[gi])) * w;
       const int Mg = pad8(si->r), Kg = pad8(so->r);
       gmk[2 * gi] = Mg;
-      gmk[2 * gi + 1] = Kg * split;
-      aoff[gi] = int64_t(gi) * R * RK * split / 2;
-      const int Kp = kpad(Kg, P.prec);
-      std::vector<double> G(size_t(2) * so->r), T(size_t(2) * Mg * Kp, 0.0);
+      gmk[2 * gi + 1] = Kg;
+      aoff[gi] = int64_t(gi) * R * R * split / 2;
+      std::vector<double> G(size_t(2) * so->r), T(size_t(2) * Mg * Kg, 0.0);
       for (int q = 0; q < si->r; ++q) {
         for (int p = 0; p < so->r; ++p)
           green64(si->b[3 * q] - (sx + so->b[3 * p]), si->b[3 * q + 1] - (sy + so->b[3 * p + 1]),
@@ -728,17 +711,12 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
             re += gr * dr - gi2 * di;
             im += gr * di + gi2 * dr;
           }
-          T[2 * (size_t(q) * Kp + j)] = re;
-          T[2 * (size_t(q) * Kp + j) + 1] = im;
+          T[2 * (size_t(q) * Kg + j)] = re;
+          T[2 * (size_t(q) * Kg + j) + 1] = im;
         }
       }
-      At.pack(T.data(), Mg, Kp, split, size_t(2) * R * RK * split * gi);
+      At.pack(T.data(), Mg, Kg, split, size_t(2) * R * R * split * gi, gi);
     });
-    if (half) {
-      std::vector<int32_t> aexp;
-      to_half_ops(At.f, ngroups, int64_t(2) * R * RK * split, P.prec, aexp);
-      G.aexp.upload(aexp);
-    }
     G.prec = P.prec;
     G.M = R;
     G.K = R;
@@ -748,7 +726,7 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
     G.ngroups = ngroups;
     G.nvec = int64_t(vsrc.size());
     G.nops = ngroups;
-    At.upload(G.A);
+    At.upload(G);
     G.aoff.upload(aoff);
     G.gmk.upload(gmk);
     G.ops.upload(opsv);
@@ -760,7 +738,7 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
     G.kpk_h.resize(size_t(ngroups));
     G.opflops.resize(size_t(ngroups));
     for (int64_t gi = 0; gi < ngroups; ++gi) {
-      G.kpk_h[size_t(gi)] = kpad(gmk[2 * gi + 1] / split, P.prec) * split;
+      G.kpk_h[size_t(gi)] = gmk[2 * gi + 1];
       const PairRec& r = pr[rep[gi]];
       G.opflops[size_t(gi)] = 8.0 * skin[r.din < 0 ? 0 : r.din]->r * skin[r.dout < 0 ? 0 : r.dout]->r;
     }
@@ -816,9 +794,9 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
     // G(b^c + delta_o, a^{w,l}) (D^{w,l})^T (Rc x R) maps the parent's incoming
     // check potentials to the child's (c = the child skeleton of wedge l).
     int ndir = int(6 * w * w);
-    const int KU = kpad(H.Rc, P.prec), KD = kpad(H.R, P.prec);  // packed K of the up / down operators
-    OpStore Mu(fp64, size_t(2) * ndir * 8 * H.R * KU * hf_split);
-    OpStore Md(fp64, size_t(2) * ndir * 8 * H.Rc * KD * hf_split);
+    const int64_t per_op = int64_t(2) * H.R * H.Rc * hf_split;  // storage of one operator, up or down
+    OpStore Mu(P.prec, size_t(per_op) * ndir * 8, int64_t(ndir) * 8);
+    OpStore Md(P.prec, size_t(per_op) * ndir * 8, int64_t(ndir) * 8);
     std::vector<char> dir_used(ndir, 0);
     for (auto& s : OS[l].list) dir_used[s.second] = 1;
     for (auto& s : IS[l].list) dir_used[s.second] = 1;
@@ -841,8 +819,7 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
       op_ms[id] = Ms;
       op_mc[id] = Mc;
       op_fl[id] = 8.0 * s.r * c.r;
-      const int Kpu = kpad(Mc, P.prec), Kpd = kpad(Ms, P.prec);
-      std::vector<double> up(size_t(2) * Ms * Kpu, 0.0), dn(size_t(2) * Mc * Kpd, 0.0);
+      std::vector<double> up(size_t(2) * Ms * Mc, 0.0), dn(size_t(2) * Mc * Ms, 0.0);
       for (int p = 0; p < s.r; ++p)
         for (int k = 0; k < c.r; ++k) {  // (G D^c)[p][k]
           double re = 0.0, im = 0.0;
@@ -852,8 +829,8 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
             re += gr * dr - gi * di;
             im += gr * di + gi * dr;
           }
-          up[2 * (size_t(p) * Kpu + k)] = re;
-          up[2 * (size_t(p) * Kpu + k) + 1] = im;
+          up[2 * (size_t(p) * Mc + k)] = re;
+          up[2 * (size_t(p) * Mc + k) + 1] = im;
         }
       for (int j = 0; j < c.r; ++j)
         for (int q = 0; q < s.r; ++q) {  // (G^T D^T)[j][q] = sum_p G[p][j] D[q][p]
@@ -864,11 +841,11 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
             re += gr * dr - gi * di;
             im += gr * di + gi * dr;
           }
-          dn[2 * (size_t(j) * Kpd + q)] = re;
-          dn[2 * (size_t(j) * Kpd + q) + 1] = im;
+          dn[2 * (size_t(j) * Ms + q)] = re;
+          dn[2 * (size_t(j) * Ms + q) + 1] = im;
         }
-      Mu.pack(up.data(), Ms, Kpu, hf_split, size_t(2) * id * H.R * KU * hf_split);
-      Md.pack(dn.data(), Mc, Kpd, hf_split, size_t(2) * id * H.Rc * KD * hf_split);
+      Mu.pack(up.data(), Ms, Mc, hf_split, size_t(id * per_op), id);
+      Md.pack(dn.data(), Mc, Ms, hf_split, size_t(id * per_op), id);
     });
 
     // HF-M2M and HF-L2L as pair lists: one pair per (parent slot, child), grouped
@@ -880,13 +857,13 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
       // by_op[op] = list of (source vector, destination slot)
       std::vector<int32_t> v0(1, 0), vsrc, vdst, opsv, gmk;
       std::vector<int64_t> aoff(nops);
-      for (int64_t op = 0; op < nops; ++op) aoff[op] = op * int64_t(M) * kpad(K, P.prec) * hf_split / 2;
+      for (int64_t op = 0; op < nops; ++op) aoff[op] = op * int64_t(M) * K * hf_split / 2;
       std::vector<std::vector<int32_t>> per(ndst);
       for (int64_t op = 0; op < int64_t(by_op.size()); ++op) {
         if (by_op[op].empty()) continue;
         opsv.push_back(int32_t(op));
         gmk.push_back(opM[op]);
-        gmk.push_back(opK[op] * hf_split);
+        gmk.push_back(opK[op]);
         for (auto& sd : by_op[op]) {
           per[sd.second].push_back(int32_t(vsrc.size()));
           vsrc.push_back(sd.first);
@@ -917,7 +894,7 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
       G.vdst.upload(vdst);
       G.aoff_h = aoff;
       G.kpk_h.resize(size_t(nops));
-      for (int64_t op = 0; op < nops; ++op) G.kpk_h[size_t(op)] = kpad(opK[size_t(op)], P.prec) * hf_split;
+      for (int64_t op = 0; op < nops; ++op) G.kpk_h[size_t(op)] = opK[size_t(op)];
       G.opflops = op_fl;
       rs.upload(rstart);
       ri.upload(ridx);
@@ -933,12 +910,7 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
           up_terms[size_t(e)].push_back({int32_t(i), int32_t(size_t(d) * 8 + C.octant[c]), src, 0});
         }
       }
-      if (half) {
-        std::vector<int32_t> aexp;
-        to_half_ops(Mu.f, int64_t(ndir) * 8, int64_t(2) * H.R * KU * hf_split, P.prec, aexp);
-        H.m2m.aexp.upload(aexp);
-      }
-      Mu.upload(H.m2m.A);
+      Mu.upload(H.m2m);
       finish_pairs(H.m2m, by_op, H.R, H.Rc, int64_t(ndir) * 8, H.nout, H.m2m_rs, H.m2m_ri, H.m2m_npairs, op_ms,
                    op_mc);
     }
@@ -988,12 +960,7 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
         }
         for (int32_t sidx : parents) info.bytes_l2l_vec += 8.0 * sk[size_t(IS[l].list[size_t(sidx)].second)].r;
       }
-      if (half) {
-        std::vector<int32_t> aexp;
-        to_half_ops(Md.f, int64_t(ndir) * 8, int64_t(2) * H.Rc * KD * hf_split, P.prec, aexp);
-        H.l2l.aexp.upload(aexp);
-      }
-      Md.upload(H.l2l.A);
+      Md.upload(H.l2l);
       finish_pairs(H.l2l, by_op, H.Rc, H.R, int64_t(ndir) * 8, H.nchild_in, H.l2l_rs, H.l2l_ri, H.l2l_npairs,
                    op_mc, op_ms);
     }
@@ -1020,11 +987,9 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
   // (child width w, delta_o = (o - 1/2) w): LF-M2M G(a_P - delta_o, b_C) D_C,
   // LF-L2L G(b_C + delta_o, a_P) D_P^T.
   auto build_lf_transfer = [&](const Skel& sp, const Skel& sc, double wc, GGemm& up, GGemm& dn) {
-    const int RK = kpad(Rlf, P.prec);
-    const size_t per = size_t(2) * Rlf * RK;  // storage of one operator
-    OpStore Au(fp64, per * 8), Ad(fp64, per * 8);
+    const size_t per = size_t(2) * Rlf * Rlf;  // storage of one operator
+    OpStore Au(P.prec, per * 8, 8), Ad(P.prec, per * 8, 8);
     const int Mp = pad8(sp.r), Mc = pad8(sc.r);
-    const int Kpu = kpad(Mc, P.prec), Kpd = kpad(Mp, P.prec);
     parallel_for(8, [&](int64_t o) {
       const double dx = ((o & 1) - 0.5) * wc, dy = (((o >> 1) & 1) - 0.5) * wc, dz = (((o >> 2) & 1) - 0.5) * wc;
       std::vector<double> G(size_t(2) * sp.r * sc.r);  // G[p][j] = G(a_P[p] - delta_o, b_C[j])
@@ -1033,7 +998,7 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
           green64(sp.a[3 * p] - dx - sc.b[3 * j], sp.a[3 * p + 1] - dy - sc.b[3 * j + 1],
                   sp.a[3 * p + 2] - dz - sc.b[3 * j + 2], &G[2 * (size_t(p) * sc.r + j)],
                   &G[2 * (size_t(p) * sc.r + j) + 1]);
-      std::vector<double> U(size_t(2) * Mp * Kpu, 0.0), Dn(size_t(2) * Mc * Kpd, 0.0);
+      std::vector<double> U(size_t(2) * Mp * Mc, 0.0), Dn(size_t(2) * Mc * Mp, 0.0);
       for (int p = 0; p < sp.r; ++p)
         for (int k = 0; k < sc.r; ++k) {  // (G D_C)[p][k]
           double re = 0.0, im = 0.0;
@@ -1043,8 +1008,8 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
             re += gr * dr - gi * di;
             im += gr * di + gi * dr;
           }
-          U[2 * (size_t(p) * Kpu + k)] = re;
-          U[2 * (size_t(p) * Kpu + k) + 1] = im;
+          U[2 * (size_t(p) * Mc + k)] = re;
+          U[2 * (size_t(p) * Mc + k) + 1] = im;
         }
       for (int j = 0; j < sc.r; ++j)
         for (int q = 0; q < sp.r; ++q) {  // (G^T D_P^T)[j][q] = sum_p G[p][j] D_P[q][p]
@@ -1055,11 +1020,11 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
             re += gr * dr - gi * di;
             im += gr * di + gi * dr;
           }
-          Dn[2 * (size_t(j) * Kpd + q)] = re;
-          Dn[2 * (size_t(j) * Kpd + q) + 1] = im;
+          Dn[2 * (size_t(j) * Mp + q)] = re;
+          Dn[2 * (size_t(j) * Mp + q) + 1] = im;
         }
-      Au.pack(U.data(), Mp, Kpu, 1, per * size_t(o));
-      Ad.pack(Dn.data(), Mc, Kpd, 1, per * size_t(o));
+      Au.pack(U.data(), Mp, Mc, 1, per * size_t(o), o);
+      Ad.pack(Dn.data(), Mc, Mp, 1, per * size_t(o), o);
     });
     for (GGemm* g : {&up, &dn}) {
       const bool isup = g == &up;
@@ -1070,12 +1035,12 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
       g->split = 1;
       g->nops = 8;
       g->aoff_h.resize(8);
-      g->kpk_h.assign(8, isup ? Kpu : Kpd);
+      g->kpk_h.assign(8, isup ? Mc : Mp);
       g->opflops.assign(8, 8.0 * sp.r * sc.r);
-      for (int o = 0; o < 8; ++o) g->aoff_h[size_t(o)] = int64_t(o) * Rlf * RK / 2;
+      for (int o = 0; o < 8; ++o) g->aoff_h[size_t(o)] = int64_t(o) * Rlf * Rlf / 2;
     }
-    Au.upload(up.A);
-    Ad.upload(dn.A);
+    Au.upload(up);
+    Ad.upload(dn);
   };
   std::vector<std::vector<SlotTerm>> deep_m2l_terms(static_cast<size_t>(nl));
   P.lfd.clear();
