@@ -645,6 +645,119 @@ __device__ __forceinline__ void slot_gemm(const SlotArgs& a, int nrhs, float2* _
   }
 }
 
+// The slot form for few right-hand sides (SlotTiles): the 16 columns of a
+// workgroup are (group, rhs) of neighbouring groups, each column's vector of a
+// term comes from the term's table, and columns without the term are zeros.  With
+// one group per workgroup a single right-hand side multiplies 15 columns of
+// padding and reads and splits an operator for every term of every slot; here
+// about 5 of 16 columns of a term are in use.  A column's products and sums are
+// those of the form above, so the two give the same bits.
+struct SlotTileArgs {
+  const int* t0;
+  const int* gm;
+  const int4* head;  // (operator float4 offset, K | kind << 14, 0, 0)
+  const int* vec;
+  const int* dst;
+  const float4* A0;
+  const float4* A1;
+  const float2* X0;
+  const float2* X1;
+  int KX0, KX1;
+  int M;
+};
+// UB: columns that a wave stages (ceil(16 / waves) at least); K <= 128.  A term's
+// columns and first operator rows are loaded while the term before multiplies.
+template <int UB>
+__device__ __forceinline__ void slot_tiles(const SlotTileArgs& a, float2* __restrict__ Y) {
+  constexpr int OP = OP_F32, AW = OpForm<OP>::AW, PB = OpForm<OP>::PB;
+  extern __shared__ float4 xs4[];
+  v4u* xs = reinterpret_cast<v4u*>(xs4);
+  const int lane = int(threadIdx.x) & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  const int nw = int(blockDim.x) >> 6;
+  const int g = int(blockIdx.x);
+  const int tb = a.t0[g], te = a.t0[g + 1];
+  const int Mg = a.gm[g];
+  const int m = int(blockIdx.y) * nw + wave;
+  const bool act = 16 * m < Mg;  // wave-uniform: this wave's tile has operator rows
+  const int rows = min(16, Mg - 16 * m);
+  struct Tm {
+    const float4* A;
+    const float2* X;
+    int KX, Kg, src;  // src: the source vector of column lane mod 16
+  };
+  auto decode = [&](int i) {
+    const int4 h = a.head[i];
+    const int hx = __builtin_amdgcn_readfirstlane(h.x), hy = __builtin_amdgcn_readfirstlane(h.y);
+    const int kind = (hy >> 14) & 1;
+    return Tm{(kind ? a.A1 : a.A0) + hx, kind ? a.X1 : a.X0, kind ? a.KX1 : a.KX0, hy & 0xFFF,
+              a.vec[int64_t(i) * kTileCols + (lane & 15)]};
+  };
+  auto tile = [&](const Tm& q) { return OpTile<OP>(OpRows(q.Kg, lane), q.A + m * (2 * q.Kg * AW), rows); };
+  double dre[4], dim_[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) dre[q] = dim_[q] = 0.0;
+  if (tb < te) {
+    Tm T = decode(tb), Tn = decode(min(tb + 1, te - 1));
+    float4 raw[AW], xv[UB];
+    auto x_load = [&](const Tm& q) {
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        const int src = __builtin_amdgcn_readlane(q.src, min(wave + u * nw, kTileCols - 1));
+        xv[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (src >= 0 && lane < q.Kg / 2) xv[u] = reinterpret_cast<const float4*>(q.X + int64_t(src) * q.KX)[lane];
+      }
+    };
+    if (act) load_first<OP>(tile(T), raw);
+    x_load(T);
+    for (int t = tb; t < te; ++t) {
+      const int pad_col = 4 * col_chunks(T.Kg), cs = col_units(T.Kg, PB);
+      __syncthreads();  // the previous term's columns are consumed
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        const int col = wave + u * nw;
+        if (col < kTileCols && lane < pad_col) stage_pair<OP>(reinterpret_cast<unsigned*>(xs + col * cs), lane, xv[u]);
+      }
+      __syncthreads();
+      const Tm Tnn = decode(min(t + 2, te - 1));
+      x_load(Tn);
+      if (act) {
+        const OpRows o(T.Kg, lane);
+        tile_product<OP, 1>(o, tile(T), tile(Tn), xs + o.j * cs, cs, raw, [&](int, const StepSums& s, auto merged) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            if constexpr (decltype(merged)::value) dre[q] += double(s.p[q]);
+            else dre[q] += double(s.p[q] - s.q[q]);
+            dim_[q] += double(s.i[q]);
+          }
+        });
+      }
+      T = Tn;
+      Tn = Tnn;
+    }
+  }
+  const int out = a.dst[int64_t(g) * kTileCols + (lane & 15)];
+  const int row = 16 * m + 4 * (lane >> 4);
+  if (row < a.M && out >= 0) {
+    float4 w0 = make_float4(0.f, 0.f, 0.f, 0.f), w1 = w0;
+    if (row < Mg) {
+      w0 = make_float4(float(dre[0]), float(dim_[0]), float(dre[1]), float(dim_[1]));
+      w1 = make_float4(float(dre[2]), float(dim_[2]), float(dre[3]), float(dim_[3]));
+    }
+    float4* y = reinterpret_cast<float4*>(Y + int64_t(out) * a.M + row);
+    y[0] = w0;
+    y[1] = w1;
+  }
+}
+template <int UB>
+__global__ void __launch_bounds__(64 * 8, 4) k_m2m_tiles(const SlotTileArgs a, float2* __restrict__ Y) {
+  slot_tiles<UB>(a, Y);
+}
+template <int UB>
+__global__ void __launch_bounds__(64 * 8, 4) k_m2l_tiles(const SlotTileArgs a, float2* __restrict__ Y) {
+  slot_tiles<UB>(a, Y);
+}
+
 // The slot form under two names, so that kernel traces separate the upward
 // transfers (M2M) from the downward pass (M2L pairs and L2L terms of a level).
 constexpr int SLOT_MAXW = 8;  // waves per workgroup
@@ -1331,6 +1444,7 @@ struct SlotLaunch {
   int waves = 1;       // waves per workgroup
   int cpg = 1;         // column chunks per group
   int64_t nchunks = 0;
+  std::unique_ptr<SlotTiles> tiles;  // tables for few right-hand sides (else null)
 };
 
 // The GEMM launches of one nrhs (chunk tables and tuned shapes).
@@ -1405,6 +1519,7 @@ struct ApplyState {
   std::vector<DevBuf> retired;  // workspaces replaced after a graph capture (captured graphs hold them)
   bool captured = false;      // an apply of this plan has been captured into a graph
   std::map<int, std::unique_ptr<LaunchSet>> sets;
+  std::map<int, std::unique_ptr<Tiles64>> sets64;  // float64 plans, few right-hand sides
   // second stream for the near field (default priority) and its fork/join events
   hipStream_t side = nullptr;
   hipEvent_t fork = nullptr, join = nullptr;
@@ -1620,6 +1735,22 @@ static void launch_slot(const SlotLaunch& L, const float4* A0, const float2* X0,
   const SlotGemm& S = *L.S;
   SlotArgs a{S.order.as<int>(), S.t0.as<int>(), S.gm.as<int>(), S.terms.as<int4>(), A0, A1 ? A1 : A0, X0,
              X1 ? X1 : X0, KX0, X1 ? KX1 : KX0, S.M, L.cpg, int(slot_col_units(S, L.nt)), L.waves, gdst};
+  if (L.tiles) {
+    const SlotTiles& T = *L.tiles;
+    const SlotTileArgs t{T.t0.as<int>(), T.gm.as<int>(), T.head.as<int4>(), T.vec.as<int>(), T.dst.as<int>(),
+                         A0, a.A1, X0, a.X1, KX0, a.KX1, S.M};
+    // as few as three waves (row tiles) per workgroup until the launch has two
+    // workgroups per CU; each slice stages the columns again
+    const int nM = (S.M + 15) / 16;
+    int slices = (nM + 7) / 8;
+    while ((nM + slices) / (slices + 1) >= 3 && T.ntiles * slices < 512) ++slices;
+    const int waves = std::max((nM + slices - 1) / slices, 3);
+    auto kern = waves >= 6 ? (m2l ? &k_m2l_tiles<3> : &k_m2m_tiles<3>) : (m2l ? &k_m2l_tiles<6> : &k_m2m_tiles<6>);
+    ensure_lds_limit(reinterpret_cast<const void*>(kern));
+    hipLaunchKernelGGL(kern, dim3(unsigned(T.ntiles), unsigned(slices)), dim3(unsigned(64 * waves)),
+                       slot_col_units(S, 1) * 16, st, t, Y);
+    return;
+  }
   if (L.nt == 2) launch_slot_t<2>(L, a, nrhs, Y, m2l, st);
   else launch_slot_t<1>(L, a, nrhs, Y, m2l, st);
 }
@@ -1639,6 +1770,26 @@ static void prepare_slot_set(const dfmm_plan_s& P, int nrhs, LaunchSet& LS) {
   for (size_t k = 0; k < P.lfd.size(); ++k) {
     prepare_slot(LS.lfd_up[k], P.lfd[k].up, nrhs, nt);
     prepare_slot(LS.lfd_down[k], P.lfd[k].down, nrhs, nt);
+  }
+  // few right-hand sides (adaptive trees; a uniform one takes the pair form there):
+  // two neighbouring groups or more share a tile's 16 columns
+  if (2 * nrhs > kTileCols) return;
+  auto tiles = [&](SlotLaunch& L, const std::vector<int32_t>* gdst = nullptr) {
+    std::unique_ptr<SlotTiles> t(new SlotTiles());
+    if (L.S->ngroups > 0 && L.S->Kmax <= 128 && build_slot_tiles(*L.S, nrhs, (L.S->M + 15) / 16, *t, gdst)) L.tiles = std::move(t);
+  };
+  try {
+    for (size_t e = 0; e < P.hf.size(); ++e) {
+      tiles(LS.up[e]);
+      tiles(LS.down[e]);
+    }
+    tiles(LS.lf_down);
+    for (size_t k = 0; k < P.lfd.size(); ++k) {
+      tiles(LS.lfd_up[k], &P.lfd[k].up_dst_h);
+      tiles(LS.lfd_down[k]);
+    }
+  } catch (const Error& e) {  // no memory for the rest of the tables: the general form needs none
+    if (e.code != DFMM_ENOMEM) throw;
   }
 }
 
@@ -2044,18 +2195,30 @@ void run_apply(dfmm_plan_s& P, const ReqTable& R, int nrhs, hipStream_t st, void
     if (!own && ws_bytes < need)
       throw Error{DFMM_EINVAL, "workspace of " + std::to_string(ws_bytes) + " bytes; this apply needs " +
                                    std::to_string(need)};
+    // few right-hand sides: tables that the first uncaptured apply of this nrhs
+    // makes (a captured one without them takes the general form)
+    const Tiles64* T = nullptr;
+    if (nrhs <= kTiles64Rhs) {
+      std::unique_ptr<Tiles64>& t = AS.sets64[nrhs];
+      if (!t && !capturing) {
+        try {
+          t.reset(new Tiles64(P, nrhs));
+        } catch (const Error& e) {  // no memory for the tables: the general form needs none
+          if (e.code != DFMM_ENOMEM) throw;
+        }
+      }
+      T = t.get();
+    }
     if (own) {
-      hipStreamCaptureStatus c2 = hipStreamCaptureStatusNone;
-      DFMM_HIP(hipStreamIsCapturing(st, &c2));
-      if (c2 != hipStreamCaptureStatusNone && (!AS.buf.p || AS.buf.bytes < need))
+      if (capturing && (!AS.buf.p || AS.buf.bytes < need))
         throw Error{DFMM_EINVAL, "dfmm_apply under stream capture needs an earlier uncaptured apply"};
-      if (c2 != hipStreamCaptureStatusNone) AS.captured = true;
+      if (capturing) AS.captured = true;
       ensure_workspace(AS, need);
     } else {
       lock.unlock();
     }
     run_apply64(P, reinterpret_cast<const double2*>(R.f[0]), reinterpret_cast<double2*>(R.u[0]), nrhs, st,
-                own ? AS.buf.p : ws);
+                own ? AS.buf.p : ws, T);
     return;
   }
   const WsLayout L = plan_layout(P, nrhs);

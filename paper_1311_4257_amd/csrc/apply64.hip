@@ -32,8 +32,10 @@ __global__ void k_permute_in64(const double2* __restrict__ f, double2* __restric
 }
 
 // Leaf S2M: chk[b][k][p] = sum_{j in leaf b} V[j][p] fs[j][k]; one block per leaf,
-// threads over check points, sources in order.
-constexpr int S64_BS = 128;
+// threads over check points, sources in order.  The loop over the leaf's sources
+// waits on its loads, so the weights of S64_SU sources are loaded before the
+// first is used.
+constexpr int S64_BS = 128, S64_SU = 4;
 __global__ void __launch_bounds__(S64_BS) k_s2m64(const int* __restrict__ lstart, const double2* __restrict__ V,
                                                    const double2* __restrict__ fs, int R, int nrhs,
                                                    double2* __restrict__ clf) {
@@ -42,16 +44,27 @@ __global__ void __launch_bounds__(S64_BS) k_s2m64(const int* __restrict__ lstart
   for (int k = 0; k < nrhs; ++k)
     for (int p = threadIdx.x; p < R; p += S64_BS) {
       double re = 0.0, im = 0.0;
-      for (int j = s0; j < s1; ++j) {
-        const double2 v = V[int64_t(j) * R + p], x = fs[int64_t(j) * nrhs + k];
+      auto add = [&](double2 v, double2 x) {
         re = fma(v.x, x.x, fma(-v.y, x.y, re));
         im = fma(v.x, x.y, fma(v.y, x.x, im));
+      };
+      int j = s0;
+      for (; j + S64_SU <= s1; j += S64_SU) {
+        double2 v[S64_SU];
+#pragma unroll
+        for (int u = 0; u < S64_SU; ++u) v[u] = V[int64_t(j + u) * R + p];
+#pragma unroll
+        for (int u = 0; u < S64_SU; ++u) add(v[u], fs[int64_t(j + u) * nrhs + k]);
       }
+      for (; j < s1; ++j) add(V[int64_t(j) * R + p], fs[int64_t(j) * nrhs + k]);
       clf[(int64_t(b) * nrhs + k) * R + p] = make_double2(re, im);
     }
 }
 
-// Near-field sum in float64: one block of 64 threads per leaf; the adjacent
+// Near-field sum in float64: one wave per leaf, lane = (target t = lane mod 16, a
+// quarter lane / 16 of the sources), as in the float32 path: a leaf of the
+// K = 8 sphere with 16,384 points holds 15, which left three quarters of the
+// lanes idle with one target per lane (140 us there).  The adjacent
 // leaves' points (separations from the hi / lo float parts, formed in float64)
 // and densities are staged in LDS a chunk at a time; G = exp(2 pi i r) / r with
 // the phase reduced in float64 and sin / cos of it in float64.
@@ -90,8 +103,8 @@ __global__ void __launch_bounds__(N64_BS) k_near64(const float4* __restrict__ ph
   const int total = nb_off[nn];
   for (int k0 = 0; k0 < nrhs; k0 += N64_RC) {
     const int nk = min(N64_RC, nrhs - k0);
-    for (int t0 = s0; t0 < s1; t0 += N64_BS) {
-      const int t = t0 + lane;
+    for (int t0 = s0; t0 < s1; t0 += 16) {
+      const int t = t0 + (lane & 15), sl = lane >> 4;
       const bool act = t < s1;
       const int tt = act ? t : s0;
       const float4 th = phi[tt], tq = plo[tt];
@@ -117,7 +130,7 @@ __global__ void __launch_bounds__(N64_BS) k_near64(const float4* __restrict__ ph
             sf[i * N64_RC + k] = k < nk ? fs[int64_t(j) * nrhs + k0 + k] : make_double2(0.0, 0.0);
         }
         __syncthreads();
-        for (int i = 0; i < fill; ++i) {
+        for (int i = sl; i < fill; i += 4) {
           const double dx = tx - sx[i], dy = ty - sy[i], dz = tz - sz[i];
           const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
           if (r2 == 0.0) continue;  // coincident points contribute nothing
@@ -134,7 +147,14 @@ __global__ void __launch_bounds__(N64_BS) k_near64(const float4* __restrict__ ph
           }
         }
       }
-      if (act)
+#pragma unroll
+      for (int k = 0; k < N64_RC; ++k) {
+        ar[k] += __shfl_xor(ar[k], 16, 64);
+        ai[k] += __shfl_xor(ai[k], 16, 64);
+        ar[k] += __shfl_xor(ar[k], 32, 64);
+        ai[k] += __shfl_xor(ai[k], 32, 64);
+      }
+      if (act && sl == 0)
         for (int k = 0; k < nk; ++k) unear[int64_t(k0 + k) * N + t] = make_double2(ar[k], ai[k]);
     }
   }
@@ -242,24 +262,175 @@ __global__ void __launch_bounds__(256) k_slot64(const Slot64Args a, int nrhs, do
   }
 }
 
-// L2T and the output: u[k][perm[t]] = sum_q W[t][q] U_LF[leaf(t)][k][q] + unear[k][t].
-__global__ void k_l2t64(const double2* __restrict__ W, const double2* __restrict__ ulf, const int* __restrict__ leaf_of,
-                        const double2* __restrict__ unear, const int* __restrict__ perm, int R, int nrhs, int64_t N,
-                        double2* __restrict__ u) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= N * nrhs) return;
-  const int k = int(i / N);
-  const int64_t t = i % N;
-  const double2* w = W + t * R;
-  const double2* x = ulf + (int64_t(leaf_of[t]) * nrhs + k) * R;
-  double re = 0.0, im = 0.0;
-  for (int q = 0; q < R; ++q) {
-    const double2 a = w[q], b = x[q];
-    re = fma(a.x, b.x, fma(-a.y, b.y, re));
-    im = fma(a.x, b.y, fma(a.y, b.x, im));
+// The same for few right-hand sides (SlotTiles): the 16 columns of a workgroup are
+// (group, rhs) of neighbouring groups, each column's vector of a term comes from
+// the term's table, and columns without the term are zeros.  At one right-hand
+// side the form above multiplies 15 columns of padding and reads an operator
+// (0.8 MB at rank 232) for every term of every slot; here about 5 of 16 columns
+// of a term are in use.  A column's products and their order are those of the
+// form above, so the two give the same bits.  A wave takes MT row tiles of the
+// slice blockIdx.y, with the operator rows of T64_RING steps in flight (a step
+// is 256 matrix-core cycles; 12 steps measured the same).  Eight waves share the
+// 60 KB of staged columns (rank 232): two workgroups of 8 fit a CU, two of 4
+// left half of its wave slots empty and ran a second round.  A term's columns, and the
+// first operator rows, are loaded while the term before multiplies.
+struct Tile64Args {
+  const int* t0;
+  const int* gm;
+  const int4* head;  // (operator double4 offset, K | kind << 14, 0, 0)
+  const int* vec;
+  const int* dst;
+  const double4* A0;
+  const double4* A1;
+  const double2* X0;
+  const double2* X1;
+  int KX0, KX1;
+  int M;
+  int S;  // LDS column stride in double4
+};
+constexpr int T64_RING = 4;
+constexpr int T64_NW = 8;   // waves per workgroup
+constexpr int T64_TPC = 64 * T64_NW / kTileCols;  // threads that stage a column
+constexpr int T64_XQ = 4;   // double4 per thread and term
+constexpr int T64_MAXK = 2 * T64_TPC * T64_XQ;
+
+template <int MT>
+__global__ void __launch_bounds__(64 * T64_NW, 4) k_tile64(const Tile64Args a, double2* __restrict__ Y) {
+  extern __shared__ double4 xs64[];  // 16 columns x S double4
+  const int tid = int(threadIdx.x);
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j = lane & 15, kr = lane >> 4;
+  const bool odd = (j & 1) != 0;
+  const int g = int(blockIdx.x);
+  const int tb = a.t0[g], te = a.t0[g + 1];
+  const int nM = a.gm[g] / 8;
+  const int m0 = int(blockIdx.y) * T64_NW + wave, mstep = T64_NW * int(gridDim.y);
+  v4d acc[MT];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) acc[t] = v4d{0.0, 0.0, 0.0, 0.0};
+  const int sc = tid / T64_TPC, sq = tid % T64_TPC;  // this thread's column and first entry of the staging
+  double4 ring[T64_RING];
+  auto rows = [&](int4 h, int m) {
+    const int kind = (h.y >> 14) & 1, Q4 = (h.y & 0xFFF) / 8;
+    return (kind ? a.A1 : a.A0) + h.x + int64_t(m) * Q4 * 32 + (j >> 1) * 4 + kr;
+  };
+  auto fill = [&](int4 h, int m) {
+    const double4* ap = rows(h, m);
+    const int Q4 = (h.y & 0xFFF) / 8;
+#pragma unroll
+    for (int u = 0; u < T64_RING; ++u) ring[u] = ap[min(u, Q4 - 1) * 32];
+  };
+  auto uni = [](int4 h) {
+    h.x = __builtin_amdgcn_readfirstlane(h.x);
+    h.y = __builtin_amdgcn_readfirstlane(h.y);
+    return h;
+  };
+  double4 xv[T64_XQ];
+  auto x_load = [&](int4 h, int src) {
+    const int kind = (h.y >> 14) & 1, Kg = h.y & 0xFFF;
+    const double4* X =
+        reinterpret_cast<const double4*>((kind ? a.X1 : a.X0) + int64_t(max(src, 0)) * (kind ? a.KX1 : a.KX0));
+#pragma unroll
+    for (int u = 0; u < T64_XQ; ++u) {
+      const int q = sq + T64_TPC * u;
+      xv[u] = make_double4(0.0, 0.0, 0.0, 0.0);
+      if (src >= 0 && q < Kg / 2) xv[u] = X[q];
+    }
+  };
+  auto vec = [&](int i) { return a.vec[int64_t(min(i, te - 1)) * kTileCols + sc]; };
+  int4 h = make_int4(0, 8, 0, 0);
+  int src1 = -1;  // the next term's source
+  if (tb < te) {
+    h = uni(a.head[tb]);
+    if (m0 < nM) fill(h, m0);
+    x_load(h, vec(tb));
+    src1 = vec(tb + 1);
   }
-  const double2 nf = unear[int64_t(k) * N + t];
-  u[int64_t(k) * N + perm[t]] = make_double2(re + nf.x, im + nf.y);
+  for (int i = tb; i < te; ++i) {
+    const int4 hn = i + 1 < te ? uni(a.head[i + 1]) : h;
+    const int Kg = h.y & 0xFFF, Q4 = Kg / 8;
+    __syncthreads();  // the previous term's columns are consumed
+#pragma unroll
+    for (int u = 0; u < T64_XQ; ++u)
+      if (sq + T64_TPC * u < Kg / 2) xs64[sc * a.S + sq + T64_TPC * u] = xv[u];
+    __syncthreads();
+    x_load(hn, src1);
+    src1 = vec(i + 2);
+    const double4* bcol = xs64 + j * a.S + kr * Q4;
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      const int m = m0 + mstep * t;
+      if (m < nM) {  // wave-uniform
+        const double4* ap = rows(h, m);
+        for (int s0 = 0; s0 < Q4; s0 += T64_RING)
+#pragma unroll
+          for (int u = 0; u < T64_RING; ++u)
+            if (s0 + u < Q4) {
+              const double4 v = ring[u];
+              ring[u] = ap[min(s0 + u + T64_RING, Q4 - 1) * 32];
+              const double4 b = bcol[s0 + u];
+              const double f0 = odd ? v.y : v.x, f1 = odd ? v.x : -v.y, f2 = odd ? v.w : v.z, f3 = odd ? v.z : -v.w;
+              acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(f0, b.x, acc[t], 0, 0, 0);
+              acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(f1, b.y, acc[t], 0, 0, 0);
+              acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(f2, b.z, acc[t], 0, 0, 0);
+              acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(f3, b.w, acc[t], 0, 0, 0);
+            }
+        // the next tile of this term, or the first one of the next term
+        const bool more = t + 1 < MT && m + mstep < nM;
+        fill(more ? h : hn, more ? m + mstep : m0);
+      }
+    }
+    h = hn;
+  }
+  // (the accumulator layout of k_slot64)
+  const int out = a.dst[int64_t(g) * kTileCols + j];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    const int m = m0 + mstep * t;
+    const v4d o = m < nM ? acc[t] : v4d{0.0, 0.0, 0.0, 0.0};
+    double im[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) im[r] = __shfl_xor(o[r], 16, 64);
+    if (out >= 0 && (kr & 1) == 0 && m < a.M / 8) {
+      double2* yp = Y + int64_t(out) * a.M + 8 * m + (kr >> 1);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) yp[2 * r] = make_double2(o[r], im[r]);
+    }
+  }
+}
+
+// L2T and the output: u[k][perm[t]] = sum_q W[t][q] U_LF[leaf(t)][k][q] + unear[k][t].
+// 16 lanes per target read 16 consecutive q at a time (256-byte runs of W); with
+// one target per lane every load of a wave touched 64 rows.
+constexpr int L64_BS = 256;
+__global__ void __launch_bounds__(L64_BS) k_l2t64(const double2* __restrict__ W, const double2* __restrict__ ulf,
+                                                   const int* __restrict__ leaf_of, const double2* __restrict__ unear,
+                                                   const int* __restrict__ perm, int R, int nrhs, int64_t N,
+                                                   double2* __restrict__ u) {
+  const int64_t i = (int64_t(blockIdx.x) * L64_BS + threadIdx.x) >> 4;
+  const int l = threadIdx.x & 15;
+  const bool act = i < N;
+  const int64_t t = act ? i : 0;
+  const double2* w = W + t * R;
+  for (int k = 0; k < nrhs; ++k) {
+    const double2* x = ulf + (int64_t(leaf_of[t]) * nrhs + k) * R;
+    double re = 0.0, im = 0.0;
+    for (int q = l; q < R; q += 16) {
+      const double2 a = w[q], b = x[q];
+      re = fma(a.x, b.x, fma(-a.y, b.y, re));
+      im = fma(a.x, b.y, fma(a.y, b.x, im));
+    }
+#pragma unroll
+    for (int m = 8; m > 0; m >>= 1) {
+      re += __shfl_xor(re, m, 16);
+      im += __shfl_xor(im, m, 16);
+    }
+    if (act && l == 0) {
+      const double2 nf = unear[int64_t(k) * N + t];
+      u[int64_t(k) * N + perm[t]] = make_double2(re + nf.x, im + nf.y);
+    }
+  }
 }
 
 // tiles per wave of the largest group
@@ -267,26 +438,28 @@ int slot64_mt(const SlotGemm& S) { return (S.M / 8 + 3) / 4; }
 
 constexpr int kLds64 = 159 * 1024;  // dynamic LDS limit set on the float64 slot kernels
 
-template <int MT>
-void launch_slot64_t(const SlotGemm& S, const Slot64Args& a, int nrhs, double2* Y, hipStream_t st) {
-  const size_t lds = sizeof(double4) * 16 * size_t(a.S);
+// raise a kernel's dynamic LDS limit, once per (kernel, device)
+void lds_limit64(const void* fn) {
   static std::mutex mu;
-  static std::set<int> done;  // devices on which the attribute is set
+  static std::set<std::pair<const void*, int>> done;
   int dev = 0;
   DFMM_HIP(hipGetDevice(&dev));
-  {
-    std::lock_guard<std::mutex> lock(mu);
-    if (!done.count(dev)) {
-      DFMM_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_slot64<MT>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, kLds64));
-      done.insert(dev);
-    }
-  }
-  hipLaunchKernelGGL(k_slot64<MT>, dim3(unsigned(S.ngroups * a.cpg)), dim3(256), lds, st, a, nrhs, Y);
+  std::lock_guard<std::mutex> lock(mu);
+  if (done.count({fn, dev})) return;
+  DFMM_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLds64));
+  done.insert({fn, dev});
 }
 
-void launch_slot64(const SlotGemm& S, const double4* A0, const double2* X0, int KX0, const double4* A1,
-                   const double2* X1, int KX1, int nrhs, double2* Y, hipStream_t st) {
+template <int MT>
+void launch_slot64_t(const SlotGemm& S, const Slot64Args& a, int nrhs, double2* Y, hipStream_t st) {
+  lds_limit64(reinterpret_cast<const void*>(&k_slot64<MT>));
+  hipLaunchKernelGGL(k_slot64<MT>, dim3(unsigned(S.ngroups * a.cpg)), dim3(256), sizeof(double4) * 16 * size_t(a.S), st,
+                     a, nrhs, Y);
+}
+
+// T: the tables for few right-hand sides, or null
+void launch_slot64(const SlotGemm& S, const SlotTiles* T, const double4* A0, const double2* X0, int KX0,
+                   const double4* A1, const double2* X1, int KX1, int nrhs, double2* Y, hipStream_t st) {
   if (S.ngroups == 0) return;
   if (S.split2 || S.Kmax % 8 != 0) throw Error{DFMM_EUNSUPPORTED, "float64 slot GEMM: bad operator packing"};
   const int cpg = (nrhs + 15) / 16;
@@ -295,6 +468,20 @@ void launch_slot64(const SlotGemm& S, const double4* A0, const double2* X0, int 
   const int mt = slot64_mt(S);
   if (sizeof(double4) * 16 * size_t(a.S) > size_t(kLds64))
     throw Error{DFMM_EUNSUPPORTED, "skeleton rank too large for the float64 slot GEMM"};
+  if (T && T->ntiles > 0 && S.Kmax <= T64_MAXK) {
+    Tile64Args t{T->t0.as<int>(), T->gm.as<int>(), T->head.as<int4>(), T->vec.as<int>(), T->dst.as<int>(),
+                 A0, a.A1, X0, a.X1, KX0, a.KX1, S.M, a.S};
+    // one row tile per wave until the launch has two workgroups per CU, then two:
+    // each slice stages the columns again
+    const int nM = S.M / 8;
+    const bool two = T->ntiles * ((nM + 2 * T64_NW - 1) / (2 * T64_NW)) >= 512;
+    const int per = (two ? 2 : 1) * T64_NW;
+    const dim3 grid(unsigned(T->ntiles), unsigned((nM + per - 1) / per));
+    auto kern = two ? &k_tile64<2> : &k_tile64<1>;
+    lds_limit64(reinterpret_cast<const void*>(kern));
+    hipLaunchKernelGGL(kern, grid, dim3(64 * T64_NW), sizeof(double4) * 16 * size_t(a.S), st, t, Y);
+    return;
+  }
   if (mt <= 2) launch_slot64_t<2>(S, a, nrhs, Y, st);
   else if (mt <= 4) launch_slot64_t<4>(S, a, nrhs, Y, st);
   else if (mt <= 8) launch_slot64_t<8>(S, a, nrhs, Y, st);
@@ -303,7 +490,16 @@ void launch_slot64(const SlotGemm& S, const double4* A0, const double2* X0, int 
 
 }  // namespace
 
-void run_apply64(dfmm_plan_s& P, const double2* f, double2* u, int nrhs, hipStream_t st, void* ws) {
+Tiles64::Tiles64(const dfmm_plan_s& P, int nrhs) : up(P.hf.size()), down(P.hf.size()) {
+  bool ok = build_slot_tiles(P.lf.down, nrhs, P.lf.down.M / 8, lf);
+  for (size_t e = 0; e < P.hf.size(); ++e)
+    ok = build_slot_tiles(P.hf[e].up, nrhs, P.hf[e].up.M / 8, up[e]) &&
+         build_slot_tiles(P.hf[e].down, nrhs, P.hf[e].down.M / 8, down[e]) && ok;
+  usable = ok;
+}
+
+void run_apply64(dfmm_plan_s& P, const double2* f, double2* u, int nrhs, hipStream_t st, void* ws, const Tiles64* T) {
+  if (T && !T->usable) T = nullptr;
   const WsLayout L = ws_layout(ws_shape64(P), nrhs, false, 16);
   if (!ws) throw Error{DFMM_EINVAL, "no workspace"};
   char* b = static_cast<char*>(ws);
@@ -326,19 +522,19 @@ void run_apply64(dfmm_plan_s& P, const double2* f, double2* u, int nrhs, hipStre
   for (int e = 0; e <= e_top; ++e) {
     const double2* Fc = e == 0 ? flf : F[size_t(e - 1)];
     const int KC = e == 0 ? Rl : P.hf[size_t(e - 1)].R;
-    launch_slot64(P.hf[size_t(e)].up, P.hf[size_t(e)].m2m.A.as<double4>(), Fc, KC, nullptr, nullptr, 0, nrhs,
+    launch_slot64(P.hf[size_t(e)].up, T ? &T->up[size_t(e)] : nullptr, P.hf[size_t(e)].m2m.A.as<double4>(), Fc, KC, nullptr, nullptr, 0, nrhs,
                   F[size_t(e)], st);
   }
   for (int e = e_top; e >= 0; --e) {
     const HFLevel& H = P.hf[size_t(e)];
     const bool par = e < e_top;
-    launch_slot64(H.down, H.m2l.A.as<double4>(), F[size_t(e)], H.R,
+    launch_slot64(H.down, T ? &T->down[size_t(e)] : nullptr, H.m2l.A.as<double4>(), F[size_t(e)], H.R,
                   par ? P.hf[size_t(e + 1)].l2l.A.as<double4>() : nullptr, par ? U[size_t(e + 1)] : nullptr,
                   par ? P.hf[size_t(e + 1)].R : 0, nrhs, U[size_t(e)], st);
   }
-  launch_slot64(P.lf.down, P.lf.m2l.A.as<double4>(), flf, Rl, e_top >= 0 ? P.hf[0].l2l.A.as<double4>() : nullptr,
+  launch_slot64(P.lf.down, T ? &T->lf : nullptr, P.lf.m2l.A.as<double4>(), flf, Rl, e_top >= 0 ? P.hf[0].l2l.A.as<double4>() : nullptr,
                 e_top >= 0 ? U[0] : nullptr, e_top >= 0 ? P.hf[0].R : 0, nrhs, ulf, st);
-  hipLaunchKernelGGL(k_l2t64, dim3(nblk(N * nrhs, 256)), dim3(256), 0, st, P.lf.W.as<double2>(), ulf,
+  hipLaunchKernelGGL(k_l2t64, dim3(nblk(N * 16, L64_BS)), dim3(L64_BS), 0, st, P.lf.W.as<double2>(), ulf,
                      P.leaf_of.as<int>(), unear, P.perm_d.as<int>(), Rl, nrhs, N, u);
   DFMM_HIP(hipGetLastError());
 }

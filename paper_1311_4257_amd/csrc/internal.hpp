@@ -157,7 +157,28 @@ struct SlotGemm {
   DevBuf gm;                 // int32[ngroups]: padded rows M_g of the group's operators
   DevBuf terms;              // int32[nterms][4]: (operator float4 offset, source vector,
                              //   packed K | split << 12 | kind << 14, 0)
+  // host copies: term ranges and table, operator index of each term, padded rows and
+  // neighbourhood order of each group (slot_tiles)
+  std::vector<int32_t> t0_h, terms_h, op_h, gm_h;
+  std::vector<int64_t> near_h;
 };
+// Slot-form tables for few right-hand sides: a tile holds 16 columns, one per
+// (group, rhs) of 16 / nrhs neighbouring groups, and walks the union of their
+// terms, so that an operator is read and multiplied once for all of its groups
+// that use it.  A column without the term has zeros there, which leave its sum as
+// it is: every column sums its own group's terms in their order.
+constexpr int kTileCols = 16;
+struct SlotTiles {
+  int64_t ntiles = 0;
+  DevBuf t0;    // int32[ntiles + 1]: term range of each tile (longest first)
+  DevBuf gm;    // int32[ntiles]: padded rows
+  DevBuf head;  // int32[nterms][4]: (operator offset, K | kind << 14, 0, 0)
+  DevBuf vec;   // int32[nterms][kTileCols]: source vector (slot nrhs + rhs) of each column, -1: none
+  DevBuf dst;   // int32[ntiles][kTileCols]: output vector of each column, -1: none
+};
+// False if the groups' terms have no common order (the tables are then not made).
+// row_tiles: row tiles (waves) of a tile in the kernel that uses the tables.
+bool build_slot_tiles(const SlotGemm& S, int nrhs, int row_tiles, SlotTiles& T, const std::vector<int32_t>* gdst = nullptr);
 // Host view of one kind's operators: float4 offset and packed K (split doubling
 // included) of every operator index, and the split factor.
 struct SlotKind {
@@ -166,7 +187,8 @@ struct SlotKind {
 };
 // Term lists -> device tables; terms of a group keep the order given.
 void build_slot_gemm(SlotGemm& S, int M, int64_t ngroups, const std::vector<int32_t>& gM,
-                     const std::vector<SlotTerm>& terms, const SlotKind kinds[2], int kx_max);
+                     const std::vector<SlotTerm>& terms, const SlotKind kinds[2], int kx_max,
+                     const std::vector<int64_t>& near);
 
 // Pack an M x K complex matrix (row-major, interleaved float64) into the
 // fragment order of the float64 GEMM kernel
@@ -225,6 +247,7 @@ struct LFDeep {
   DevBuf red_start, red_idx; // pair-form CSR of the M2L (built with the operators, unused)
   SlotGemm up;               // LF-M2M: the split boxes of level l - 1 <- their children
   DevBuf up_dst;             // int32[nsplit]: LF vector index of each of those parents
+  std::vector<int32_t> up_dst_h;
   SlotGemm down;             // LF-M2L pairs + LF-L2L term of every box of this level
 };
 
@@ -330,7 +353,16 @@ size_t plan_device_bytes(const dfmm_plan_s& P);
 // float64 plans: the whole pass in complex128 on a caller-sized workspace
 // (ws_layout(ws_shape64(P), nrhs, false, 16))
 WsShape ws_shape64(const dfmm_plan_s& P);
-void run_apply64(dfmm_plan_s& P, const double2* f, double2* u, int nrhs, hipStream_t st, void* ws);
+// The tables of a float64 apply with few right-hand sides (up to kTiles64Rhs; null:
+// the general form, with the same results bit for bit).
+constexpr int kTiles64Rhs = kTileCols / 2;
+struct Tiles64 {
+  std::vector<SlotTiles> up, down;  // per HF level
+  SlotTiles lf;
+  bool usable = false;
+  Tiles64(const dfmm_plan_s& P, int nrhs);
+};
+void run_apply64(dfmm_plan_s& P, const double2* f, double2* u, int nrhs, hipStream_t st, void* ws, const Tiles64* T);
 // S2M and L2T weights of every sorted point (float64, then stored in the plan's
 // precision).  DT holds D^T of each LF skeleton at R x R offsets, P.lf.a64 its
 // check points at R offsets; ra the skeletons' ranks, sk_of the skeleton of each leaf.

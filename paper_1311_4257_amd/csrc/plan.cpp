@@ -273,7 +273,8 @@ struct OpStore {
 };
 
 void build_slot_gemm(SlotGemm& S, int M, int64_t ngroups, const std::vector<int32_t>& gM,
-                     const std::vector<SlotTerm>& terms, const SlotKind kinds[2], int kx_max) {
+                     const std::vector<SlotTerm>& terms, const SlotKind kinds[2], int kx_max,
+                     const std::vector<int64_t>& near) {
   S.M = M;
   S.KXmax = kx_max;
   S.split2 = false;
@@ -287,7 +288,7 @@ void build_slot_gemm(SlotGemm& S, int M, int64_t ngroups, const std::vector<int3
     ++cnt[size_t(t.dst) + 1];
   }
   for (int64_t g = 0; g < ngroups; ++g) cnt[size_t(g) + 1] += cnt[size_t(g)];
-  std::vector<int32_t> pos(cnt.begin(), cnt.end() - 1), tab(size_t(4) * terms.size());
+  std::vector<int32_t> pos(cnt.begin(), cnt.end() - 1), tab(size_t(4) * terms.size()), op(terms.size());
   int kmax = 8;
   for (const SlotTerm& t : terms) {
     const SlotKind& k = kinds[t.kind];
@@ -296,7 +297,9 @@ void build_slot_gemm(SlotGemm& S, int M, int64_t ngroups, const std::vector<int3
     const int kp = k.G->kpk_h[size_t(t.op)];
     if (aoff > INT32_MAX || kp >= (1 << 12) || kp < 8 || kp % 8 != 0 || k.split > 3)
       throw Error{DFMM_EUNSUPPORTED, "operator table too large for the slot-form GEMM"};
-    int32_t* e = &tab[size_t(4) * size_t(pos[size_t(t.dst)]++)];
+    const size_t at = size_t(pos[size_t(t.dst)]++);
+    op[at] = t.op;
+    int32_t* e = &tab[size_t(4) * at];
     e[0] = int32_t(aoff);
     e[1] = t.src;
     e[2] = kp | (k.split << 12) | (t.kind << 14);
@@ -319,6 +322,105 @@ void build_slot_gemm(SlotGemm& S, int M, int64_t ngroups, const std::vector<int3
   S.t0.upload(cnt);
   S.gm.upload(gM);
   S.terms.upload(tab);
+  S.t0_h = std::move(cnt);
+  S.terms_h = std::move(tab);
+  S.op_h = std::move(op);
+  S.gm_h = gM;
+  S.near_h = near;
+}
+
+bool build_slot_tiles(const SlotGemm& S, int nrhs, int row_tiles, SlotTiles& T, const std::vector<int32_t>* gdst) {
+  // groups of a tile: more of them share more operators (about 1.8 columns of a
+  // term in use with 4, 5 with 16), but leave fewer waves, one per row tile; as
+  // many as leave 1.5 waves for each of the 1,024 SIMDs
+  int per = kTileCols / nrhs;
+  while (per > 1 && (S.ngroups + per - 1) / per * row_tiles < 1536) per /= 2;
+  // the common order: the kind that groups start with, then the operator index
+  int first = -1;
+  for (int64_t g = 0; g < S.ngroups; ++g) {
+    int last_rank = -1, last_op = -1;
+    for (int32_t i = S.t0_h[size_t(g)]; i < S.t0_h[size_t(g) + 1]; ++i) {
+      const int kind = (S.terms_h[size_t(4) * size_t(i) + 2] >> 14) & 1;
+      // a group with one kind only fits either order; those with both decide it
+      if (i > S.t0_h[size_t(g)] && last_rank >= 0) {
+        const int prev = (S.terms_h[size_t(4) * size_t(i - 1) + 2] >> 14) & 1;
+        if (prev != kind) {
+          if (first >= 0 && first != prev) return false;
+          first = prev;
+        } else if (S.op_h[size_t(i)] <= last_op) {
+          return false;
+        }
+      }
+      last_rank = kind;
+      last_op = S.op_h[size_t(i)];
+    }
+  }
+  if (first < 0) first = 0;
+  std::vector<int64_t> gs(static_cast<size_t>(S.ngroups));
+  for (int64_t g = 0; g < S.ngroups; ++g) gs[size_t(g)] = g;
+  std::stable_sort(gs.begin(), gs.end(), [&](int64_t a, int64_t b) {
+    if (S.gm_h[size_t(a)] != S.gm_h[size_t(b)]) return S.gm_h[size_t(a)] < S.gm_h[size_t(b)];
+    return S.near_h[size_t(a)] < S.near_h[size_t(b)];
+  });
+  struct Tile {
+    std::vector<int64_t> g;
+    std::vector<std::array<int32_t, 4>> head;
+    std::vector<int32_t> vec;
+  };
+  std::vector<Tile> tiles;
+  for (size_t i = 0; i < gs.size();) {
+    Tile t;
+    while (i < gs.size() && int(t.g.size()) < per &&
+           (t.g.empty() || (S.gm_h[size_t(gs[i])] == S.gm_h[size_t(t.g[0])] &&
+                            (S.near_h[size_t(gs[i])] >> 32) == (S.near_h[size_t(t.g[0])] >> 32))))
+      t.g.push_back(gs[i++]);
+    tiles.push_back(std::move(t));
+  }
+  parallel_for(int64_t(tiles.size()), [&](int64_t ti) {
+    Tile& t = tiles[size_t(ti)];
+    std::vector<int32_t> at;
+    for (int64_t g : t.g) at.push_back(S.t0_h[size_t(g)]);
+    auto key = [&](int32_t i) {
+      const int kind = (S.terms_h[size_t(4) * size_t(i) + 2] >> 14) & 1;
+      return int64_t(kind == first ? 0 : 1) << 32 | S.op_h[size_t(i)];
+    };
+    for (;;) {
+      int64_t best = INT64_MAX;
+      for (size_t c = 0; c < t.g.size(); ++c)
+        if (at[c] < S.t0_h[size_t(t.g[c]) + 1]) best = std::min(best, key(at[c]));
+      if (best == INT64_MAX) break;
+      std::array<int32_t, 4> h{0, 0, 0, 0};
+      const size_t v0 = t.vec.size();
+      t.vec.resize(v0 + kTileCols, -1);
+      for (size_t c = 0; c < t.g.size(); ++c) {
+        if (at[c] >= S.t0_h[size_t(t.g[c]) + 1] || key(at[c]) != best) continue;
+        const int32_t* e = &S.terms_h[size_t(4) * size_t(at[c]++)];
+        h = {e[0], e[2], 0, 0};
+        for (int k = 0; k < nrhs; ++k) t.vec[v0 + c * size_t(nrhs) + size_t(k)] = e[1] * nrhs + k;
+      }
+      t.head.push_back(h);
+    }
+  });
+  std::stable_sort(tiles.begin(), tiles.end(), [](const Tile& a, const Tile& b) { return a.head.size() > b.head.size(); });
+  std::vector<int32_t> t0(1, 0), gm, head, vec, dst;
+  for (const Tile& t : tiles) {
+    for (const auto& h : t.head) head.insert(head.end(), h.begin(), h.end());
+    vec.insert(vec.end(), t.vec.begin(), t.vec.end());
+    t0.push_back(int32_t(head.size() / 4));
+    gm.push_back(S.gm_h[size_t(t.g[0])]);
+    const size_t d0 = dst.size();
+    dst.resize(d0 + kTileCols, -1);
+    for (size_t c = 0; c < t.g.size(); ++c)
+      for (int k = 0; k < nrhs; ++k)
+        dst[d0 + c * size_t(nrhs) + size_t(k)] = (gdst ? (*gdst)[size_t(t.g[c])] : int32_t(t.g[c])) * nrhs + k;
+  }
+  T.ntiles = int64_t(tiles.size());
+  T.t0.upload(t0);
+  T.gm.upload(gm);
+  T.head.upload(head);
+  T.vec.upload(vec);
+  T.dst.upload(dst);
+  return true;
 }
 
 // Device bytes held by a plan (every table and operator array; the apply
@@ -1072,19 +1174,31 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
         gm[size_t(i)] = pad8(ops.hf[e][(in ? IS[l] : OS[l]).list[size_t(i)].second].r);
       return gm;
     };
+    // neighbourhood order of the slots of a level: by wedge, from width 1 down by
+    // octant (boxes of one octant have the same candidate offsets), then Morton
+    auto near_key = [&](int64_t cls, int l, int64_t b, bool octant) {
+      return (cls * 8 + (octant ? T.lv[size_t(l)].octant[size_t(b)] : 0)) << 32 | b;
+    };
+    auto slot_near = [&](int l, const std::vector<std::pair<int64_t, int>>& list, bool in) {
+      std::vector<int64_t> v;
+      for (const auto& s : list) v.push_back(near_key(s.second, l, s.first, in && l == D - 1));
+      return v;
+    };
     for (int e = 0; e <= e_top; ++e) {
       HFLevel& H = P.hf[size_t(e)];
       const int l = H.l;
       SlotKind up[2] = {{&H.m2m, hf_split}, {nullptr, 1}};
       build_slot_gemm(H.up, H.R, H.nout, slot_m(l, H.nout, false), up_terms[size_t(e)], up,
-                      e == 0 ? Rlf : P.hf[size_t(e - 1)].R);
+                      e == 0 ? Rlf : P.hf[size_t(e - 1)].R, slot_near(l, OS[l].list, false));
       SlotKind dn[2] = {{&H.m2l, hf_split}, {e < e_top ? &P.hf[size_t(e + 1)].l2l : nullptr, hf_split}};
       build_slot_gemm(H.down, H.R, H.nin, slot_m(l, H.nin, true), down_terms[size_t(e)], dn,
-                      std::max(H.R, e < e_top ? P.hf[size_t(e + 1)].R : 0));
+                      std::max(H.R, e < e_top ? P.hf[size_t(e + 1)].R : 0), slot_near(l, IS[l].list, true));
     }
+    std::vector<int64_t> lf_near;
+    for (int64_t b = 0; b < nD; ++b) lf_near.push_back(near_key(0, D, b, true));
     SlotKind dn[2] = {{&P.lf.m2l, 1}, {e_top >= 0 ? &P.hf[0].l2l : nullptr, hf_split}};
     build_slot_gemm(P.lf.down, Rlf, nD, std::vector<int32_t>(size_t(nD), Rlf), lf_terms, dn,
-                    std::max(Rlf, e_top >= 0 ? P.hf[0].R : 0));
+                    std::max(Rlf, e_top >= 0 ? P.hf[0].R : 0), lf_near);
     // adaptive levels below D.  LF-M2M: a group per split box of level l - 1
     // (written at its LF vector through up_dst), a term per child.  Downward: a
     // group per box of level l: its M2L pairs (kind 0, sources at their LF
@@ -1094,10 +1208,12 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
       const auto& Lc = T.lv[size_t(D + k)];
       std::vector<SlotTerm> up_t;
       std::vector<int32_t> up_dst;
+      std::vector<int64_t> up_near, dn_near;
       for (size_t p = 0; p < AL.box[size_t(k - 1)].size(); ++p) {
         if (!AL.split[size_t(k - 1)][p]) continue;
         const int32_t g = int32_t(up_dst.size());
         up_dst.push_back(int32_t(AL.base[size_t(k - 1)] + int64_t(p)));
+        up_near.push_back(int64_t(p));
         for (int64_t c = AL.c0[size_t(k - 1)][p]; c < AL.c1[size_t(k - 1)][p]; ++c)
           up_t.push_back({g, int32_t(Lc.octant[size_t(AL.box[size_t(k)][size_t(c)])]),
                           int32_t(Q.base + c), 0});
@@ -1105,8 +1221,9 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
       Q.nsplit = int64_t(up_dst.size());
       SlotKind uk[2] = {{&Q.m2m, 1}, {nullptr, 1}};
       build_slot_gemm(Q.up, Rlf, Q.nsplit, std::vector<int32_t>(up_dst.size(), pad8(lsk[size_t(k - 1)]->r)), up_t,
-                      uk, Rlf);
+                      uk, Rlf, up_near);
       Q.up_dst.upload(up_dst);
+      Q.up_dst_h = up_dst;
       std::vector<SlotTerm> dn_t;
       for (const SlotTerm& t : deep_m2l_terms[size_t(k)])
         dn_t.push_back({t.dst, t.op, int32_t(Q.base + t.src), 0});
@@ -1114,7 +1231,8 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
         dn_t.push_back({int32_t(b), int32_t(Lc.octant[size_t(AL.box[size_t(k)][size_t(b)])]),
                         int32_t(AL.base[size_t(k - 1)] + AL.par[size_t(k)][size_t(b)]), 1});
       SlotKind dk[2] = {{&Q.m2l, 1}, {&Q.l2l, 1}};
-      build_slot_gemm(Q.down, Rlf, Q.nb, std::vector<int32_t>(size_t(Q.nb), pad8(Q.r)), dn_t, dk, Rlf);
+      for (int64_t b = 0; b < Q.nb; ++b) dn_near.push_back(near_key(0, D + k, AL.box[size_t(k)][size_t(b)], true));
+      build_slot_gemm(Q.down, Rlf, Q.nb, std::vector<int32_t>(size_t(Q.nb), pad8(Q.r)), dn_t, dk, Rlf, dn_near);
       for (const SlotTerm& t : up_t) info.flops_m2m += Q.m2m.opflops[size_t(t.op)];
       for (int64_t b = 0; b < Q.nb; ++b) info.flops_l2l += Q.l2l.opflops[0];
     }
