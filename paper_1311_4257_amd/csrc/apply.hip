@@ -675,10 +675,10 @@ __device__ __forceinline__ void slot_tiles(const SlotTileArgs& a, float2* __rest
   const int lane = int(threadIdx.x) & 63;
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const int nw = int(blockDim.x) >> 6;
-  const int g = int(blockIdx.x);
+  const int g = int(blockIdx.y);
   const int tb = a.t0[g], te = a.t0[g + 1];
   const int Mg = a.gm[g];
-  const int m = int(blockIdx.y) * nw + wave;
+  const int m = int(blockIdx.x) * nw + wave;
   const bool act = 16 * m < Mg;  // wave-uniform: this wave's tile has operator rows
   const int rows = min(16, Mg - 16 * m);
   struct Tm {
@@ -1747,7 +1747,7 @@ static void launch_slot(const SlotLaunch& L, const float4* A0, const float2* X0,
     const int waves = std::max((nM + slices - 1) / slices, 3);
     auto kern = waves >= 6 ? (m2l ? &k_m2l_tiles<3> : &k_m2m_tiles<3>) : (m2l ? &k_m2l_tiles<6> : &k_m2m_tiles<6>);
     ensure_lds_limit(reinterpret_cast<const void*>(kern));
-    hipLaunchKernelGGL(kern, dim3(unsigned(T.ntiles), unsigned(slices)), dim3(unsigned(64 * waves)),
+    hipLaunchKernelGGL(kern, dim3(unsigned(slices), unsigned(T.ntiles)), dim3(unsigned(64 * waves)),
                        slot_col_units(S, 1) * 16, st, t, Y);
     return;
   }

@@ -269,7 +269,7 @@ __global__ void __launch_bounds__(256) k_slot64(const Slot64Args a, int nrhs, do
 // (0.8 MB at rank 232) for every term of every slot; here about 5 of 16 columns
 // of a term are in use.  A column's products and their order are those of the
 // form above, so the two give the same bits.  A wave takes MT row tiles of the
-// slice blockIdx.y, with the operator rows of T64_RING steps in flight (a step
+// slice blockIdx.x, with the operator rows of T64_RING steps in flight (a step
 // is 256 matrix-core cycles; 12 steps measured the same).  Eight waves share the
 // 60 KB of staged columns (rank 232): two workgroups of 8 fit a CU, two of 4
 // left half of its wave slots empty and ran a second round.  A term's columns, and the
@@ -302,10 +302,10 @@ __global__ void __launch_bounds__(64 * T64_NW, 4) k_tile64(const Tile64Args a, d
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 15, kr = lane >> 4;
   const bool odd = (j & 1) != 0;
-  const int g = int(blockIdx.x);
+  const int g = int(blockIdx.y);
   const int tb = a.t0[g], te = a.t0[g + 1];
   const int nM = a.gm[g] / 8;
-  const int m0 = int(blockIdx.y) * T64_NW + wave, mstep = T64_NW * int(gridDim.y);
+  const int m0 = int(blockIdx.x) * T64_NW + wave, mstep = T64_NW * int(gridDim.x);
   v4d acc[MT];
 #pragma unroll
   for (int t = 0; t < MT; ++t) acc[t] = v4d{0.0, 0.0, 0.0, 0.0};
@@ -476,7 +476,9 @@ void launch_slot64(const SlotGemm& S, const SlotTiles* T, const double4* A0, con
     const int nM = S.M / 8;
     const bool two = T->ntiles * ((nM + 2 * T64_NW - 1) / (2 * T64_NW)) >= 512;
     const int per = (two ? 2 : 1) * T64_NW;
-    const dim3 grid(unsigned(T->ntiles), unsigned((nM + per - 1) / per));
+    // the slices first: workgroups go to the 8 XCDs in turn, so the tiles on one of
+    // them read the same rows of every operator
+    const dim3 grid(unsigned((nM + per - 1) / per), unsigned(T->ntiles));
     auto kern = two ? &k_tile64<2> : &k_tile64<1>;
     lds_limit64(reinterpret_cast<const void*>(kern));
     hipLaunchKernelGGL(kern, grid, dim3(64 * T64_NW), sizeof(double4) * 16 * size_t(a.S), st, t, Y);
