@@ -802,6 +802,42 @@ __global__ void k_reduce(const int* __restrict__ rs, const int* __restrict__ ri,
   U[t] = make_float2(float(ax), float(ay));
 }
 
+// A level's L2L and M2L pairs in one pass: U[slot] = (float)(sum of the L2L pairs) +
+// sum of the M2L pairs, the values of k_reduce over the one and then, accumulating,
+// over the other.  The two passes wrote U and read it back, and at one right-hand
+// side each costs a launch and a tail of its own (7 us of 182 on the K = 8 sphere).
+__global__ void k_reduce2(const int* __restrict__ ls, const int* __restrict__ li, const float2* __restrict__ YL,
+                          const int* __restrict__ rs, const int* __restrict__ ri, const float2* __restrict__ Y,
+                          int64_t nslot, int RN, float2* __restrict__ U) {
+  const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (t >= nslot * RN) return;
+  const int64_t s = t / RN;
+  const int e = int(t % RN);
+  double ax = 0.0, ay = 0.0;
+  auto sum = [&](const int* st, const int* ix, const float2* y) {
+    int j = st[s];
+    const int j1 = st[s + 1];
+    for (; j + 4 <= j1; j += 4) {  // four loads in flight, added in order
+      const float2 y0 = y[int64_t(ix[j]) * RN + e], y1 = y[int64_t(ix[j + 1]) * RN + e];
+      const float2 y2 = y[int64_t(ix[j + 2]) * RN + e], y3 = y[int64_t(ix[j + 3]) * RN + e];
+      ax += y0.x; ay += y0.y;
+      ax += y1.x; ay += y1.y;
+      ax += y2.x; ay += y2.y;
+      ax += y3.x; ay += y3.y;
+    }
+    for (; j < j1; ++j) {
+      const float2 v = y[int64_t(ix[j]) * RN + e];
+      ax += v.x;
+      ay += v.y;
+    }
+  };
+  sum(ls, li, YL);
+  ax = double(float(ax));
+  ay = double(float(ay));
+  sum(rs, ri, Y);
+  U[t] = make_float2(float(ax), float(ay));
+}
+
 // ---- leaf evaluation: L2T plus the near-field sum, written in user order ----------
 // One wave per leaf.  Lane = (target t = lane % 16, slice s = lane / 16): the
 // wave takes the leaf's targets 16 at a time and every lane sums over a quarter
@@ -2386,45 +2422,64 @@ void run_apply(dfmm_plan_s& P, const ReqTable& R, int nrhs, hipStream_t st, void
     launch_fused(P, S, LS.fused, nrhs, st);
     mark(ST_M2L);
   }
+  // Fast plans reduce a level's L2L and M2L pairs in one pass (the pair scratch
+  // holds the transfers' outputs beside the M2L's); precise plans, whose scratch
+  // holds one launch's outputs, in two.
+  const bool both = !P.precise;
+  float2* ys = S.Y.as<float2>();
+  float2* ym = both ? ys + pair_rows_transfer(P) * nrhs : ys;  // separate M2L launches' outputs
+  auto m2l_gemm = [&](int e) {  // level e (-1: the leaves); returns its pair outputs
+    if (fused) return ym2l[e >= 0 ? size_t(e) : P.hf.size()];
+    launch_gemm(e >= 0 ? LS.m2l[size_t(e)] : LS.lf_m2l, nrhs, e >= 0 ? S.F[size_t(e)].as<float2>() : S.flf.as<float2>(),
+                ym, st);
+    mark(e >= 0 ? ST_M2L : ST_LF_M2L);
+    return static_cast<const float2*>(ym);
+  };
+  auto reduce_m2l = [&](int e, const float2* y, int accumulate) {
+    const int RN = (e >= 0 ? P.hf[size_t(e)].R : Rl) * nrhs;
+    const int64_t n = e >= 0 ? P.hf[size_t(e)].nin : P.lf.nbox;
+    const DevBuf& rs = e >= 0 ? P.hf[size_t(e)].red_start : P.lf.red_start;
+    const DevBuf& ri = e >= 0 ? P.hf[size_t(e)].red_idx : P.lf.red_idx;
+    hipLaunchKernelGGL(k_reduce, dim3(nblocks(n * RN, 256)), dim3(256), 0, st, rs.as<int>(), ri.as<int>(), y, n, RN,
+                       accumulate, e >= 0 ? S.U[size_t(e)].as<float2>() : S.ulf.as<float2>());
+    mark(e >= 0 ? ST_REDUCE : ST_LF_REDUCE);
+  };
+  if (!LS.slot && top_m2l) reduce_m2l(e_top, m2l_gemm(e_top), 0);
   for (int e = e_top; e >= 0 && !LS.slot; --e) {
     HFLevel& H = P.hf[e];
-    if (LS.m2l[e].nchunks > 0) {
-      if (!fused) {
-        launch_gemm(LS.m2l[e], nrhs, S.F[e].as<float2>(), S.Y.as<float2>(), st);
-        mark(ST_M2L);
-      }
-      int RN = H.R * nrhs;
-      hipLaunchKernelGGL(k_reduce, dim3(nblocks(H.nin * RN, 256)), dim3(256), 0, st, H.red_start.as<int>(),
-                         H.red_idx.as<int>(), ym2l[size_t(e)], H.nin, RN, e == e_top ? 0 : 1,
-                         S.U[e].as<float2>());
-      mark(ST_REDUCE);
-    }
     float2* Uc = e == 0 ? S.ulf.as<float2>() : S.U[e - 1].as<float2>();
-    launch_gemm(LS.l2l[e], nrhs, S.U[e].as<float2>(), S.Y.as<float2>(), st);
-    int RNc = H.Rc * nrhs;
+    launch_gemm(LS.l2l[e], nrhs, S.U[e].as<float2>(), ys, st);
+    const int RNc = H.Rc * nrhs;
+    const bool m2l = (e == 0 ? LS.lf_m2l : LS.m2l[size_t(e - 1)]).nchunks > 0;  // the children have M2L pairs
+    // one pass while the L2L outputs stay in the Infinity Cache until the M2L has run
+    // (64 MB of 256; the K = 32 sphere at 4 rhs, with 300 MB, lost 2% to it)
+    const bool small = H.l2l_npairs * RNc * int64_t(sizeof(float2)) <= int64_t(64) << 20;
+    if (both && small && m2l && H.nchild_in > 0) {
+      mark(ST_L2L);
+      const float2* y = m2l_gemm(e - 1);
+      const DevBuf& rs = e > 0 ? P.hf[size_t(e - 1)].red_start : P.lf.red_start;
+      const DevBuf& ri = e > 0 ? P.hf[size_t(e - 1)].red_idx : P.lf.red_idx;
+      hipLaunchKernelGGL(k_reduce2, dim3(nblocks(H.nchild_in * RNc, 256)), dim3(256), 0, st, H.l2l_rs.as<int>(),
+                         H.l2l_ri.as<int>(), ys, rs.as<int>(), ri.as<int>(), y, H.nchild_in, RNc, Uc);
+      mark(e > 0 ? ST_REDUCE : ST_LF_REDUCE);
+      continue;
+    }
     if (H.nchild_in > 0)
       hipLaunchKernelGGL(k_reduce, dim3(nblocks(H.nchild_in * RNc, 256)), dim3(256), 0, st, H.l2l_rs.as<int>(),
-                         H.l2l_ri.as<int>(), S.Y.as<float2>(), H.nchild_in, RNc, 0, Uc);
+                         H.l2l_ri.as<int>(), ys, H.nchild_in, RNc, 0, Uc);
     mark(ST_L2L);
+    if (m2l) reduce_m2l(e - 1, m2l_gemm(e - 1), 1);
   }
   // without HF levels nothing has written the LF incoming slots: the LF
   // reduction writes them itself, or they are cleared if it does not run
-  if (e_top < 0 && !LS.slot && LS.lf_m2l.nchunks == 0) {
-    int64_t n = P.lf.nbox * Rl * nrhs;
-    hipLaunchKernelGGL(k_zero, dim3(nblocks(n, 256)), dim3(256), 0, st, S.ulf.as<float2>(), n);
-    mark(ST_ZERO);
-  }
-  // LF-M2L
-  if (!LS.slot && LS.lf_m2l.nchunks > 0) {
-    if (!fused) {
-      launch_gemm(LS.lf_m2l, nrhs, S.flf.as<float2>(), S.Y.as<float2>(), st);
-      mark(ST_LF_M2L);
+  if (e_top < 0 && !LS.slot) {
+    if (LS.lf_m2l.nchunks > 0) {
+      reduce_m2l(-1, m2l_gemm(-1), 0);
+    } else {
+      int64_t n = P.lf.nbox * Rl * nrhs;
+      hipLaunchKernelGGL(k_zero, dim3(nblocks(n, 256)), dim3(256), 0, st, S.ulf.as<float2>(), n);
+      mark(ST_ZERO);
     }
-    int RN = Rl * nrhs;
-    hipLaunchKernelGGL(k_reduce, dim3(nblocks(P.lf.nbox * RN, 256)), dim3(256), 0, st, P.lf.red_start.as<int>(),
-                       P.lf.red_idx.as<int>(), ym2l[P.hf.size()], P.lf.nbox, RN, e_top >= 0 ? 1 : 0,
-                       S.ulf.as<float2>());
-    mark(ST_LF_REDUCE);
   }
   if (own) DFMM_HIP(hipStreamWaitEvent(st, AS.join, 0));
   if (Rl > 16 * L2T_QMAX || Rl % 2 != 0) throw Error{DFMM_EUNSUPPORTED, "leaf skeleton rank unsupported by L2T"};
