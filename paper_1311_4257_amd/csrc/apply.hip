@@ -317,22 +317,24 @@ __global__ void __launch_bounds__(64 * S2M_MT_NW) k_s2m_mfma(const int* __restri
 // products, which grows with their length, stays at that of one step.
 struct GgArgs {
   const float4* A;
-  const int64_t* aoff;
-  const int* aexp;
-  const int* gmk;
-  const int* gops;
-  const int* gv0;
   const int* vsrc;
   const float2* X;
   float2* Y;
   int M, K;  // row strides of the Y and X vectors
-  int half;  // 8 columns per chunk instead of 16 (operators too long for LDS with 16; 16-column launches only)
+};
+// A workgroup's work, read in one go: through the group's tables (chunk, group,
+// operator, offset) the first load of operator rows was the fourth in a chain,
+// which the launches of small problems consist of.
+struct GgChunk {
+  int aoff, aoff_hi;  // its operator's float4 offset
+  int mk;             // the operator's rows | columns << 16
+  int aexp;           // its scale exponent (FP16X3)
+  int vbeg, c0, nc;   // the group's first vector; the chunk's first column and its columns
+  int prob;           // problem (fused launch)
 };
 
 template <int NT, bool ACC64, int OP>
-__device__ __forceinline__ void ggemm_tile(const GgArgs& a, const int* __restrict__ chunk_grp,
-                                           const int* __restrict__ chunk_c0, int nrhs, int chunk, int slice,
-                                           int nslices) {
+__device__ __forceinline__ void ggemm_tile(const GgArgs& a, const GgChunk& ch, int nrhs, int slice, int nslices) {
   extern __shared__ float4 xs4[];
   __shared__ int cexp[16 * NT];  // FP16X3: power-of-two scale exponent of each column
   constexpr int NC = NT * 16, AW = OpForm<OP>::AW;
@@ -340,20 +342,17 @@ __device__ __forceinline__ void ggemm_tile(const GgArgs& a, const int* __restric
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const int nw = int(blockDim.x) >> 6;
-  const int g = chunk_grp[chunk];
-  const int Mg = a.gmk[2 * g], Kg = a.gmk[2 * g + 1];  // this group's operator size
+  const int Mg = ch.mk & 0xFFFF, Kg = int(unsigned(ch.mk) >> 16);  // this group's operator size
   const OpRows o(Kg, lane);
   const int cs = col_units(Kg, OpForm<OP>::PB);
   const int nM = (Mg + 15) / 16, nMall = (a.M + 15) / 16;  // row tiles with data / in the vector stride
   const int m0 = wave + nw * slice, mstep = nw * nslices;
   const int mcnt = m0 < nM ? (nM - m0 + mstep - 1) / mstep : 0;
-  const int c0 = chunk_c0[chunk];
-  const int vbeg = a.gv0[g];
-  const int64_t ncol = int64_t(a.gv0[g + 1] - vbeg) * nrhs;
-  const int ncmax = NT == 1 && a.half ? 8 : NC;
-  const int nc = int(min<int64_t>(ncmax, ncol - c0));
-  const int op = a.gops[g];
-  const float4* Aop = a.A + a.aoff[op];
+  const int c0 = ch.c0, vbeg = ch.vbeg, nc = ch.nc;
+  // Columns past nc are neither staged nor stored: whatever LDS holds there stays
+  // in its own output column.  Up to 8 columns may have LDS for 8 only.
+  const int jcol = nc <= 8 ? o.j & 7 : o.j;
+  const float4* Aop = a.A + ((int64_t(ch.aoff_hi) << 32) | unsigned(ch.aoff));
   const int tile4 = 2 * Kg * AW;  // float4 of a full row tile
   float4 raw[AW];
   auto tile = [&](int m) { return OpTile<OP>(o, Aop + m * tile4, min(16, Mg - 16 * m)); };
@@ -374,20 +373,20 @@ __device__ __forceinline__ void ggemm_tile(const GgArgs& a, const int* __restric
       if (s < 0 || q >= per_col) return make_float4(0.f, 0.f, 0.f, 0.f);
       return reinterpret_cast<const float4*>(a.X + int64_t(s) * a.K)[q];
     };
-    for (int cb = wave; cb < ncmax; cb += UB * nw) {
+    for (int cb = wave; cb < nc; cb += UB * nw) {
       float4 v[UB];
       int e[UB];
 #pragma unroll
       for (int u = 0; u < UB; ++u) {
         const int col = cb + u * nw;
         e[u] = 0;
-        v[u] = col < ncmax ? at(col, lane) : make_float4(0.f, 0.f, 0.f, 0.f);
+        v[u] = col < nc ? at(col, lane) : make_float4(0.f, 0.f, 0.f, 0.f);
       }
       if constexpr (OP == OP_F16) {  // largest column entry below 2^14 after scaling
 #pragma unroll
         for (int u = 0; u < UB; ++u) {
           const int col = cb + u * nw;
-          if (col >= ncmax) break;
+          if (col >= nc) break;
           float mx = 0.f;
           for (int q = lane;;) {
             const float4 w = q == lane ? v[u] : at(col, q);
@@ -407,7 +406,7 @@ __device__ __forceinline__ void ggemm_tile(const GgArgs& a, const int* __restric
 #pragma unroll
       for (int u = 0; u < UB; ++u) {
         const int col = cb + u * nw;
-        if (col >= ncmax) break;
+        if (col >= nc) break;
         unsigned* xc = reinterpret_cast<unsigned*>(xs + col * cs);
         for (int q0 = 0; q0 < pad_col; q0 += 64) {
           float4 w = q0 == 0 ? v[u] : at(col, q0 + lane);
@@ -423,12 +422,11 @@ __device__ __forceinline__ void ggemm_tile(const GgArgs& a, const int* __restric
   float osc[NT];
   if constexpr (OP == OP_F16) {
     // operator scale of the group and column scales: the sums are unscaled at the write
-    const int ea = a.aexp[op];
+    const int ea = ch.aexp;
 #pragma unroll
-    for (int n = 0; n < NT; ++n) osc[n] = ldexpf(1.0f, -(ea + cexp[n * 16 + (ncmax < 16 ? o.j & 7 : o.j)]));
+    for (int n = 0; n < NT; ++n) osc[n] = ldexpf(1.0f, -(ea + cexp[n * 16 + jcol]));
   }
   float2* yb = a.Y + (int64_t(vbeg) * nrhs + c0) * a.M + 4 * o.kr;  // lane: rows 4 kr .. 4 kr + 3 of a tile
-  const int jcol = ncmax < 16 ? o.j & 7 : o.j;
   using Acc = typename std::conditional<ACC64, double, float>::type;
   Acc re[NT][4], im[NT][4];
   for (int m = m0; m < nM; m += mstep) {
@@ -483,15 +481,16 @@ constexpr int GG_MINW = 2, GG_MAXW = 8;  // waves per workgroup
 // Waves per SIMD that the registers have to allow: 4 for up to 32 columns.
 #define DFMM_GG_BOUNDS(NT, OP) __launch_bounds__(64 * GG_MAXW, OP == OP_P4 ? 2 : 4)
 template <int NT, bool ACC64, int OP>
-__global__ void DFMM_GG_BOUNDS(NT, (ACC64 ? OP_P4 : OP)) k_m2l(const GgArgs a, const int* __restrict__ chunk_grp,
-                                                      const int* __restrict__ chunk_c0, int nrhs) {
-  ggemm_tile<NT, ACC64, OP>(a, chunk_grp, chunk_c0, nrhs, int(blockIdx.x), int(blockIdx.y), int(gridDim.y));
+__global__ void DFMM_GG_BOUNDS(NT, (ACC64 ? OP_P4 : OP)) k_m2l(const GgArgs a, const GgChunk* __restrict__ chunks,
+                                                               int nrhs) {
+  ggemm_tile<NT, ACC64, OP>(a, chunks[blockIdx.x], nrhs, int(blockIdx.y), int(gridDim.y));
 }
 template <int NT, bool ACC64, int OP>
-__global__ void DFMM_GG_BOUNDS(NT, (ACC64 ? OP_P4 : OP)) k_transfer(const GgArgs a, const int* __restrict__ chunk_grp,
-                                                           const int* __restrict__ chunk_c0, int nrhs) {
-  ggemm_tile<NT, ACC64, OP>(a, chunk_grp, chunk_c0, nrhs, int(blockIdx.x), int(blockIdx.y), int(gridDim.y));
+__global__ void DFMM_GG_BOUNDS(NT, (ACC64 ? OP_P4 : OP)) k_transfer(const GgArgs a, const GgChunk* __restrict__ chunks,
+                                                                    int nrhs) {
+  ggemm_tile<NT, ACC64, OP>(a, chunks[blockIdx.x], nrhs, int(blockIdx.y), int(gridDim.y));
 }
+
 // All M2L launches of an apply (every HF level and the leaf level) in one
 // launch: they read only the upward pass's outputs, so their chunks can share
 // the GPU (the HBM-bound HF chunks beside the compute-bound leaf-level ones).
@@ -502,11 +501,9 @@ struct GgProbs {
   GgArgs p[kMaxProbs];
 };
 template <int NT, int OP>
-__global__ void DFMM_GG_BOUNDS(NT, OP) k_m2l_fused(const GgProbs P, const int* __restrict__ chunk_ps,
-                                                   const int* __restrict__ chunk_grp,
-                                                   const int* __restrict__ chunk_c0, int nrhs) {
-  const int c = int(blockIdx.x);
-  ggemm_tile<NT, false, OP>(P.p[chunk_ps[c]], chunk_grp, chunk_c0, nrhs, c, 0, 1);
+__global__ void DFMM_GG_BOUNDS(NT, OP) k_m2l_fused(const GgProbs P, const GgChunk* __restrict__ chunks, int nrhs) {
+  const GgChunk& ch = chunks[blockIdx.x];
+  ggemm_tile<NT, false, OP>(P.p[ch.prob], ch, nrhs, 0, 1);
 }
 
 // ---- slot-form GEMM: every output slot sums its terms in registers ---------------
@@ -1439,16 +1436,17 @@ __global__ void k_zero(float2* __restrict__ p, int64_t n) {
 
 }  // namespace
 
-// Work chunks of a grouped GEMM for a given nrhs: (group, first column) per workgroup.
-static void make_chunks(const GGemm& G, int nrhs, int NC, std::vector<int32_t>& grp, std::vector<int32_t>& col0) {
-  grp.clear();
-  col0.clear();
+// Work chunks of a grouped GEMM for a given nrhs: NC columns of a group each.
+static void make_chunks(const GGemm& G, int nrhs, int NC, int prob, std::vector<GgChunk>& v) {
   for (int64_t g = 0; g < G.ngroups; ++g) {
-    int64_t ncol = int64_t(G.v0_h[g + 1] - G.v0_h[g]) * nrhs;
-    for (int64_t c = 0; c < ncol; c += NC) {
-      grp.push_back(int32_t(g));
-      col0.push_back(int32_t(c));
-    }
+    const int64_t ncol = int64_t(G.v0_h[g + 1] - G.v0_h[g]) * nrhs;
+    const size_t op = size_t(G.ops_h[size_t(g)]);
+    const int64_t off = G.aoff_h[op];
+    const int M = G.gmk_h[2 * size_t(g)], K = G.gmk_h[2 * size_t(g) + 1];
+    if (M > 0xFFFF || K > 0x7FFF) throw Error{DFMM_EUNSUPPORTED, "skeleton rank too large for the GEMM kernel"};
+    for (int64_t c = 0; c < ncol; c += NC)
+      v.push_back(GgChunk{int(off & 0xFFFFFFFF), int(off >> 32), M | K << 16, G.aexp_h.empty() ? 0 : G.aexp_h[op],
+                          G.v0_h[g], int(c), int(std::min<int64_t>(NC, ncol - c)), prob});
   }
 }
 
@@ -1459,7 +1457,7 @@ struct Launch {        // one grouped-GEMM launch prepared for the current nrhs
   int nw = 4;          // waves per workgroup
   bool m2l = false;    // translation launch (kernel name k_m2l) or tree transfer (k_transfer)
   int64_t nchunks = 0;
-  DevBuf grp, col0;
+  DevBuf chunks;       // GgChunk[nchunks]
 };
 
 // All M2L launches of an apply fused into one k_m2l_fused launch, when the
@@ -1468,7 +1466,7 @@ struct Fused {
   int nt = 0;                 // 16-column tiles per workgroup; 0: separate launches
   int nw = 4;                 // waves per workgroup
   int64_t nchunks = 0;
-  DevBuf ps, grp, col0;       // per chunk: problem, group, first column
+  DevBuf chunks;              // GgChunk[nchunks]
   std::vector<int64_t> yoff;  // per problem: offset (float2) of its pair outputs in the pair scratch
 };
 
@@ -1579,17 +1577,15 @@ void destroy_apply_state(ApplyState* s) { delete s; }
 // so the chunk table is laid out such that the workgroups that land on one XCD
 // take a contiguous range of chunks (a group's chunks share that XCD's L2).
 constexpr int kXcds = 8;
-static void xcd_order(std::initializer_list<std::vector<int32_t>*> cols) {
-  const int64_t n = int64_t((*cols.begin())->size());
+static void xcd_order(std::vector<GgChunk>& v) {
+  const int64_t n = int64_t(v.size());
   if (n <= kXcds) return;
   int64_t start[kXcds + 1];
   start[0] = 0;
   for (int x = 0; x < kXcds; ++x) start[x + 1] = start[x] + (n - x + kXcds - 1) / kXcds;  // ids b = x mod 8
-  for (std::vector<int32_t>* v : cols) {
-    std::vector<int32_t> w(static_cast<size_t>(n));
-    for (int64_t b = 0; b < n; ++b) w[size_t(b)] = (*v)[size_t(start[b % kXcds] + b / kXcds)];
-    v->swap(w);
-  }
+  std::vector<GgChunk> w(static_cast<size_t>(n));
+  for (int64_t b = 0; b < n; ++b) w[size_t(b)] = v[size_t(start[b % kXcds] + b / kXcds)];
+  v.swap(w);
 }
 
 static bool gg_half(const GGemm& G);
@@ -1599,13 +1595,12 @@ static void prepare_cfg(Launch& L, const GGemm& G, int nrhs, int nt, int slices,
   L.G = &G;
   L.nt = nt;
   L.nw = nw;
-  std::vector<int32_t> grp, col0;
-  make_chunks(G, nrhs, L.nt == 1 && gg_half(G) ? 8 : L.nt * 16, grp, col0);
-  xcd_order({&grp, &col0});
-  L.nchunks = int64_t(grp.size());
+  std::vector<GgChunk> v;
+  make_chunks(G, nrhs, L.nt == 1 && gg_half(G) ? 8 : L.nt * 16, 0, v);
+  xcd_order(v);
+  L.nchunks = int64_t(v.size());
   L.slices = slices;
-  L.grp.upload(grp);
-  L.col0.upload(col0);
+  L.chunks.upload(v);
 }
 
 // dynamic LDS limit of the GEMM kernels: 160 KB less 1 KB for their static LDS
@@ -1658,9 +1653,7 @@ static void ensure_lds_limit(const void* fn) {
 }
 
 static GgArgs gg_args(const GGemm& G, const float2* X, float2* Y) {
-  return GgArgs{G.A.as<float4>(), G.aoff.as<int64_t>(), G.aexp.as<int>(), G.gmk.as<int>(), G.ops.as<int>(),
-                G.v0.as<int>(),   G.vsrc.as<int>(),     X,                Y,               G.M,
-                G.K,              gg_half(G) ? 1 : 0};
+  return GgArgs{G.A.as<float4>(), G.vsrc.as<int>(), X, Y, G.M, G.K};
 }
 
 template <int NT, bool ACC64, int OP>
@@ -1669,7 +1662,7 @@ static void launch_nt_a(const Launch& L, int nrhs, const float2* X, float2* Y, h
   auto kern = L.m2l ? &k_m2l<NT, ACC64, OP> : &k_transfer<NT, ACC64, OP>;
   ensure_lds_limit(reinterpret_cast<const void*>(kern));
   hipLaunchKernelGGL(kern, dim3(unsigned(L.nchunks), unsigned(L.slices)), dim3(unsigned(64 * L.nw)), gg_lds_used(G, NT), st,
-                     gg_args(G, X, Y), L.grp.as<int>(), L.col0.as<int>(), nrhs);
+                     gg_args(G, X, Y), L.chunks.as<GgChunk>(), nrhs);
 }
 
 template <int NT>
@@ -1840,36 +1833,28 @@ static bool fused_fits(const dfmm_plan_s& P, int nt) {
 
 static void prepare_fused(const dfmm_plan_s& P, int nrhs, int nt, Fused& F) {
   const auto probs = m2l_problems(P);
-  std::vector<int32_t> ps, grp, col0;
+  std::vector<GgChunk> v;
   F.yoff.clear();
   int64_t off = pair_rows_transfer(P) * nrhs;  // past the transfers' scratch
+  int nM = 1;
   for (size_t i = 0; i < probs.size(); ++i) {
-    std::vector<int32_t> g1, c1;
-    make_chunks(*probs[i], nrhs, nt == 1 && gg_half(*probs[i]) ? 8 : nt * 16, g1, c1);
-    for (size_t k = 0; k < g1.size(); ++k) {
-      ps.push_back(int32_t(i));
-      grp.push_back(g1[k]);
-      col0.push_back(c1[k]);
-    }
+    make_chunks(*probs[i], nrhs, nt == 1 && gg_half(*probs[i]) ? 8 : nt * 16, int(i), v);
     F.yoff.push_back(off);
     off += probs[i]->nvec * probs[i]->M * nrhs;
+    nM = std::max(nM, (probs[i]->M + 15) / 16);
   }
-  xcd_order({&ps, &grp, &col0});
+  xcd_order(v);
   F.nt = nt;
-  int nM = 1;
-  for (const GGemm* G : probs) nM = std::max(nM, (G->M + 15) / 16);
-  F.nw = std::max(std::min(nM, GG_MAXW), 4);  // a wave per row tile
-  F.nchunks = int64_t(ps.size());
-  F.ps.upload(ps);
-  F.grp.upload(grp);
-  F.col0.upload(col0);
+  F.nw = std::min(nM, GG_MAXW);  // a wave per row tile
+  F.nchunks = int64_t(v.size());
+  F.chunks.upload(v);
 }
 
 template <int NT, int OP>
 static void launch_fused_t(const GgProbs& pr, size_t lds, const Fused& F, int nrhs, hipStream_t st) {
   ensure_lds_limit(reinterpret_cast<const void*>(&k_m2l_fused<NT, OP>));
   hipLaunchKernelGGL((k_m2l_fused<NT, OP>), dim3(unsigned(F.nchunks)), dim3(unsigned(64 * F.nw)), lds, st, pr,
-                     F.ps.as<int>(), F.grp.as<int>(), F.col0.as<int>(), nrhs);
+                     F.chunks.as<GgChunk>(), nrhs);
 }
 
 template <int OP>

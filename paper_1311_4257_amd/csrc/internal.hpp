@@ -106,7 +106,7 @@ struct DevBuf {
 // ---- grouped gather GEMM (the MFMA engine of M2M, M2L and L2L) ---------------
 // Vectors are complex64, one per (slot, rhs), stored [slot][rhs][row].  A
 // launch computes, for every vector column v of every group g,
-//   Y[vdst[v]] = sum_{t < T} A[ops[g T + t]] X[vsrc[v T + t]]
+//   Y[v] = sum_{t < T} A[ops[g T + t]] X[vsrc[v T + t]]
 // (a term with source -1 contributes nothing).  Each operator is an M x K
 // complex matrix (M, K multiples of 8) stored in MFMA fragment order, see
 // pack_operator().
@@ -116,18 +116,16 @@ struct GGemm {
                              // vector is read twice, so the float32 rounding of T cancels
   bool acc64 = false;        // float64 partial sums every two k-steps (precise plans)
   int prec = 0;              // DFMM_PREC_*: FP16X3 / BF16X3 hold A as 16-bit hi + lo pairs, K padded
-                             // to 16 (kpad), one power-of-two scale exponent per operator (aexp)
-  DevBuf aexp;               // int32[nops] (FP16X3)
+                             // to 16 (kpad), one power-of-two scale exponent per operator (aexp_h)
   int64_t ngroups = 0, nvec = 0, nops = 0;
-  DevBuf A;                  // operators in fragment order, op i at float4 offset aoff[i]
-  DevBuf aoff;               // int64[nops]
-  DevBuf gmk;                // int32[ngroups][2]: (M_g, K_g) of the group's operators, multiples of 8
-  DevBuf ops;                // int32[ngroups][T]
-  DevBuf v0;                 // int32[ngroups + 1]: vector range of each group
+  DevBuf A;                  // operators in fragment order, op i at float4 offset aoff_h[i]
   DevBuf vsrc;               // int32[nvec][T]
-  DevBuf vdst;               // int32[nvec]
-  std::vector<int32_t> v0_h; // host copy of v0 (work chunking)
-  std::vector<int64_t> aoff_h;  // host copy of aoff, per operator index
+  // host tables (work chunks)
+  std::vector<int32_t> aexp_h;  // per operator: scale exponent (FP16X3)
+  std::vector<int32_t> gmk_h;   // per group: (M_g, K_g) of its operator, multiples of 8
+  std::vector<int32_t> ops_h;   // per group: its operator
+  std::vector<int32_t> v0_h;    // vector range of each group
+  std::vector<int64_t> aoff_h;  // per operator
   std::vector<int32_t> kpk_h;   // packed K of each operator index (split doubling included)
   std::vector<double> opflops;  // 8 r_out r_in of each operator index (unpadded ranks)
 };

@@ -268,7 +268,7 @@ struct OpStore {
   void upload(GGemm& G) {
     if (prec == DFMM_PREC_FP64) G.A.upload(d);
     else G.A.upload(f);
-    if (prec == DFMM_PREC_FP16X3 || prec == DFMM_PREC_BF16X3) G.aexp.upload(aexp);
+    if (prec == DFMM_PREC_FP16X3 || prec == DFMM_PREC_BF16X3) G.aexp_h = aexp;
   }
 };
 
@@ -426,8 +426,7 @@ bool build_slot_tiles(const SlotGemm& S, int nrhs, int row_tiles, SlotTiles& T, 
 // Device bytes held by a plan (every table and operator array; the apply
 // workspace is separate).
 static size_t gg_bytes(const GGemm& G) {
-  return G.aexp.bytes + G.A.bytes + G.aoff.bytes + G.gmk.bytes + G.ops.bytes + G.v0.bytes + G.vsrc.bytes +
-         G.vdst.bytes;
+  return G.A.bytes + G.vsrc.bytes;
 }
 static size_t slot_bytes(const SlotGemm& S) { return S.order.bytes + S.t0.bytes + S.gm.bytes + S.terms.bytes; }
 size_t plan_device_bytes(const dfmm_plan_s& P) {
@@ -785,8 +784,6 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
       ridx.insert(ridx.end(), v.begin(), v.end());
       rstart.push_back(int32_t(ridx.size()));
     }
-    std::vector<int32_t> vdst(vsrc.size());
-    for (size_t i = 0; i < vdst.size(); ++i) vdst[i] = int32_t(i);
     OpStore At(P.prec, size_t(2) * R * R * split * ngroups, ngroups);
     std::vector<int32_t> gmk(size_t(2) * ngroups);
     std::vector<int64_t> aoff(ngroups);
@@ -829,13 +826,10 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
     G.nvec = int64_t(vsrc.size());
     G.nops = ngroups;
     At.upload(G);
-    G.aoff.upload(aoff);
-    G.gmk.upload(gmk);
-    G.ops.upload(opsv);
-    G.v0.upload(v0);
+    G.gmk_h = gmk;
+    G.ops_h = opsv;
     G.v0_h = v0;
     G.vsrc.upload(vsrc);
-    G.vdst.upload(vdst);
     G.aoff_h = aoff;
     G.kpk_h.resize(size_t(ngroups));
     G.opflops.resize(size_t(ngroups));
@@ -957,7 +951,7 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
                             int K, int64_t nops, int64_t ndst, DevBuf& rs, DevBuf& ri, int64_t& npairs,
                             const std::vector<int32_t>& opM, const std::vector<int32_t>& opK) {
       // by_op[op] = list of (source vector, destination slot)
-      std::vector<int32_t> v0(1, 0), vsrc, vdst, opsv, gmk;
+      std::vector<int32_t> v0(1, 0), vsrc, opsv, gmk;
       std::vector<int64_t> aoff(nops);
       for (int64_t op = 0; op < nops; ++op) aoff[op] = op * int64_t(M) * K * hf_split / 2;
       std::vector<std::vector<int32_t>> per(ndst);
@@ -969,7 +963,6 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
         for (auto& sd : by_op[op]) {
           per[sd.second].push_back(int32_t(vsrc.size()));
           vsrc.push_back(sd.first);
-          vdst.push_back(int32_t(vdst.size()));
         }
         v0.push_back(int32_t(vsrc.size()));
       }
@@ -987,13 +980,10 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
       G.ngroups = int64_t(v0.size()) - 1;
       G.nvec = int64_t(vsrc.size());
       G.nops = nops;
-      G.aoff.upload(aoff);
-      G.gmk.upload(gmk);
-      G.ops.upload(opsv);
-      G.v0.upload(v0);
+      G.gmk_h = gmk;
+      G.ops_h = opsv;
       G.v0_h = v0;
       G.vsrc.upload(vsrc);
-      G.vdst.upload(vdst);
       G.aoff_h = aoff;
       G.kpk_h.resize(size_t(nops));
       for (int64_t op = 0; op < nops; ++op) G.kpk_h[size_t(op)] = opK[size_t(op)];
