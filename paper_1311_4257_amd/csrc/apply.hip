@@ -1478,7 +1478,7 @@ struct SlotLaunch {
   int waves = 1;       // waves per workgroup
   int cpg = 1;         // column chunks per group
   int64_t nchunks = 0;
-  std::unique_ptr<SlotTiles> tiles;  // tables for few right-hand sides (else null)
+  SlotTiles tiles;     // tables for few right-hand sides (else none)
 };
 
 // The GEMM launches of one nrhs (chunk tables and tuned shapes).
@@ -1490,6 +1490,7 @@ struct LaunchSet {
   std::vector<SlotLaunch> up, down;   // per HF level
   SlotLaunch lf_down;
   std::vector<SlotLaunch> lfd_up, lfd_down;  // per LF level below width 1/2 (adaptive trees)
+  DevBuf tile_buf;                    // the slot launches' tables for few right-hand sides
 };
 
 // The M2L problems of a plan in apply order: HF levels from the top down, then
@@ -1764,10 +1765,9 @@ static void launch_slot(const SlotLaunch& L, const float4* A0, const float2* X0,
   const SlotGemm& S = *L.S;
   SlotArgs a{S.order.as<int>(), S.t0.as<int>(), S.gm.as<int>(), S.terms.as<int4>(), A0, A1 ? A1 : A0, X0,
              X1 ? X1 : X0, KX0, X1 ? KX1 : KX0, S.M, L.cpg, int(slot_col_units(S, L.nt)), L.waves, gdst};
-  if (L.tiles) {
-    const SlotTiles& T = *L.tiles;
-    const SlotTileArgs t{T.t0.as<int>(), T.gm.as<int>(), T.head.as<int4>(), T.vec.as<int>(), T.dst.as<int>(),
-                         A0, a.A1, X0, a.X1, KX0, a.KX1, S.M};
+  if (L.tiles.ntiles > 0) {
+    const SlotTiles& T = L.tiles;
+    const SlotTileArgs t{T.t0, T.gm, T.head, T.vec, T.dst, A0, a.A1, X0, a.X1, KX0, a.KX1, S.M};
     // as few as three waves (row tiles) per workgroup until the launch has two
     // workgroups per CU; each slice stages the columns again
     const int nM = (S.M + 15) / 16;
@@ -1803,21 +1803,22 @@ static void prepare_slot_set(const dfmm_plan_s& P, int nrhs, LaunchSet& LS) {
   // few right-hand sides (adaptive trees; a uniform one takes the pair form there):
   // two neighbouring groups or more share a tile's 16 columns
   if (2 * nrhs > kTileCols) return;
-  auto tiles = [&](SlotLaunch& L, const std::vector<int32_t>* gdst = nullptr) {
-    std::unique_ptr<SlotTiles> t(new SlotTiles());
-    if (L.S->ngroups > 0 && L.S->Kmax <= 128 && build_slot_tiles(*L.S, nrhs, (L.S->M + 15) / 16, *t, gdst)) L.tiles = std::move(t);
+  std::vector<TileJob> jobs;
+  auto job = [&](SlotLaunch& L, const std::vector<int32_t>* gdst = nullptr) {
+    if (L.S->Kmax <= 128) jobs.push_back({L.S, (L.S->M + 15) / 16, gdst, &L.tiles});
   };
+  for (size_t e = 0; e < P.hf.size(); ++e) {
+    job(LS.up[e]);
+    job(LS.down[e]);
+  }
+  job(LS.lf_down);
+  for (size_t k = 0; k < P.lfd.size(); ++k) {
+    job(LS.lfd_up[k], &P.lfd[k].up_dst_h);
+    job(LS.lfd_down[k]);
+  }
   try {
-    for (size_t e = 0; e < P.hf.size(); ++e) {
-      tiles(LS.up[e]);
-      tiles(LS.down[e]);
-    }
-    tiles(LS.lf_down);
-    for (size_t k = 0; k < P.lfd.size(); ++k) {
-      tiles(LS.lfd_up[k], &P.lfd[k].up_dst_h);
-      tiles(LS.lfd_down[k]);
-    }
-  } catch (const Error& e) {  // no memory for the rest of the tables: the general form needs none
+    build_slot_tiles(jobs, nrhs, LS.tile_buf);
+  } catch (const Error& e) {  // no memory for the tables: the general form needs none
     if (e.code != DFMM_ENOMEM) throw;
   }
 }

@@ -469,8 +469,7 @@ void launch_slot64(const SlotGemm& S, const SlotTiles* T, const double4* A0, con
   if (sizeof(double4) * 16 * size_t(a.S) > size_t(kLds64))
     throw Error{DFMM_EUNSUPPORTED, "skeleton rank too large for the float64 slot GEMM"};
   if (T && T->ntiles > 0 && S.Kmax <= T64_MAXK) {
-    Tile64Args t{T->t0.as<int>(), T->gm.as<int>(), T->head.as<int4>(), T->vec.as<int>(), T->dst.as<int>(),
-                 A0, a.A1, X0, a.X1, KX0, a.KX1, S.M, a.S};
+    Tile64Args t{T->t0, T->gm, T->head, T->vec, T->dst, A0, a.A1, X0, a.X1, KX0, a.KX1, S.M, a.S};
     // one row tile per wave until the launch has two workgroups per CU, then two:
     // each slice stages the columns again
     const int nM = S.M / 8;
@@ -493,15 +492,15 @@ void launch_slot64(const SlotGemm& S, const SlotTiles* T, const double4* A0, con
 }  // namespace
 
 Tiles64::Tiles64(const dfmm_plan_s& P, int nrhs) : up(P.hf.size()), down(P.hf.size()) {
-  bool ok = build_slot_tiles(P.lf.down, nrhs, P.lf.down.M / 8, lf);
-  for (size_t e = 0; e < P.hf.size(); ++e)
-    ok = build_slot_tiles(P.hf[e].up, nrhs, P.hf[e].up.M / 8, up[e]) &&
-         build_slot_tiles(P.hf[e].down, nrhs, P.hf[e].down.M / 8, down[e]) && ok;
-  usable = ok;
+  std::vector<TileJob> jobs{{&P.lf.down, P.lf.down.M / 8, nullptr, &lf}};
+  for (size_t e = 0; e < P.hf.size(); ++e) {
+    jobs.push_back({&P.hf[e].up, P.hf[e].up.M / 8, nullptr, &up[e]});
+    jobs.push_back({&P.hf[e].down, P.hf[e].down.M / 8, nullptr, &down[e]});
+  }
+  build_slot_tiles(jobs, nrhs, buf);
 }
 
 void run_apply64(dfmm_plan_s& P, const double2* f, double2* u, int nrhs, hipStream_t st, void* ws, const Tiles64* T) {
-  if (T && !T->usable) T = nullptr;
   const WsLayout L = ws_layout(ws_shape64(P), nrhs, false, 16);
   if (!ws) throw Error{DFMM_EINVAL, "no workspace"};
   char* b = static_cast<char*>(ws);

@@ -168,15 +168,24 @@ struct SlotGemm {
 constexpr int kTileCols = 16;
 struct SlotTiles {
   int64_t ntiles = 0;
-  DevBuf t0;    // int32[ntiles + 1]: term range of each tile (longest first)
-  DevBuf gm;    // int32[ntiles]: padded rows
-  DevBuf head;  // int32[nterms][4]: (operator offset, K | kind << 14, 0, 0)
-  DevBuf vec;   // int32[nterms][kTileCols]: source vector (slot nrhs + rhs) of each column, -1: none
-  DevBuf dst;   // int32[ntiles][kTileCols]: output vector of each column, -1: none
+  // device tables (in the buffer of build_slot_tiles)
+  const int* t0 = nullptr;    // [ntiles + 1]: term range of each tile (longest first)
+  const int* gm = nullptr;    // [ntiles]: padded rows
+  const int4* head = nullptr; // [nterms]: (operator offset, K | kind << 14, 0, 0)
+  const int* vec = nullptr;   // [nterms][kTileCols]: source vector (slot nrhs + rhs) of each column, -1: none
+  const int* dst = nullptr;   // [ntiles][kTileCols]: output vector of each column, -1: none
 };
-// False if the groups' terms have no common order (the tables are then not made).
-// row_tiles: row tiles (waves) of a tile in the kernel that uses the tables.
-bool build_slot_tiles(const SlotGemm& S, int nrhs, int row_tiles, SlotTiles& T, const std::vector<int32_t>* gdst = nullptr);
+// One launch's tables to make.  row_tiles: row tiles (waves) of a tile in the kernel
+// that uses them; gdst: output vector of each group (null: its own index).
+struct TileJob {
+  const SlotGemm* S;
+  int row_tiles;
+  const std::vector<int32_t>* gdst;
+  SlotTiles* out;
+};
+// Makes the tables of all jobs in one device buffer.  A job whose groups' terms have
+// no common order keeps ntiles = 0.
+void build_slot_tiles(const std::vector<TileJob>& jobs, int nrhs, DevBuf& buf);
 // Host view of one kind's operators: float4 offset and packed K (split doubling
 // included) of every operator index, and the split factor.
 struct SlotKind {
@@ -357,7 +366,7 @@ constexpr int kTiles64Rhs = kTileCols / 2;
 struct Tiles64 {
   std::vector<SlotTiles> up, down;  // per HF level
   SlotTiles lf;
-  bool usable = false;
+  DevBuf buf;
   Tiles64(const dfmm_plan_s& P, int nrhs);
 };
 void run_apply64(dfmm_plan_s& P, const double2* f, double2* u, int nrhs, hipStream_t st, void* ws, const Tiles64* T);

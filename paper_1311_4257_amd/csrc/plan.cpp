@@ -329,98 +329,145 @@ void build_slot_gemm(SlotGemm& S, int M, int64_t ngroups, const std::vector<int3
   S.near_h = near;
 }
 
-bool build_slot_tiles(const SlotGemm& S, int nrhs, int row_tiles, SlotTiles& T, const std::vector<int32_t>* gdst) {
-  // groups of a tile: more of them share more operators (about 1.8 columns of a
-  // term in use with 4, 5 with 16), but leave fewer waves, one per row tile; as
-  // many as leave 1.5 waves for each of the 1,024 SIMDs
-  int per = kTileCols / nrhs;
-  while (per > 1 && (S.ngroups + per - 1) / per * row_tiles < 1536) per /= 2;
-  // the common order: the kind that groups start with, then the operator index
+namespace {
+struct HostTile {
+  std::vector<int64_t> g;    // its groups
+  std::vector<int32_t> at;   // where each of them stands in its terms
+  std::vector<int32_t> head, vec;
+};
+
+inline int term_kind(const SlotGemm& S, int32_t i) { return (S.terms_h[size_t(4) * size_t(i) + 2] >> 14) & 1; }
+
+// The common order of the groups' terms: the kind that they start with, then the
+// operator index.  Returns that kind, -1 if there is none.
+int common_order(const SlotGemm& S) {
   int first = -1;
-  for (int64_t g = 0; g < S.ngroups; ++g) {
-    int last_rank = -1, last_op = -1;
-    for (int32_t i = S.t0_h[size_t(g)]; i < S.t0_h[size_t(g) + 1]; ++i) {
-      const int kind = (S.terms_h[size_t(4) * size_t(i) + 2] >> 14) & 1;
-      // a group with one kind only fits either order; those with both decide it
-      if (i > S.t0_h[size_t(g)] && last_rank >= 0) {
-        const int prev = (S.terms_h[size_t(4) * size_t(i - 1) + 2] >> 14) & 1;
-        if (prev != kind) {
-          if (first >= 0 && first != prev) return false;
-          first = prev;
-        } else if (S.op_h[size_t(i)] <= last_op) {
-          return false;
+  for (int64_t g = 0; g < S.ngroups; ++g)
+    for (int32_t i = S.t0_h[size_t(g)] + 1; i < S.t0_h[size_t(g) + 1]; ++i) {
+      const int prev = term_kind(S, i - 1);
+      if (prev != term_kind(S, i)) {  // groups with both kinds decide it
+        if (first >= 0 && first != prev) return -1;
+        first = prev;
+      } else if (S.op_h[size_t(i)] <= S.op_h[size_t(i) - 1]) {
+        return -1;
+      }
+    }
+  return std::max(first, 0);
+}
+}  // namespace
+
+void build_slot_tiles(const std::vector<TileJob>& jobs, int nrhs, DevBuf& buf) {
+  std::vector<std::vector<HostTile>> all(jobs.size());
+  std::vector<int> first(jobs.size());
+  std::vector<std::pair<size_t, size_t>> work;  // (job, tile)
+  for (size_t q = 0; q < jobs.size(); ++q) {
+    const SlotGemm& S = *jobs[q].S;
+    jobs[q].out->ntiles = 0;
+    first[q] = common_order(S);
+    if (S.ngroups == 0 || first[q] < 0) continue;
+    // groups of a tile: more of them share more operators (about 1.8 columns of a
+    // term in use with 4, 5 with 16), but leave fewer waves, one per row tile; as
+    // many as leave 1.5 waves for each of the 1,024 SIMDs
+    int per = kTileCols / nrhs;
+    while (per > 1 && (S.ngroups + per - 1) / per * jobs[q].row_tiles < 1536) per /= 2;
+    std::vector<int64_t> gs(static_cast<size_t>(S.ngroups));
+    for (int64_t g = 0; g < S.ngroups; ++g) gs[size_t(g)] = g;
+    std::stable_sort(gs.begin(), gs.end(), [&](int64_t a, int64_t b) {
+      if (S.gm_h[size_t(a)] != S.gm_h[size_t(b)]) return S.gm_h[size_t(a)] < S.gm_h[size_t(b)];
+      return S.near_h[size_t(a)] < S.near_h[size_t(b)];
+    });
+    for (size_t i = 0; i < gs.size();) {
+      HostTile t;
+      while (i < gs.size() && int(t.g.size()) < per &&
+             (t.g.empty() || (S.gm_h[size_t(gs[i])] == S.gm_h[size_t(t.g[0])] &&
+                              (S.near_h[size_t(gs[i])] >> 32) == (S.near_h[size_t(t.g[0])] >> 32))))
+        t.g.push_back(gs[i++]);
+      work.push_back({q, all[q].size()});
+      all[q].push_back(std::move(t));
+    }
+  }
+  // merge the term lists of each tile's groups
+  constexpr size_t kStep = 16;  // tiles per task
+  parallel_for(int64_t((work.size() + kStep - 1) / kStep), [&](int64_t w) {
+    for (size_t i = size_t(w) * kStep; i < std::min(work.size(), size_t(w + 1) * kStep); ++i) {
+      const SlotGemm& S = *jobs[work[i].first].S;
+      const int lead = first[work[i].first];
+      HostTile& t = all[work[i].first][work[i].second];
+      const size_t n = t.g.size();
+      std::vector<int64_t> key(n);
+      size_t most = 0;
+      auto look = [&](size_t c) {
+        const int32_t k = t.at[c];
+        key[c] = k >= S.t0_h[size_t(t.g[c]) + 1]
+                     ? INT64_MAX
+                     : (int64_t(term_kind(S, k) == lead ? 0 : 1) << 32 | S.op_h[size_t(k)]);
+      };
+      for (size_t c = 0; c < n; ++c) {
+        t.at.push_back(S.t0_h[size_t(t.g[c])]);
+        most += size_t(S.t0_h[size_t(t.g[c]) + 1] - t.at[c]);
+        look(c);
+      }
+      t.head.reserve(4 * most);
+      t.vec.reserve(kTileCols * most);
+      for (;;) {
+        const int64_t best = *std::min_element(key.begin(), key.end());
+        if (best == INT64_MAX) break;
+        const size_t v0 = t.vec.size(), h0 = t.head.size();
+        t.vec.resize(v0 + kTileCols, -1);
+        t.head.resize(h0 + 4, 0);
+        for (size_t c = 0; c < n; ++c) {
+          if (key[c] != best) continue;
+          const int32_t* e = &S.terms_h[size_t(4) * size_t(t.at[c]++)];
+          t.head[h0] = e[0];
+          t.head[h0 + 1] = e[2];
+          for (int k = 0; k < nrhs; ++k) t.vec[v0 + c * size_t(nrhs) + size_t(k)] = e[1] * nrhs + k;
+          look(c);
         }
       }
-      last_rank = kind;
-      last_op = S.op_h[size_t(i)];
     }
-  }
-  if (first < 0) first = 0;
-  std::vector<int64_t> gs(static_cast<size_t>(S.ngroups));
-  for (int64_t g = 0; g < S.ngroups; ++g) gs[size_t(g)] = g;
-  std::stable_sort(gs.begin(), gs.end(), [&](int64_t a, int64_t b) {
-    if (S.gm_h[size_t(a)] != S.gm_h[size_t(b)]) return S.gm_h[size_t(a)] < S.gm_h[size_t(b)];
-    return S.near_h[size_t(a)] < S.near_h[size_t(b)];
   });
-  struct Tile {
-    std::vector<int64_t> g;
-    std::vector<std::array<int32_t, 4>> head;
-    std::vector<int32_t> vec;
+  // one buffer for the tables of all jobs, each at a multiple of 16 bytes
+  std::vector<int32_t> host;
+  struct At {
+    size_t t0, gm, head, vec, dst;
   };
-  std::vector<Tile> tiles;
-  for (size_t i = 0; i < gs.size();) {
-    Tile t;
-    while (i < gs.size() && int(t.g.size()) < per &&
-           (t.g.empty() || (S.gm_h[size_t(gs[i])] == S.gm_h[size_t(t.g[0])] &&
-                            (S.near_h[size_t(gs[i])] >> 32) == (S.near_h[size_t(t.g[0])] >> 32))))
-      t.g.push_back(gs[i++]);
-    tiles.push_back(std::move(t));
-  }
-  parallel_for(int64_t(tiles.size()), [&](int64_t ti) {
-    Tile& t = tiles[size_t(ti)];
-    std::vector<int32_t> at;
-    for (int64_t g : t.g) at.push_back(S.t0_h[size_t(g)]);
-    auto key = [&](int32_t i) {
-      const int kind = (S.terms_h[size_t(4) * size_t(i) + 2] >> 14) & 1;
-      return int64_t(kind == first ? 0 : 1) << 32 | S.op_h[size_t(i)];
-    };
-    for (;;) {
-      int64_t best = INT64_MAX;
+  std::vector<At> at(jobs.size());
+  auto put = [&](const std::vector<int32_t>& v) {
+    const size_t a = host.size();
+    host.insert(host.end(), v.begin(), v.end());
+    host.resize((host.size() + 3) / 4 * 4, 0);
+    return a;
+  };
+  for (size_t q = 0; q < jobs.size(); ++q) {
+    if (all[q].empty()) continue;
+    const SlotGemm& S = *jobs[q].S;
+    std::stable_sort(all[q].begin(), all[q].end(),
+                     [](const HostTile& a, const HostTile& b) { return a.head.size() > b.head.size(); });
+    std::vector<int32_t> t0(1, 0), gm, dst;
+    for (const HostTile& t : all[q]) {
+      t0.push_back(t0.back() + int32_t(t.head.size() / 4));
+      gm.push_back(S.gm_h[size_t(t.g[0])]);
+      const size_t d0 = dst.size();
+      dst.resize(d0 + kTileCols, -1);
       for (size_t c = 0; c < t.g.size(); ++c)
-        if (at[c] < S.t0_h[size_t(t.g[c]) + 1]) best = std::min(best, key(at[c]));
-      if (best == INT64_MAX) break;
-      std::array<int32_t, 4> h{0, 0, 0, 0};
-      const size_t v0 = t.vec.size();
-      t.vec.resize(v0 + kTileCols, -1);
-      for (size_t c = 0; c < t.g.size(); ++c) {
-        if (at[c] >= S.t0_h[size_t(t.g[c]) + 1] || key(at[c]) != best) continue;
-        const int32_t* e = &S.terms_h[size_t(4) * size_t(at[c]++)];
-        h = {e[0], e[2], 0, 0};
-        for (int k = 0; k < nrhs; ++k) t.vec[v0 + c * size_t(nrhs) + size_t(k)] = e[1] * nrhs + k;
-      }
-      t.head.push_back(h);
+        for (int k = 0; k < nrhs; ++k)
+          dst[d0 + c * size_t(nrhs) + size_t(k)] =
+              (jobs[q].gdst ? (*jobs[q].gdst)[size_t(t.g[c])] : int32_t(t.g[c])) * nrhs + k;
     }
-  });
-  std::stable_sort(tiles.begin(), tiles.end(), [](const Tile& a, const Tile& b) { return a.head.size() > b.head.size(); });
-  std::vector<int32_t> t0(1, 0), gm, head, vec, dst;
-  for (const Tile& t : tiles) {
-    for (const auto& h : t.head) head.insert(head.end(), h.begin(), h.end());
-    vec.insert(vec.end(), t.vec.begin(), t.vec.end());
-    t0.push_back(int32_t(head.size() / 4));
-    gm.push_back(S.gm_h[size_t(t.g[0])]);
-    const size_t d0 = dst.size();
-    dst.resize(d0 + kTileCols, -1);
-    for (size_t c = 0; c < t.g.size(); ++c)
-      for (int k = 0; k < nrhs; ++k)
-        dst[d0 + c * size_t(nrhs) + size_t(k)] = (gdst ? (*gdst)[size_t(t.g[c])] : int32_t(t.g[c])) * nrhs + k;
+    at[q].t0 = put(t0);
+    at[q].gm = put(gm);
+    at[q].dst = put(dst);
+    at[q].head = host.size();
+    for (const HostTile& t : all[q]) host.insert(host.end(), t.head.begin(), t.head.end());
+    at[q].vec = host.size();
+    for (const HostTile& t : all[q]) host.insert(host.end(), t.vec.begin(), t.vec.end());
   }
-  T.ntiles = int64_t(tiles.size());
-  T.t0.upload(t0);
-  T.gm.upload(gm);
-  T.head.upload(head);
-  T.vec.upload(vec);
-  T.dst.upload(dst);
-  return true;
+  buf.upload(host);
+  const int* d = buf.as<int>();
+  for (size_t q = 0; q < jobs.size(); ++q)
+    if (!all[q].empty())
+      *jobs[q].out = SlotTiles{int64_t(all[q].size()),  d + at[q].t0,  d + at[q].gm,
+                               reinterpret_cast<const int4*>(d + at[q].head), d + at[q].vec, d + at[q].dst};
 }
 
 // Device bytes held by a plan (every table and operator array; the apply
