@@ -155,10 +155,12 @@ struct SlotGemm {
   DevBuf gm;                 // int32[ngroups]: padded rows M_g of the group's operators
   DevBuf terms;              // int32[nterms][4]: (operator float4 offset, source vector,
                              //   packed K | split << 12 | kind << 14, 0)
-  // host copies: term ranges and table, operator index of each term, padded rows and
-  // neighbourhood order of each group (slot_tiles)
-  std::vector<int32_t> t0_h, terms_h, op_h, gm_h;
+  // for build_slot_tiles: host copies of the term ranges and table, operator index of
+  // each term, padded rows and neighbourhood key of each group, the groups ordered by
+  // the two, and the kind that the groups' terms start with (-1: no common order)
+  std::vector<int32_t> t0_h, terms_h, op_h, gm_h, by_near_h;
   std::vector<int64_t> near_h;
+  int lead = -1;
 };
 // Slot-form tables for few right-hand sides: a tile holds 16 columns, one per
 // (group, rhs) of 16 / nrhs neighbouring groups, and walks the union of their

@@ -272,6 +272,33 @@ struct OpStore {
   }
 };
 
+namespace {
+inline int term_kind(const SlotGemm& S, int32_t i) { return (S.terms_h[size_t(4) * size_t(i) + 2] >> 14) & 1; }
+
+// The common order of the groups' terms: the kind that they start with, then the
+// operator index.  Returns that kind, -1 if there is none.
+int lead_kind(const SlotGemm& S) {
+  int lead = -1;
+  for (int64_t g = 0; g < S.ngroups; ++g)
+    for (int32_t i = S.t0_h[size_t(g)] + 1; i < S.t0_h[size_t(g) + 1]; ++i) {
+      const int prev = term_kind(S, i - 1);
+      if (prev != term_kind(S, i)) {  // groups with both kinds decide it
+        if (lead >= 0 && lead != prev) return -1;
+        lead = prev;
+      } else if (S.op_h[size_t(i)] <= S.op_h[size_t(i) - 1]) {
+        return -1;
+      }
+    }
+  return std::max(lead, 0);
+}
+
+struct HostTile {
+  std::vector<int32_t> g;  // its groups
+  std::vector<int32_t> at;  // where each of them stands in its terms
+  std::vector<int32_t> head, vec;
+};
+}  // namespace
+
 void build_slot_gemm(SlotGemm& S, int M, int64_t ngroups, const std::vector<int32_t>& gM,
                      const std::vector<SlotTerm>& terms, const SlotKind kinds[2], int kx_max,
                      const std::vector<int64_t>& near) {
@@ -327,55 +354,28 @@ void build_slot_gemm(SlotGemm& S, int M, int64_t ngroups, const std::vector<int3
   S.op_h = std::move(op);
   S.gm_h = gM;
   S.near_h = near;
+  S.by_near_h.resize(size_t(S.ngroups));
+  for (int64_t g = 0; g < S.ngroups; ++g) S.by_near_h[size_t(g)] = int32_t(g);
+  std::stable_sort(S.by_near_h.begin(), S.by_near_h.end(), [&](int32_t a, int32_t b) {
+    if (S.gm_h[size_t(a)] != S.gm_h[size_t(b)]) return S.gm_h[size_t(a)] < S.gm_h[size_t(b)];
+    return S.near_h[size_t(a)] < S.near_h[size_t(b)];
+  });
+  S.lead = lead_kind(S);
 }
-
-namespace {
-struct HostTile {
-  std::vector<int64_t> g;    // its groups
-  std::vector<int32_t> at;   // where each of them stands in its terms
-  std::vector<int32_t> head, vec;
-};
-
-inline int term_kind(const SlotGemm& S, int32_t i) { return (S.terms_h[size_t(4) * size_t(i) + 2] >> 14) & 1; }
-
-// The common order of the groups' terms: the kind that they start with, then the
-// operator index.  Returns that kind, -1 if there is none.
-int common_order(const SlotGemm& S) {
-  int first = -1;
-  for (int64_t g = 0; g < S.ngroups; ++g)
-    for (int32_t i = S.t0_h[size_t(g)] + 1; i < S.t0_h[size_t(g) + 1]; ++i) {
-      const int prev = term_kind(S, i - 1);
-      if (prev != term_kind(S, i)) {  // groups with both kinds decide it
-        if (first >= 0 && first != prev) return -1;
-        first = prev;
-      } else if (S.op_h[size_t(i)] <= S.op_h[size_t(i) - 1]) {
-        return -1;
-      }
-    }
-  return std::max(first, 0);
-}
-}  // namespace
 
 void build_slot_tiles(const std::vector<TileJob>& jobs, int nrhs, DevBuf& buf) {
   std::vector<std::vector<HostTile>> all(jobs.size());
-  std::vector<int> first(jobs.size());
   std::vector<std::pair<size_t, size_t>> work;  // (job, tile)
   for (size_t q = 0; q < jobs.size(); ++q) {
     const SlotGemm& S = *jobs[q].S;
     jobs[q].out->ntiles = 0;
-    first[q] = common_order(S);
-    if (S.ngroups == 0 || first[q] < 0) continue;
+    if (S.ngroups == 0 || S.lead < 0) continue;
     // groups of a tile: more of them share more operators (about 1.8 columns of a
     // term in use with 4, 5 with 16), but leave fewer waves, one per row tile; as
     // many as leave 1.5 waves for each of the 1,024 SIMDs
     int per = kTileCols / nrhs;
     while (per > 1 && (S.ngroups + per - 1) / per * jobs[q].row_tiles < 1536) per /= 2;
-    std::vector<int64_t> gs(static_cast<size_t>(S.ngroups));
-    for (int64_t g = 0; g < S.ngroups; ++g) gs[size_t(g)] = g;
-    std::stable_sort(gs.begin(), gs.end(), [&](int64_t a, int64_t b) {
-      if (S.gm_h[size_t(a)] != S.gm_h[size_t(b)]) return S.gm_h[size_t(a)] < S.gm_h[size_t(b)];
-      return S.near_h[size_t(a)] < S.near_h[size_t(b)];
-    });
+    const std::vector<int32_t>& gs = S.by_near_h;
     for (size_t i = 0; i < gs.size();) {
       HostTile t;
       while (i < gs.size() && int(t.g.size()) < per &&
@@ -391,7 +391,6 @@ void build_slot_tiles(const std::vector<TileJob>& jobs, int nrhs, DevBuf& buf) {
   parallel_for(int64_t((work.size() + kStep - 1) / kStep), [&](int64_t w) {
     for (size_t i = size_t(w) * kStep; i < std::min(work.size(), size_t(w + 1) * kStep); ++i) {
       const SlotGemm& S = *jobs[work[i].first].S;
-      const int lead = first[work[i].first];
       HostTile& t = all[work[i].first][work[i].second];
       const size_t n = t.g.size();
       std::vector<int64_t> key(n);
@@ -400,7 +399,7 @@ void build_slot_tiles(const std::vector<TileJob>& jobs, int nrhs, DevBuf& buf) {
         const int32_t k = t.at[c];
         key[c] = k >= S.t0_h[size_t(t.g[c]) + 1]
                      ? INT64_MAX
-                     : (int64_t(term_kind(S, k) == lead ? 0 : 1) << 32 | S.op_h[size_t(k)]);
+                     : (int64_t(term_kind(S, k) == S.lead ? 0 : 1) << 32 | S.op_h[size_t(k)]);
       };
       for (size_t c = 0; c < n; ++c) {
         t.at.push_back(S.t0_h[size_t(t.g[c])]);
@@ -426,47 +425,54 @@ void build_slot_tiles(const std::vector<TileJob>& jobs, int nrhs, DevBuf& buf) {
       }
     }
   });
-  // one buffer for the tables of all jobs, each at a multiple of 16 bytes
-  std::vector<int32_t> host;
+  // one buffer for the tables of all jobs: the small ones of each, its heads, its
+  // vectors, each at a multiple of 16 bytes
   struct At {
-    size_t t0, gm, head, vec, dst;
+    size_t t0, gm, dst, head, vec;
   };
   std::vector<At> at(jobs.size());
-  auto put = [&](const std::vector<int32_t>& v) {
-    const size_t a = host.size();
-    host.insert(host.end(), v.begin(), v.end());
-    host.resize((host.size() + 3) / 4 * 4, 0);
-    return a;
-  };
+  size_t words = 0;
   for (size_t q = 0; q < jobs.size(); ++q) {
-    if (all[q].empty()) continue;
-    const SlotGemm& S = *jobs[q].S;
     std::stable_sort(all[q].begin(), all[q].end(),
                      [](const HostTile& a, const HostTile& b) { return a.head.size() > b.head.size(); });
-    std::vector<int32_t> t0(1, 0), gm, dst;
-    for (const HostTile& t : all[q]) {
-      t0.push_back(t0.back() + int32_t(t.head.size() / 4));
-      gm.push_back(S.gm_h[size_t(t.g[0])]);
-      const size_t d0 = dst.size();
-      dst.resize(d0 + kTileCols, -1);
+    const size_t n = all[q].size();
+    size_t nterms = 0;
+    for (const HostTile& t : all[q]) nterms += t.head.size() / 4;
+    at[q].t0 = words;
+    at[q].gm = at[q].t0 + (n + 4) / 4 * 4;
+    at[q].dst = at[q].gm + (n + 3) / 4 * 4;
+    at[q].head = at[q].dst + kTileCols * n;
+    at[q].vec = at[q].head + 4 * nterms;
+    words = at[q].vec + kTileCols * nterms;
+    if (nterms > size_t(INT32_MAX)) throw Error{DFMM_ENOMEM, "slot tile tables too large"};
+  }
+  const std::unique_ptr<int32_t[]> host(new int32_t[std::max<size_t>(words, 1)]);
+  for (size_t q = 0; q < jobs.size(); ++q) {
+    int32_t t0 = host[at[q].t0] = 0;
+    for (size_t i = 0; i < all[q].size(); ++i) host[at[q].t0 + i + 1] = t0 += int32_t(all[q][i].head.size() / 4);
+  }
+  parallel_for(int64_t((work.size() + kStep - 1) / kStep), [&](int64_t w) {
+    for (size_t i = size_t(w) * kStep; i < std::min(work.size(), size_t(w + 1) * kStep); ++i) {
+      const size_t q = work[i].first, ti = work[i].second;
+      const SlotGemm& S = *jobs[q].S;
+      const HostTile& t = all[q][ti];
+      host[at[q].gm + ti] = S.gm_h[size_t(t.g[0])];
+      int32_t* dst = &host[at[q].dst + kTileCols * ti];
+      std::fill(dst, dst + kTileCols, -1);
       for (size_t c = 0; c < t.g.size(); ++c)
         for (int k = 0; k < nrhs; ++k)
-          dst[d0 + c * size_t(nrhs) + size_t(k)] =
-              (jobs[q].gdst ? (*jobs[q].gdst)[size_t(t.g[c])] : int32_t(t.g[c])) * nrhs + k;
+          dst[c * size_t(nrhs) + size_t(k)] = (jobs[q].gdst ? (*jobs[q].gdst)[size_t(t.g[c])] : t.g[c]) * nrhs + k;
+      const size_t b = size_t(host[at[q].t0 + ti]);
+      std::copy(t.head.begin(), t.head.end(), &host[at[q].head + 4 * b]);
+      std::copy(t.vec.begin(), t.vec.end(), &host[at[q].vec + kTileCols * b]);
     }
-    at[q].t0 = put(t0);
-    at[q].gm = put(gm);
-    at[q].dst = put(dst);
-    at[q].head = host.size();
-    for (const HostTile& t : all[q]) host.insert(host.end(), t.head.begin(), t.head.end());
-    at[q].vec = host.size();
-    for (const HostTile& t : all[q]) host.insert(host.end(), t.vec.begin(), t.vec.end());
-  }
-  buf.upload(host);
+  });
+  buf.alloc(words * sizeof(int32_t));
+  if (words > 0) DFMM_HIP(hipMemcpy(buf.p, host.get(), words * sizeof(int32_t), hipMemcpyHostToDevice));
   const int* d = buf.as<int>();
   for (size_t q = 0; q < jobs.size(); ++q)
     if (!all[q].empty())
-      *jobs[q].out = SlotTiles{int64_t(all[q].size()),  d + at[q].t0,  d + at[q].gm,
+      *jobs[q].out = SlotTiles{int64_t(all[q].size()), d + at[q].t0, d + at[q].gm,
                                reinterpret_cast<const int4*>(d + at[q].head), d + at[q].vec, d + at[q].dst};
 }
 
