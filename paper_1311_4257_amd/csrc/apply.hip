@@ -1478,7 +1478,15 @@ struct SlotLaunch {
   int waves = 1;       // waves per workgroup
   int cpg = 1;         // column chunks per group
   int64_t nchunks = 0;
-  SlotTiles tiles;     // tables for few right-hand sides (else none)
+};
+
+// Tables of the slot launches for few right-hand sides, in the order of a LaunchSet.
+struct SlotTileSet {
+  std::vector<SlotTiles> up, down, lfd_up, lfd_down;
+  SlotTiles lf_down;
+  DevBuf buf;
+  explicit SlotTileSet(const dfmm_plan_s& P)
+      : up(P.hf.size()), down(P.hf.size()), lfd_up(P.lfd.size()), lfd_down(P.lfd.size()) {}
 };
 
 // The GEMM launches of one nrhs (chunk tables and tuned shapes).
@@ -1490,7 +1498,9 @@ struct LaunchSet {
   std::vector<SlotLaunch> up, down;   // per HF level
   SlotLaunch lf_down;
   std::vector<SlotLaunch> lfd_up, lfd_down;  // per LF level below width 1/2 (adaptive trees)
-  DevBuf tile_buf;                    // the slot launches' tables for few right-hand sides
+  // few right-hand sides: tables of the slot launches, made behind the first uncaptured
+  // apply and not changed after (read and set under ApplyState::mu)
+  std::unique_ptr<SlotTileSet> tiles;
 };
 
 // The M2L problems of a plan in apply order: HF levels from the top down, then
@@ -1758,25 +1768,24 @@ static void launch_slot_t(const SlotLaunch& L, const SlotArgs& a, int nrhs, floa
 }
 
 // kind 0: operators A0 on source vectors X0 (row stride KX0); kind 1 likewise
-static void launch_slot(const SlotLaunch& L, const float4* A0, const float2* X0, int KX0, const float4* A1,
-                        const float2* X1, int KX1, int nrhs, float2* Y, bool m2l, hipStream_t st,
+static void launch_slot(const SlotLaunch& L, const SlotTiles* T, const float4* A0, const float2* X0, int KX0,
+                        const float4* A1, const float2* X1, int KX1, int nrhs, float2* Y, bool m2l, hipStream_t st,
                         const int* gdst = nullptr) {
   if (L.nchunks == 0) return;
   const SlotGemm& S = *L.S;
   SlotArgs a{S.order.as<int>(), S.t0.as<int>(), S.gm.as<int>(), S.terms.as<int4>(), A0, A1 ? A1 : A0, X0,
              X1 ? X1 : X0, KX0, X1 ? KX1 : KX0, S.M, L.cpg, int(slot_col_units(S, L.nt)), L.waves, gdst};
-  if (L.tiles.ntiles > 0) {
-    const SlotTiles& T = L.tiles;
-    const SlotTileArgs t{T.t0, T.gm, T.head, T.vec, T.dst, A0, a.A1, X0, a.X1, KX0, a.KX1, S.M};
+  if (T && T->ntiles > 0) {
+    const SlotTileArgs t{T->t0, T->gm, T->head, T->vec, T->dst, A0, a.A1, X0, a.X1, KX0, a.KX1, S.M};
     // as few as three waves (row tiles) per workgroup until the launch has two
     // workgroups per CU; each slice stages the columns again
     const int nM = (S.M + 15) / 16;
     int slices = (nM + 7) / 8;
-    while ((nM + slices) / (slices + 1) >= 3 && T.ntiles * slices < 512) ++slices;
+    while ((nM + slices) / (slices + 1) >= 3 && T->ntiles * slices < 512) ++slices;
     const int waves = std::max((nM + slices - 1) / slices, 3);
     auto kern = waves >= 6 ? (m2l ? &k_m2l_tiles<3> : &k_m2m_tiles<3>) : (m2l ? &k_m2l_tiles<6> : &k_m2m_tiles<6>);
     ensure_lds_limit(reinterpret_cast<const void*>(kern));
-    hipLaunchKernelGGL(kern, dim3(unsigned(slices), unsigned(T.ntiles)), dim3(unsigned(64 * waves)),
+    hipLaunchKernelGGL(kern, dim3(unsigned(slices), unsigned(T->ntiles)), dim3(unsigned(64 * waves)),
                        slot_col_units(S, 1) * 16, st, t, Y);
     return;
   }
@@ -1800,27 +1809,33 @@ static void prepare_slot_set(const dfmm_plan_s& P, int nrhs, LaunchSet& LS) {
     prepare_slot(LS.lfd_up[k], P.lfd[k].up, nrhs, nt);
     prepare_slot(LS.lfd_down[k], P.lfd[k].down, nrhs, nt);
   }
-  // few right-hand sides (adaptive trees; a uniform one takes the pair form there):
-  // two neighbouring groups or more share a tile's 16 columns
-  if (2 * nrhs > kTileCols) return;
+}
+
+// Few right-hand sides (adaptive trees; a uniform one takes the pair form there): two
+// neighbouring groups or more share a tile's 16 columns.
+static void prepare_tiles(const dfmm_plan_s& P, int nrhs, LaunchSet& LS) {
+  std::unique_ptr<SlotTileSet> T(new SlotTileSet(P));
   std::vector<TileJob> jobs;
-  auto job = [&](SlotLaunch& L, const std::vector<int32_t>* gdst = nullptr) {
-    if (L.S->Kmax <= 128) jobs.push_back({L.S, (L.S->M + 15) / 16, gdst, &L.tiles});
+  auto job = [&](const SlotGemm& S, SlotTiles& t, const std::vector<int32_t>* gdst = nullptr) {
+    if (S.Kmax <= 128) jobs.push_back({&S, (S.M + 15) / 16, gdst, &t});
   };
   for (size_t e = 0; e < P.hf.size(); ++e) {
-    job(LS.up[e]);
-    job(LS.down[e]);
+    job(P.hf[e].up, T->up[e]);
+    job(P.hf[e].down, T->down[e]);
   }
-  job(LS.lf_down);
+  job(P.lf.down, T->lf_down);
   for (size_t k = 0; k < P.lfd.size(); ++k) {
-    job(LS.lfd_up[k], &P.lfd[k].up_dst_h);
-    job(LS.lfd_down[k]);
+    job(P.lfd[k].up, T->lfd_up[k], &P.lfd[k].up_dst_h);
+    job(P.lfd[k].down, T->lfd_down[k]);
   }
   try {
-    build_slot_tiles(jobs, nrhs, LS.tile_buf);
+    build_slot_tiles(jobs, nrhs, T->buf);
   } catch (const Error& e) {  // no memory for the tables: the general form needs none
     if (e.code != DFMM_ENOMEM) throw;
+    (void)hipGetLastError();
+    T.reset(new SlotTileSet(P));
   }
+  LS.tiles = std::move(T);
 }
 
 // ---- fused M2L launch ----------------------------------------------------------------
@@ -2227,6 +2242,7 @@ void run_apply(dfmm_plan_s& P, const ReqTable& R, int nrhs, hipStream_t st, void
           t.reset(new Tiles64(P, nrhs));
         } catch (const Error& e) {  // no memory for the tables: the general form needs none
           if (e.code != DFMM_ENOMEM) throw;
+    (void)hipGetLastError();
         }
       }
       T = t.get();
@@ -2255,8 +2271,12 @@ void run_apply(dfmm_plan_s& P, const ReqTable& R, int nrhs, hipStream_t st, void
   const Ws S = carve(L, own ? AS.buf.p : ws);
   LaunchSet& LS = launch_set(P, AS, S, nrhs, st);
   if (capturing) AS.captured = true;
-  // the launch set is immutable from here; applies on caller workspaces run
-  // concurrently (the stage timer and the second stream belong to dfmm_apply)
+  // few right-hand sides: the first apply takes the general form (the same sums), and
+  // the host makes the tables while the device works on it
+  const SlotTileSet* T = LS.tiles.get();
+  const bool make_tiles = !T && LS.slot && 2 * nrhs <= kTileCols && !capturing && !existing_only;
+  // the launch set is immutable from here but for its tables; applies on caller
+  // workspaces run concurrently (the stage timer and the second stream belong to dfmm_apply)
   if (!own) lock.unlock();
   const int64_t N = P.N;
   const int64_t nleaf = P.lf.nleaf;
@@ -2344,33 +2364,38 @@ void run_apply(dfmm_plan_s& P, const ReqTable& R, int nrhs, hipStream_t st, void
     // trees first run LF-M2M from the deepest LF level up to width 1/2.
     for (int k = int(P.lfd.size()) - 1; k >= 0; --k) {
       const LFDeep& Q = P.lfd[size_t(k)];
-      launch_slot(LS.lfd_up[size_t(k)], Q.m2m.A.as<float4>(), S.flf.as<float2>(), Rl, nullptr, nullptr, 0, nrhs,
+      launch_slot(LS.lfd_up[size_t(k)], T ? &T->lfd_up[size_t(k)] : nullptr,
+                  Q.m2m.A.as<float4>(), S.flf.as<float2>(), Rl, nullptr, nullptr, 0, nrhs,
                   S.flf.as<float2>(), false, st, Q.up_dst.as<int>());
       mark(ST_M2M);
     }
     for (int e = 0; e <= e_top; ++e) {
       const float2* Fc = e == 0 ? S.flf.as<float2>() : S.F[e - 1].as<float2>();
       const int KC = e == 0 ? Rl : P.hf[e - 1].R;
-      launch_slot(LS.up[e], P.hf[e].m2m.A.as<float4>(), Fc, KC, nullptr, nullptr, 0, nrhs,
+      launch_slot(LS.up[e], T ? &T->up[e] : nullptr,
+                  P.hf[e].m2m.A.as<float4>(), Fc, KC, nullptr, nullptr, 0, nrhs,
                   S.F[e].as<float2>(), false, st);
       mark(ST_M2M);
     }
     for (int e = e_top; e >= 0; --e) {
       const HFLevel& H = P.hf[e];
       const bool par = e < e_top;
-      launch_slot(LS.down[e], H.m2l.A.as<float4>(), S.F[e].as<float2>(), H.R,
+      launch_slot(LS.down[e], T ? &T->down[e] : nullptr,
+                  H.m2l.A.as<float4>(), S.F[e].as<float2>(), H.R,
                   par ? P.hf[e + 1].l2l.A.as<float4>() : nullptr, par ? S.U[e + 1].as<float2>() : nullptr,
                   par ? P.hf[e + 1].R : 0, nrhs, S.U[e].as<float2>(), true, st);
       mark(ST_M2L);
     }
-    launch_slot(LS.lf_down, P.lf.m2l.A.as<float4>(), S.flf.as<float2>(), Rl,
+    launch_slot(LS.lf_down, T ? &T->lf_down : nullptr,
+                P.lf.m2l.A.as<float4>(), S.flf.as<float2>(), Rl,
                 e_top >= 0 ? P.hf[0].l2l.A.as<float4>() : nullptr, e_top >= 0 ? S.U[0].as<float2>() : nullptr,
                 e_top >= 0 ? P.hf[0].R : 0, nrhs, S.ulf.as<float2>(), true, st);
     mark(ST_LF_M2L);
     // adaptive trees: LF-M2L + LF-L2L of each deeper level into its boxes' LF vectors
     for (size_t k = 0; k < P.lfd.size(); ++k) {
       const LFDeep& Q = P.lfd[k];
-      launch_slot(LS.lfd_down[k], Q.m2l.A.as<float4>(), S.flf.as<float2>(), Rl, Q.l2l.A.as<float4>(),
+      launch_slot(LS.lfd_down[k], T ? &T->lfd_down[k] : nullptr,
+                  Q.m2l.A.as<float4>(), S.flf.as<float2>(), Rl, Q.l2l.A.as<float4>(),
                   S.ulf.as<float2>(), Rl, nrhs, S.ulf.as<float2>() + Q.base * nrhs * Rl, true, st);
       mark(ST_LF_M2L);
     }
@@ -2497,6 +2522,10 @@ void run_apply(dfmm_plan_s& P, const ReqTable& R, int nrhs, hipStream_t st, void
   }
   mark(ST_LEAF);
   DFMM_HIP(hipGetLastError());
+  if (make_tiles) {
+    if (!own) lock.lock();
+    if (!LS.tiles) prepare_tiles(P, nrhs, LS);
+  }
 }
 
 // ---- applies without allocation -------------------------------------------------------
