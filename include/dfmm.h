@@ -127,7 +127,9 @@ typedef struct {
 } dfmm_options;
 
 /* Arithmetic of the translation GEMMs (M2M, M2L, L2L) of a plan.  FP32: float32
- * MFMA.  FP16X3 / BF16X3: every operator entry a and vector entry x is split into
+ * products, each factor the exact sum of three bfloat16 parts and six products of
+ * parts on the 16-bit MFMA (the dropped ones are below 2^-24 of the product), float32
+ * accumulation.  FP16X3 / BF16X3: every operator entry a and vector entry x is split into
  * a hi and a lo part of the 16-bit type (a = a_hi + a_lo to 22 resp. 16 bits)
  * and a x is formed as a_hi x_hi + a_hi x_lo + a_lo x_hi on the 16-bit MFMA with
  * float32 accumulation.  FP16X3 scales each operator (at plan time) and each
@@ -169,8 +171,8 @@ void dfmm_options_default(dfmm_options* opt);
  * geometry (Section 2.2), and are cached in the cache directory.  Plans with
  * eps < 1e-5 (or an operator set with tau < 3e-6) are "precise": the
  * near-field distances, 1/r and products are float64, the directional
- * operators are stored as float32 hi + lo parts, and every translation GEMM adds
- * its float32 sums into float64 partial sums every 32 products. */
+ * operators are stored to 32 bits (four bfloat16 parts), and every translation GEMM
+ * adds its float32 sums into float64 partial sums every 32 complex products. */
 int dfmm_plan(const double* points, int64_t N, double K, double eps, dfmm_plan_t* out);
 int dfmm_plan_ex(const double* points, int64_t N, double K, const dfmm_options* opt,
                  dfmm_plan_t* out);

@@ -112,11 +112,10 @@ struct DevBuf {
 // pack_operator().
 struct GGemm {
   int M = 0, K = 0, T = 1;   // vector strides (rows of Y and of X vectors); per-group sizes <= these
-  int split = 1;             // 2: each operator is [T_hi | T_lo] (K doubled) and every source
-                             // vector is read twice, so the float32 rounding of T cancels
-  bool acc64 = false;        // float64 partial sums every two k-steps (precise plans)
-  int prec = 0;              // DFMM_PREC_*: FP16X3 / BF16X3 hold A as 16-bit hi + lo pairs, K padded
-                             // to 16 (kpad), one power-of-two scale exponent per operator (aexp_h)
+  int split = 1;             // 2: a fourth plane holds what three bfloat16 planes of T leave
+  bool acc64 = false;        // float64 partial sums after every step (precise plans)
+  int prec = 0;              // DFMM_PREC_*: FP16X3 / BF16X3 hold A as 16-bit hi + lo pairs, with
+                             // one power-of-two scale exponent per operator (aexp_h)
   int64_t ngroups = 0, nvec = 0, nops = 0;
   DevBuf A;                  // operators in fragment order, op i at float4 offset aoff_h[i]
   DevBuf vsrc;               // int32[nvec][T]
@@ -126,7 +125,7 @@ struct GGemm {
   std::vector<int32_t> ops_h;   // per group: its operator
   std::vector<int32_t> v0_h;    // vector range of each group
   std::vector<int64_t> aoff_h;  // per operator
-  std::vector<int32_t> kpk_h;   // packed K of each operator index (split doubling included)
+  std::vector<int32_t> kpk_h;   // packed K of each operator index
   std::vector<double> opflops;  // 8 r_out r_in of each operator index (unpadded ranks)
 };
 

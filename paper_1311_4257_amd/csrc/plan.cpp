@@ -908,7 +908,7 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
   }
 
   // ---- HF levels ----------------------------------------------------------------
-  // precise plans split the directional operators into float32 hi + lo parts
+  // precise plans hold the directional operators in four bfloat16 planes instead of three
   const int hf_split = P.precise ? 2 : 1;
   P.hf.clear();
   P.hf.resize(e_top + 1);
