@@ -20,7 +20,7 @@ peak is 157.3), or against 8 TB/s when the algorithmic bytes make HBM the lower
 ceiling.
 The algorithmic bytes of the M2L are the operators once per offset group,
 every source slot read once and every target slot read and written once;
-where the slot form runs (16 rhs and more) its launches also carry the L2L
+where the slot form runs (30-32 rhs, 59-64, ...) its launches also carry the L2L
 terms, whose operators (once each) and parent slots (read once) are added.
 The CPU baseline times the float64 oracle pass on a bounded sample of the
 same geometry (the first points of the same point set: same K, same tree
