@@ -661,9 +661,12 @@ struct SlotTileArgs {
   const float2* X1;
   int KX0, KX1;
   int M;
+  int slices;  // workgroups of a tile
 };
 // UB: columns that a wave stages (ceil(16 / waves) at least); K <= 128.  A term's
 // columns and first operator rows are loaded while the term before multiplies.
+// Workgroup id = tile x slices + slice, on grid x: y ends at 65,535 workgroups, which
+// the tiles of 131,072 slots reach at 8 right-hand sides.
 template <int UB>
 __device__ __forceinline__ void slot_tiles(const SlotTileArgs& a, float2* __restrict__ Y) {
   constexpr int OP = OP_F32, AW = OpForm<OP>::AW, PB = OpForm<OP>::PB;
@@ -672,10 +675,10 @@ __device__ __forceinline__ void slot_tiles(const SlotTileArgs& a, float2* __rest
   const int lane = int(threadIdx.x) & 63;
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const int nw = int(blockDim.x) >> 6;
-  const int g = int(blockIdx.y);
+  const int g = int(blockIdx.x) / a.slices, slice = int(blockIdx.x) - g * a.slices;
   const int tb = a.t0[g], te = a.t0[g + 1];
   const int Mg = a.gm[g];
-  const int m = int(blockIdx.x) * nw + wave;
+  const int m = slice * nw + wave;
   const bool act = 16 * m < Mg;  // wave-uniform: this wave's tile has operator rows
   const int rows = min(16, Mg - 16 * m);
   struct Tm {
@@ -1776,16 +1779,16 @@ static void launch_slot(const SlotLaunch& L, const SlotTiles* T, const float4* A
   SlotArgs a{S.order.as<int>(), S.t0.as<int>(), S.gm.as<int>(), S.terms.as<int4>(), A0, A1 ? A1 : A0, X0,
              X1 ? X1 : X0, KX0, X1 ? KX1 : KX0, S.M, L.cpg, int(slot_col_units(S, L.nt)), L.waves, gdst};
   if (T && T->ntiles > 0) {
-    const SlotTileArgs t{T->t0, T->gm, T->head, T->vec, T->dst, A0, a.A1, X0, a.X1, KX0, a.KX1, S.M};
     // as few as three waves (row tiles) per workgroup until the launch has two
     // workgroups per CU; each slice stages the columns again
     const int nM = (S.M + 15) / 16;
     int slices = (nM + 7) / 8;
     while ((nM + slices) / (slices + 1) >= 3 && T->ntiles * slices < 512) ++slices;
     const int waves = std::max((nM + slices - 1) / slices, 3);
+    const SlotTileArgs t{T->t0, T->gm, T->head, T->vec, T->dst, A0, a.A1, X0, a.X1, KX0, a.KX1, S.M, slices};
     auto kern = waves >= 6 ? (m2l ? &k_m2l_tiles<3> : &k_m2m_tiles<3>) : (m2l ? &k_m2l_tiles<6> : &k_m2m_tiles<6>);
     ensure_lds_limit(reinterpret_cast<const void*>(kern));
-    hipLaunchKernelGGL(kern, dim3(unsigned(slices), unsigned(T->ntiles)), dim3(unsigned(64 * waves)),
+    hipLaunchKernelGGL(kern, dim3(unsigned(T->ntiles * slices)), dim3(unsigned(64 * waves)),
                        slot_col_units(S, 1) * 16, st, t, Y);
     return;
   }

@@ -269,7 +269,7 @@ __global__ void __launch_bounds__(256) k_slot64(const Slot64Args a, int nrhs, do
 // (0.8 MB at rank 232) for every term of every slot; here about 5 of 16 columns
 // of a term are in use.  A column's products and their order are those of the
 // form above, so the two give the same bits.  A wave takes MT row tiles of the
-// slice blockIdx.x, with the operator rows of T64_RING steps in flight (a step
+// slice, with the operator rows of T64_RING steps in flight (a step
 // is 256 matrix-core cycles; 12 steps measured the same).  Eight waves share the
 // 60 KB of staged columns (rank 232): two workgroups of 8 fit a CU, two of 4
 // left half of its wave slots empty and ran a second round.  A term's columns, and the
@@ -287,6 +287,7 @@ struct Tile64Args {
   int KX0, KX1;
   int M;
   int S;  // LDS column stride in double4
+  int slices;  // workgroups of a tile
 };
 constexpr int T64_RING = 4;
 constexpr int T64_NW = 8;   // waves per workgroup
@@ -302,10 +303,11 @@ __global__ void __launch_bounds__(64 * T64_NW, 4) k_tile64(const Tile64Args a, d
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 15, kr = lane >> 4;
   const bool odd = (j & 1) != 0;
-  const int g = int(blockIdx.y);
+  // workgroup id = tile x slices + slice, on grid x (y ends at 65,535)
+  const int g = int(blockIdx.x) / a.slices, slice = int(blockIdx.x) - g * a.slices;
   const int tb = a.t0[g], te = a.t0[g + 1];
   const int nM = a.gm[g] / 8;
-  const int m0 = int(blockIdx.x) * T64_NW + wave, mstep = T64_NW * int(gridDim.x);
+  const int m0 = slice * T64_NW + wave, mstep = T64_NW * a.slices;
   v4d acc[MT];
 #pragma unroll
   for (int t = 0; t < MT; ++t) acc[t] = v4d{0.0, 0.0, 0.0, 0.0};
@@ -469,7 +471,6 @@ void launch_slot64(const SlotGemm& S, const SlotTiles* T, const double4* A0, con
   if (sizeof(double4) * 16 * size_t(a.S) > size_t(kLds64))
     throw Error{DFMM_EUNSUPPORTED, "skeleton rank too large for the float64 slot GEMM"};
   if (T && T->ntiles > 0 && S.Kmax <= T64_MAXK) {
-    Tile64Args t{T->t0, T->gm, T->head, T->vec, T->dst, A0, a.A1, X0, a.X1, KX0, a.KX1, S.M, a.S};
     // one row tile per wave until the launch has two workgroups per CU, then two:
     // each slice stages the columns again
     const int nM = S.M / 8;
@@ -477,10 +478,11 @@ void launch_slot64(const SlotGemm& S, const SlotTiles* T, const double4* A0, con
     const int per = (two ? 2 : 1) * T64_NW;
     // the slices first: workgroups go to the 8 XCDs in turn, so the tiles on one of
     // them read the same rows of every operator
-    const dim3 grid(unsigned((nM + per - 1) / per), unsigned(T->ntiles));
+    const int slices = (nM + per - 1) / per;
+    const Tile64Args t{T->t0, T->gm, T->head, T->vec, T->dst, A0, a.A1, X0, a.X1, KX0, a.KX1, S.M, a.S, slices};
     auto kern = two ? &k_tile64<2> : &k_tile64<1>;
     lds_limit64(reinterpret_cast<const void*>(kern));
-    hipLaunchKernelGGL(kern, grid, dim3(64 * T64_NW), sizeof(double4) * 16 * size_t(a.S), st, t, Y);
+    hipLaunchKernelGGL(kern, dim3(unsigned(T->ntiles * slices)), dim3(64 * T64_NW), sizeof(double4) * 16 * size_t(a.S), st, t, Y);
     return;
   }
   if (mt <= 2) launch_slot64_t<2>(S, a, nrhs, Y, st);
