@@ -24,6 +24,7 @@
 #include <utility>
 
 #include "internal.hpp"
+#include "slot_merge.hpp"
 #include "split_mfma.hpp"
 
 namespace dfmm {
@@ -522,7 +523,7 @@ struct SlotArgs {
   const int* order;   // launch order of the groups
   const int* t0;      // term range of each group
   const int* gm;      // padded rows of each group's operators
-  const int4* terms;  // (operator float4 offset, source vector, K | kind << 14, 0)
+  const int4* terms;  // (operator float4 offset, K | kind << 14, source vector, key)
   const float4* A0;
   const float4* A1;
   const float2* X0;
@@ -563,12 +564,12 @@ __device__ __forceinline__ void slot_gemm(const SlotArgs& a, int nrhs, float2* _
     e.x = __builtin_amdgcn_readfirstlane(e.x);
     e.y = __builtin_amdgcn_readfirstlane(e.y);
     e.z = __builtin_amdgcn_readfirstlane(e.z);
-    const int kind = (e.z >> 14) & 1;
+    const int kind = (e.y >> 14) & 1;
     Tm r;
     r.KX = kind ? a.KX1 : a.KX0;
     r.A = (kind ? a.A1 : a.A0) + e.x;
-    r.X = (kind ? a.X1 : a.X0) + (int64_t(e.y) * nrhs + c0) * r.KX;
-    r.Kg = e.z & 0xFFF;
+    r.X = (kind ? a.X1 : a.X0) + (int64_t(e.z) * nrhs + c0) * r.KX;
+    r.Kg = e.y & 0xFFF;
     return r;
   };
   double dre[NT][4], dim_[NT][4];
@@ -642,28 +643,28 @@ __device__ __forceinline__ void slot_gemm(const SlotArgs& a, int nrhs, float2* _
   }
 }
 
-// The slot form for few right-hand sides (SlotTiles): the 16 columns of a
-// workgroup are (group, rhs) of neighbouring groups, each column's vector of a
-// term comes from the term's table, and columns without the term are zeros.  With
-// one group per workgroup a single right-hand side multiplies 15 columns of
-// padding and reads and splits an operator for every term of every slot; here
-// about 5 of 16 columns of a term are in use.  A column's products and sums are
-// those of the form above, so the two give the same bits.
+// The slot form for few right-hand sides (TileTerms): the 16 columns of a workgroup
+// are (group, rhs) of neighbouring groups, and columns without a term are zeros
+// there, which leave their sums as they are.  With one group per workgroup a single
+// right-hand side multiplies 15 columns of padding and reads and splits an operator
+// for every term of every slot; here 1.8 to 5 of 16 columns of a term are in use
+// (tiles of 4 to 16 groups).  A column's products and sums are those of the form
+// above, so the two give the same bits.
 struct SlotTileArgs {
-  const int* t0;
-  const int* gm;
-  const int4* head;  // (operator float4 offset, K | kind << 14, 0, 0)
-  const int* vec;
-  const int* dst;
+  const int4* rec;    // SlotGemm: the cut's records, terms
+  const int4* terms;  // (operator float4 offset, K | kind << 14, source vector, key)
   const float4* A0;
   const float4* A1;
   const float2* X0;
   const float2* X1;
   int KX0, KX1;
   int M;
+  int cu;  // LDS units of the columns (the term lists follow)
+  int nrhs, per, lead;
   int slices;  // workgroups of a tile
 };
-// UB: columns that a wave stages (ceil(16 / waves) at least); K <= 128.  A term's
+// UB: columns that a wave stages (ceil(16 / waves) at least); K <= kTileMaxK, a lane
+// stages one float4 of a column.  A term's
 // columns and first operator rows are loaded while the term before multiplies.
 // Workgroup id = tile x slices + slice, on grid x: y ends at 65,535 workgroups, which
 // the tiles of 131,072 slots reach at 8 right-hand sides.
@@ -676,67 +677,62 @@ __device__ __forceinline__ void slot_tiles(const SlotTileArgs& a, float2* __rest
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const int nw = int(blockDim.x) >> 6;
   const int g = int(blockIdx.x) / a.slices, slice = int(blockIdx.x) - g * a.slices;
-  const int tb = a.t0[g], te = a.t0[g + 1];
-  const int Mg = a.gm[g];
+  TileTerms list(a.rec + int64_t(g) * a.per, a.per, a.terms, a.nrhs, a.lead, reinterpret_cast<int2*>(xs4 + a.cu));
+  const int Mg = list.Mg;
   const int m = slice * nw + wave;
   const bool act = 16 * m < Mg;  // wave-uniform: this wave's tile has operator rows
   const int rows = min(16, Mg - 16 * m);
-  struct Tm {
-    const float4* A;
-    const float2* X;
-    int KX, Kg, src;  // src: the source vector of column lane mod 16
+  auto tile = [&](const TileTerm& q) {
+    return OpTile<OP>(OpRows(q.K, lane), (q.kind ? a.A1 : a.A0) + q.aoff + m * (2 * q.K * AW), rows);
   };
-  auto decode = [&](int i) {
-    const int4 h = a.head[i];
-    const int hx = __builtin_amdgcn_readfirstlane(h.x), hy = __builtin_amdgcn_readfirstlane(h.y);
-    const int kind = (hy >> 14) & 1;
-    return Tm{(kind ? a.A1 : a.A0) + hx, kind ? a.X1 : a.X0, kind ? a.KX1 : a.KX0, hy & 0xFFF,
-              a.vec[int64_t(i) * kTileCols + (lane & 15)]};
-  };
-  auto tile = [&](const Tm& q) { return OpTile<OP>(OpRows(q.Kg, lane), q.A + m * (2 * q.Kg * AW), rows); };
   double dre[4], dim_[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) dre[q] = dim_[q] = 0.0;
-  if (tb < te) {
-    Tm T = decode(tb), Tn = decode(min(tb + 1, te - 1));
+  TileTerm T = list.next();
+  if (T.any) {
+    TileTerm Tn = list.next();
     float4 raw[AW], xv[UB];
-    auto x_load = [&](const Tm& q) {
+    auto x_load = [&](const TileTerm& q) {
+      const float2* X = q.kind ? a.X1 : a.X0;
+      const int KX = q.kind ? a.KX1 : a.KX0;
 #pragma unroll
       for (int u = 0; u < UB; ++u) {
         const int src = __builtin_amdgcn_readlane(q.src, min(wave + u * nw, kTileCols - 1));
         xv[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (src >= 0 && lane < q.Kg / 2) xv[u] = reinterpret_cast<const float4*>(q.X + int64_t(src) * q.KX)[lane];
+        if (src >= 0 && lane < q.K / 2) xv[u] = reinterpret_cast<const float4*>(X + int64_t(src) * KX)[lane];
       }
     };
     if (act) load_first<OP>(tile(T), raw);
     x_load(T);
-    for (int t = tb; t < te; ++t) {
-      const int pad_col = 4 * col_chunks(T.Kg), cs = col_units(T.Kg, PB);
+    for (;;) {
+      const int pad_col = 4 * col_chunks(T.K), cs = col_units(T.K, PB);
       __syncthreads();  // the previous term's columns are consumed
 #pragma unroll
       for (int u = 0; u < UB; ++u) {
         const int col = wave + u * nw;
         if (col < kTileCols && lane < pad_col) stage_pair<OP>(reinterpret_cast<unsigned*>(xs + col * cs), lane, xv[u]);
       }
+      const TileTerm Tnn = list.next();  // (while the columns go to LDS)
       __syncthreads();
-      const Tm Tnn = decode(min(t + 2, te - 1));
       x_load(Tn);
       if (act) {
-        const OpRows o(T.Kg, lane);
-        tile_product<OP, 1>(o, tile(T), tile(Tn), xs + o.j * cs, cs, raw, [&](int, const StepSums& s, auto merged) {
+        const OpRows o(T.K, lane);
+        tile_product<OP, 1>(o, tile(T), tile(Tn.any ? Tn : T), xs + o.j * cs, cs, raw,
+                            [&](int, const StepSums& s, auto merged) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            if constexpr (decltype(merged)::value) dre[q] += double(s.p[q]);
-            else dre[q] += double(s.p[q] - s.q[q]);
-            dim_[q] += double(s.i[q]);
-          }
-        });
+                              for (int q = 0; q < 4; ++q) {
+                                if constexpr (decltype(merged)::value) dre[q] += double(s.p[q]);
+                                else dre[q] += double(s.p[q] - s.q[q]);
+                                dim_[q] += double(s.i[q]);
+                              }
+                            });
       }
+      if (!Tn.any) break;
       T = Tn;
       Tn = Tnn;
     }
   }
-  const int out = a.dst[int64_t(g) * kTileCols + (lane & 15)];
+  const int out = list.out;
   const int row = 16 * m + 4 * (lane >> 4);
   if (row < a.M && out >= 0) {
     float4 w0 = make_float4(0.f, 0.f, 0.f, 0.f), w1 = w0;
@@ -1483,15 +1479,6 @@ struct SlotLaunch {
   int64_t nchunks = 0;
 };
 
-// Tables of the slot launches for few right-hand sides, in the order of a LaunchSet.
-struct SlotTileSet {
-  std::vector<SlotTiles> up, down, lfd_up, lfd_down;
-  SlotTiles lf_down;
-  DevBuf buf;
-  explicit SlotTileSet(const dfmm_plan_s& P)
-      : up(P.hf.size()), down(P.hf.size()), lfd_up(P.lfd.size()), lfd_down(P.lfd.size()) {}
-};
-
 // The GEMM launches of one nrhs (chunk tables and tuned shapes).
 struct LaunchSet {
   std::vector<Launch> m2m, l2l, m2l;  // per HF level (pair form)
@@ -1501,9 +1488,6 @@ struct LaunchSet {
   std::vector<SlotLaunch> up, down;   // per HF level
   SlotLaunch lf_down;
   std::vector<SlotLaunch> lfd_up, lfd_down;  // per LF level below width 1/2 (adaptive trees)
-  // few right-hand sides: tables of the slot launches, made behind the first uncaptured
-  // apply and not changed after (read and set under ApplyState::mu)
-  std::unique_ptr<SlotTileSet> tiles;
 };
 
 // The M2L problems of a plan in apply order: HF levels from the top down, then
@@ -1567,7 +1551,6 @@ struct ApplyState {
   std::vector<DevBuf> retired;  // workspaces replaced after a graph capture (captured graphs hold them)
   bool captured = false;      // an apply of this plan has been captured into a graph
   std::map<int, std::unique_ptr<LaunchSet>> sets;
-  std::map<int, std::unique_ptr<Tiles64>> sets64;  // float64 plans, few right-hand sides
   // second stream for the near field (default priority) and its fork/join events
   hipStream_t side = nullptr;
   hipEvent_t fork = nullptr, join = nullptr;
@@ -1771,25 +1754,28 @@ static void launch_slot_t(const SlotLaunch& L, const SlotArgs& a, int nrhs, floa
 }
 
 // kind 0: operators A0 on source vectors X0 (row stride KX0); kind 1 likewise
-static void launch_slot(const SlotLaunch& L, const SlotTiles* T, const float4* A0, const float2* X0, int KX0,
+static void launch_slot(const SlotLaunch& L, const float4* A0, const float2* X0, int KX0,
                         const float4* A1, const float2* X1, int KX1, int nrhs, float2* Y, bool m2l, hipStream_t st,
                         const int* gdst = nullptr) {
   if (L.nchunks == 0) return;
   const SlotGemm& S = *L.S;
   SlotArgs a{S.order.as<int>(), S.t0.as<int>(), S.gm.as<int>(), S.terms.as<int4>(), A0, A1 ? A1 : A0, X0,
              X1 ? X1 : X0, KX0, X1 ? KX1 : KX0, S.M, L.cpg, int(slot_col_units(S, L.nt)), L.waves, gdst};
-  if (T && T->ntiles > 0) {
+  const int64_t ntiles = nrhs <= kTileRhs ? S.cut[nrhs].ntiles : 0;
+  if (ntiles > 0) {
     // as few as three waves (row tiles) per workgroup until the launch has two
     // workgroups per CU; each slice stages the columns again
     const int nM = (S.M + 15) / 16;
     int slices = (nM + 7) / 8;
-    while ((nM + slices) / (slices + 1) >= 3 && T->ntiles * slices < 512) ++slices;
+    while ((nM + slices) / (slices + 1) >= 3 && ntiles * slices < 512) ++slices;
     const int waves = std::max((nM + slices - 1) / slices, 3);
-    const SlotTileArgs t{T->t0, T->gm, T->head, T->vec, T->dst, A0, a.A1, X0, a.X1, KX0, a.KX1, S.M, slices};
+    const size_t cu = slot_col_units(S, 1);
+    const SlotTileArgs t{S.rec.as<int4>() + S.cut[nrhs].at, a.terms, A0, a.A1, X0, a.X1, KX0, a.KX1, S.M, int(cu), nrhs,
+                         S.cut[nrhs].per, S.lead, slices};
     auto kern = waves >= 6 ? (m2l ? &k_m2l_tiles<3> : &k_m2m_tiles<3>) : (m2l ? &k_m2l_tiles<6> : &k_m2m_tiles<6>);
     ensure_lds_limit(reinterpret_cast<const void*>(kern));
-    hipLaunchKernelGGL(kern, dim3(unsigned(T->ntiles * slices)), dim3(unsigned(64 * waves)),
-                       slot_col_units(S, 1) * 16, st, t, Y);
+    hipLaunchKernelGGL(kern, dim3(unsigned(ntiles * slices)), dim3(unsigned(64 * waves)),
+                       cu * 16 + size_t(S.cut[nrhs].entries) * sizeof(int2), st, t, Y);
     return;
   }
   if (L.nt == 2) launch_slot_t<2>(L, a, nrhs, Y, m2l, st);
@@ -1812,33 +1798,6 @@ static void prepare_slot_set(const dfmm_plan_s& P, int nrhs, LaunchSet& LS) {
     prepare_slot(LS.lfd_up[k], P.lfd[k].up, nrhs, nt);
     prepare_slot(LS.lfd_down[k], P.lfd[k].down, nrhs, nt);
   }
-}
-
-// Few right-hand sides (adaptive trees; a uniform one takes the pair form there): two
-// neighbouring groups or more share a tile's 16 columns.
-static void prepare_tiles(const dfmm_plan_s& P, int nrhs, LaunchSet& LS) {
-  std::unique_ptr<SlotTileSet> T(new SlotTileSet(P));
-  std::vector<TileJob> jobs;
-  auto job = [&](const SlotGemm& S, SlotTiles& t, const std::vector<int32_t>* gdst = nullptr) {
-    if (S.Kmax <= 128) jobs.push_back({&S, (S.M + 15) / 16, gdst, &t});
-  };
-  for (size_t e = 0; e < P.hf.size(); ++e) {
-    job(P.hf[e].up, T->up[e]);
-    job(P.hf[e].down, T->down[e]);
-  }
-  job(P.lf.down, T->lf_down);
-  for (size_t k = 0; k < P.lfd.size(); ++k) {
-    job(P.lfd[k].up, T->lfd_up[k], &P.lfd[k].up_dst_h);
-    job(P.lfd[k].down, T->lfd_down[k]);
-  }
-  try {
-    build_slot_tiles(jobs, nrhs, T->buf);
-  } catch (const Error& e) {  // no memory for the tables: the general form needs none
-    if (e.code != DFMM_ENOMEM) throw;
-    (void)hipGetLastError();
-    T.reset(new SlotTileSet(P));
-  }
-  LS.tiles = std::move(T);
 }
 
 // ---- fused M2L launch ----------------------------------------------------------------
@@ -2235,21 +2194,6 @@ void run_apply(dfmm_plan_s& P, const ReqTable& R, int nrhs, hipStream_t st, void
     if (!own && ws_bytes < need)
       throw Error{DFMM_EINVAL, "workspace of " + std::to_string(ws_bytes) + " bytes; this apply needs " +
                                    std::to_string(need)};
-    // few right-hand sides: tables that the first uncaptured apply of this nrhs
-    // makes (a captured one without them takes the general form)
-    const Tiles64* T = nullptr;
-    if (nrhs <= kTiles64Rhs) {
-      std::unique_ptr<Tiles64>& t = AS.sets64[nrhs];
-      if (!t && !capturing) {
-        try {
-          t.reset(new Tiles64(P, nrhs));
-        } catch (const Error& e) {  // no memory for the tables: the general form needs none
-          if (e.code != DFMM_ENOMEM) throw;
-    (void)hipGetLastError();
-        }
-      }
-      T = t.get();
-    }
     if (own) {
       if (capturing && (!AS.buf.p || AS.buf.bytes < need))
         throw Error{DFMM_EINVAL, "dfmm_apply under stream capture needs an earlier uncaptured apply"};
@@ -2259,7 +2203,7 @@ void run_apply(dfmm_plan_s& P, const ReqTable& R, int nrhs, hipStream_t st, void
       lock.unlock();
     }
     run_apply64(P, reinterpret_cast<const double2*>(R.f[0]), reinterpret_cast<double2*>(R.u[0]), nrhs, st,
-                own ? AS.buf.p : ws, T);
+                own ? AS.buf.p : ws);
     return;
   }
   const WsLayout L = plan_layout(P, nrhs);
@@ -2274,12 +2218,8 @@ void run_apply(dfmm_plan_s& P, const ReqTable& R, int nrhs, hipStream_t st, void
   const Ws S = carve(L, own ? AS.buf.p : ws);
   LaunchSet& LS = launch_set(P, AS, S, nrhs, st);
   if (capturing) AS.captured = true;
-  // few right-hand sides: the first apply takes the general form (the same sums), and
-  // the host makes the tables while the device works on it
-  const SlotTileSet* T = LS.tiles.get();
-  const bool make_tiles = !T && LS.slot && 2 * nrhs <= kTileCols && !capturing && !existing_only;
-  // the launch set is immutable from here but for its tables; applies on caller
-  // workspaces run concurrently (the stage timer and the second stream belong to dfmm_apply)
+  // the launch set is immutable from here: applies on caller workspaces run
+  // concurrently (the stage timer and the second stream belong to dfmm_apply)
   if (!own) lock.unlock();
   const int64_t N = P.N;
   const int64_t nleaf = P.lf.nleaf;
@@ -2367,38 +2307,33 @@ void run_apply(dfmm_plan_s& P, const ReqTable& R, int nrhs, hipStream_t st, void
     // trees first run LF-M2M from the deepest LF level up to width 1/2.
     for (int k = int(P.lfd.size()) - 1; k >= 0; --k) {
       const LFDeep& Q = P.lfd[size_t(k)];
-      launch_slot(LS.lfd_up[size_t(k)], T ? &T->lfd_up[size_t(k)] : nullptr,
-                  Q.m2m.A.as<float4>(), S.flf.as<float2>(), Rl, nullptr, nullptr, 0, nrhs,
+      launch_slot(LS.lfd_up[size_t(k)], Q.m2m.A.as<float4>(), S.flf.as<float2>(), Rl, nullptr, nullptr, 0, nrhs,
                   S.flf.as<float2>(), false, st, Q.up_dst.as<int>());
       mark(ST_M2M);
     }
     for (int e = 0; e <= e_top; ++e) {
       const float2* Fc = e == 0 ? S.flf.as<float2>() : S.F[e - 1].as<float2>();
       const int KC = e == 0 ? Rl : P.hf[e - 1].R;
-      launch_slot(LS.up[e], T ? &T->up[e] : nullptr,
-                  P.hf[e].m2m.A.as<float4>(), Fc, KC, nullptr, nullptr, 0, nrhs,
+      launch_slot(LS.up[e], P.hf[e].m2m.A.as<float4>(), Fc, KC, nullptr, nullptr, 0, nrhs,
                   S.F[e].as<float2>(), false, st);
       mark(ST_M2M);
     }
     for (int e = e_top; e >= 0; --e) {
       const HFLevel& H = P.hf[e];
       const bool par = e < e_top;
-      launch_slot(LS.down[e], T ? &T->down[e] : nullptr,
-                  H.m2l.A.as<float4>(), S.F[e].as<float2>(), H.R,
+      launch_slot(LS.down[e], H.m2l.A.as<float4>(), S.F[e].as<float2>(), H.R,
                   par ? P.hf[e + 1].l2l.A.as<float4>() : nullptr, par ? S.U[e + 1].as<float2>() : nullptr,
                   par ? P.hf[e + 1].R : 0, nrhs, S.U[e].as<float2>(), true, st);
       mark(ST_M2L);
     }
-    launch_slot(LS.lf_down, T ? &T->lf_down : nullptr,
-                P.lf.m2l.A.as<float4>(), S.flf.as<float2>(), Rl,
+    launch_slot(LS.lf_down, P.lf.m2l.A.as<float4>(), S.flf.as<float2>(), Rl,
                 e_top >= 0 ? P.hf[0].l2l.A.as<float4>() : nullptr, e_top >= 0 ? S.U[0].as<float2>() : nullptr,
                 e_top >= 0 ? P.hf[0].R : 0, nrhs, S.ulf.as<float2>(), true, st);
     mark(ST_LF_M2L);
     // adaptive trees: LF-M2L + LF-L2L of each deeper level into its boxes' LF vectors
     for (size_t k = 0; k < P.lfd.size(); ++k) {
       const LFDeep& Q = P.lfd[k];
-      launch_slot(LS.lfd_down[k], T ? &T->lfd_down[k] : nullptr,
-                  Q.m2l.A.as<float4>(), S.flf.as<float2>(), Rl, Q.l2l.A.as<float4>(),
+      launch_slot(LS.lfd_down[k], Q.m2l.A.as<float4>(), S.flf.as<float2>(), Rl, Q.l2l.A.as<float4>(),
                   S.ulf.as<float2>(), Rl, nrhs, S.ulf.as<float2>() + Q.base * nrhs * Rl, true, st);
       mark(ST_LF_M2L);
     }
@@ -2525,10 +2460,6 @@ void run_apply(dfmm_plan_s& P, const ReqTable& R, int nrhs, hipStream_t st, void
   }
   mark(ST_LEAF);
   DFMM_HIP(hipGetLastError());
-  if (make_tiles) {
-    if (!own) lock.lock();
-    if (!LS.tiles) prepare_tiles(P, nrhs, LS);
-  }
 }
 
 // ---- applies without allocation -------------------------------------------------------

@@ -13,6 +13,7 @@
 #include <string>
 
 #include "internal.hpp"
+#include "slot_merge.hpp"
 
 namespace dfmm {
 
@@ -171,7 +172,7 @@ struct Slot64Args {
   const int* order;
   const int* t0;
   const int* gm;
-  const int4* terms;  // (operator double4 offset, source vector, K | kind << 14, 0)
+  const int4* terms;  // (operator double4 offset, K | kind << 14, source vector, key)
   const double4* A0;
   const double4* A1;
   const double2* X0;
@@ -202,11 +203,11 @@ __global__ void __launch_bounds__(256) k_slot64(const Slot64Args a, int nrhs, do
   for (int t = 0; t < MT; ++t) acc[t] = v4d{0.0, 0.0, 0.0, 0.0};
   for (int i = tb; i < te; ++i) {
     const int4 e = a.terms[i];
-    const int kind = (e.z >> 14) & 1;
-    const int Kg = e.z & 0xFFF;
+    const int kind = (e.y >> 14) & 1;
+    const int Kg = e.y & 0xFFF;
     const int KX = kind ? a.KX1 : a.KX0;
     const double4* A = (kind ? a.A1 : a.A0) + e.x;
-    const double2* X = (kind ? a.X1 : a.X0) + (int64_t(e.y) * nrhs + c0) * KX;
+    const double2* X = (kind ? a.X1 : a.X0) + (int64_t(e.z) * nrhs + c0) * KX;
     const int Q4 = Kg / 8;          // k-steps: 8 complex k each (4 quarters x 2)
     __syncthreads();                // the previous term's columns are consumed
     // column c: its first Kg complex entries as Kg / 2 double4, in order (quarter
@@ -262,24 +263,22 @@ __global__ void __launch_bounds__(256) k_slot64(const Slot64Args a, int nrhs, do
   }
 }
 
-// The same for few right-hand sides (SlotTiles): the 16 columns of a workgroup are
-// (group, rhs) of neighbouring groups, each column's vector of a term comes from
-// the term's table, and columns without the term are zeros.  At one right-hand
-// side the form above multiplies 15 columns of padding and reads an operator
-// (0.8 MB at rank 232) for every term of every slot; here about 5 of 16 columns
-// of a term are in use.  A column's products and their order are those of the
-// form above, so the two give the same bits.  A wave takes MT row tiles of the
-// slice, with the operator rows of T64_RING steps in flight (a step
-// is 256 matrix-core cycles; 12 steps measured the same).  Eight waves share the
-// 60 KB of staged columns (rank 232): two workgroups of 8 fit a CU, two of 4
-// left half of its wave slots empty and ran a second round.  A term's columns, and the
-// first operator rows, are loaded while the term before multiplies.
+// The same for few right-hand sides (TileTerms): the 16 columns of a workgroup are
+// (group, rhs) of neighbouring groups, and columns without a term are zeros there.
+// At one right-hand side the form above multiplies 15 columns of padding and reads
+// an operator (0.8 MB at rank 232) for every term of every slot; here 1.8 to 5 of
+// 16 columns of a term are in use (tiles of 4 to 16 groups).  A column's products
+// and their order are those of the form above, so the two give the same bits.  A
+// wave takes MT row tiles of the slice, with the operator rows of T64_RING steps in
+// flight (a step is 256 matrix-core cycles; 12 steps measured the same).  Eight
+// waves share the 60 KB of staged columns (rank 232): two workgroups of 8 fit a CU,
+// two of 4 left half of its wave slots empty and ran a second round.  A term's first
+// operator rows are loaded while the term before multiplies, its columns from when
+// those of the term before are in LDS: before the barrier and the merge, which is 8%
+// of the K = 8 sphere at one right-hand side (5.00 -> 4.60 ms).
 struct Tile64Args {
-  const int* t0;
-  const int* gm;
-  const int4* head;  // (operator double4 offset, K | kind << 14, 0, 0)
-  const int* vec;
-  const int* dst;
+  const int4* rec;    // SlotGemm: the cut's records, terms
+  const int4* terms;  // (operator double4 offset, K | kind << 14, source vector, key)
   const double4* A0;
   const double4* A1;
   const double2* X0;
@@ -287,13 +286,14 @@ struct Tile64Args {
   int KX0, KX1;
   int M;
   int S;  // LDS column stride in double4
+  int nrhs, per, lead;
   int slices;  // workgroups of a tile
 };
 constexpr int T64_RING = 4;
 constexpr int T64_NW = 8;   // waves per workgroup
 constexpr int T64_TPC = 64 * T64_NW / kTileCols;  // threads that stage a column
 constexpr int T64_XQ = 4;   // double4 per thread and term
-constexpr int T64_MAXK = 2 * T64_TPC * T64_XQ;
+static_assert(kTile64MaxK <= 2 * T64_TPC * T64_XQ, "the staging covers a column");
 
 template <int MT>
 __global__ void __launch_bounds__(64 * T64_NW, 4) k_tile64(const Tile64Args a, double2* __restrict__ Y) {
@@ -305,88 +305,83 @@ __global__ void __launch_bounds__(64 * T64_NW, 4) k_tile64(const Tile64Args a, d
   const bool odd = (j & 1) != 0;
   // workgroup id = tile x slices + slice, on grid x (y ends at 65,535)
   const int g = int(blockIdx.x) / a.slices, slice = int(blockIdx.x) - g * a.slices;
-  const int tb = a.t0[g], te = a.t0[g + 1];
-  const int nM = a.gm[g] / 8;
+  TileTerms list(a.rec + int64_t(g) * a.per, a.per, a.terms, a.nrhs, a.lead,
+                 reinterpret_cast<int2*>(xs64 + kTileCols * a.S));
+  const int nM = list.Mg / 8;
   const int m0 = slice * T64_NW + wave, mstep = T64_NW * a.slices;
   v4d acc[MT];
 #pragma unroll
   for (int t = 0; t < MT; ++t) acc[t] = v4d{0.0, 0.0, 0.0, 0.0};
   const int sc = tid / T64_TPC, sq = tid % T64_TPC;  // this thread's column and first entry of the staging
   double4 ring[T64_RING];
-  auto rows = [&](int4 h, int m) {
-    const int kind = (h.y >> 14) & 1, Q4 = (h.y & 0xFFF) / 8;
-    return (kind ? a.A1 : a.A0) + h.x + int64_t(m) * Q4 * 32 + (j >> 1) * 4 + kr;
+  auto rows = [&](const TileTerm& q, int m) {
+    return (q.kind ? a.A1 : a.A0) + q.aoff + int64_t(m) * (q.K / 8) * 32 + (j >> 1) * 4 + kr;
   };
-  auto fill = [&](int4 h, int m) {
-    const double4* ap = rows(h, m);
-    const int Q4 = (h.y & 0xFFF) / 8;
+  auto fill = [&](const TileTerm& q, int m) {
+    const double4* ap = rows(q, m);
 #pragma unroll
-    for (int u = 0; u < T64_RING; ++u) ring[u] = ap[min(u, Q4 - 1) * 32];
-  };
-  auto uni = [](int4 h) {
-    h.x = __builtin_amdgcn_readfirstlane(h.x);
-    h.y = __builtin_amdgcn_readfirstlane(h.y);
-    return h;
+    for (int u = 0; u < T64_RING; ++u) ring[u] = ap[min(u, q.K / 8 - 1) * 32];
   };
   double4 xv[T64_XQ];
-  auto x_load = [&](int4 h, int src) {
-    const int kind = (h.y >> 14) & 1, Kg = h.y & 0xFFF;
+  auto x_load = [&](const TileTerm& q) {
+    // the wave's lanes stage columns 2 wave (lower half) and 2 wave + 1
+    static_assert(T64_TPC == 32, "two columns per wave");
+    const int lo = __builtin_amdgcn_readlane(q.src, 2 * wave), hi = __builtin_amdgcn_readlane(q.src, 2 * wave + 1);
+    const int src = lane < 32 ? lo : hi;
     const double4* X =
-        reinterpret_cast<const double4*>((kind ? a.X1 : a.X0) + int64_t(max(src, 0)) * (kind ? a.KX1 : a.KX0));
+        reinterpret_cast<const double4*>((q.kind ? a.X1 : a.X0) + int64_t(max(src, 0)) * (q.kind ? a.KX1 : a.KX0));
 #pragma unroll
     for (int u = 0; u < T64_XQ; ++u) {
-      const int q = sq + T64_TPC * u;
+      const int i = sq + T64_TPC * u;
       xv[u] = make_double4(0.0, 0.0, 0.0, 0.0);
-      if (src >= 0 && q < Kg / 2) xv[u] = X[q];
+      if (src >= 0 && i < q.K / 2) xv[u] = X[i];
     }
   };
-  auto vec = [&](int i) { return a.vec[int64_t(min(i, te - 1)) * kTileCols + sc]; };
-  int4 h = make_int4(0, 8, 0, 0);
-  int src1 = -1;  // the next term's source
-  if (tb < te) {
-    h = uni(a.head[tb]);
-    if (m0 < nM) fill(h, m0);
-    x_load(h, vec(tb));
-    src1 = vec(tb + 1);
-  }
-  for (int i = tb; i < te; ++i) {
-    const int4 hn = i + 1 < te ? uni(a.head[i + 1]) : h;
-    const int Kg = h.y & 0xFFF, Q4 = Kg / 8;
-    __syncthreads();  // the previous term's columns are consumed
+  TileTerm T = list.next();
+  if (T.any) {
+    TileTerm Tn = list.next();
+    if (m0 < nM) fill(T, m0);
+    x_load(T);
+    for (;;) {
+      const int Q4 = T.K / 8;
+      __syncthreads();  // the previous term's columns are consumed
 #pragma unroll
-    for (int u = 0; u < T64_XQ; ++u)
-      if (sq + T64_TPC * u < Kg / 2) xs64[sc * a.S + sq + T64_TPC * u] = xv[u];
-    __syncthreads();
-    x_load(hn, src1);
-    src1 = vec(i + 2);
-    const double4* bcol = xs64 + j * a.S + kr * Q4;
+      for (int u = 0; u < T64_XQ; ++u)
+        if (sq + T64_TPC * u < T.K / 2) xs64[sc * a.S + sq + T64_TPC * u] = xv[u];
+      x_load(Tn);
+      const TileTerm Tnn = list.next();  // (while the columns go to LDS)
+      __syncthreads();
+      const double4* bcol = xs64 + j * a.S + kr * Q4;
 #pragma unroll
-    for (int t = 0; t < MT; ++t) {
-      const int m = m0 + mstep * t;
-      if (m < nM) {  // wave-uniform
-        const double4* ap = rows(h, m);
-        for (int s0 = 0; s0 < Q4; s0 += T64_RING)
+      for (int t = 0; t < MT; ++t) {
+        const int m = m0 + mstep * t;
+        if (m < nM) {  // wave-uniform
+          const double4* ap = rows(T, m);
+          for (int s0 = 0; s0 < Q4; s0 += T64_RING)
 #pragma unroll
-          for (int u = 0; u < T64_RING; ++u)
-            if (s0 + u < Q4) {
-              const double4 v = ring[u];
-              ring[u] = ap[min(s0 + u + T64_RING, Q4 - 1) * 32];
-              const double4 b = bcol[s0 + u];
-              const double f0 = odd ? v.y : v.x, f1 = odd ? v.x : -v.y, f2 = odd ? v.w : v.z, f3 = odd ? v.z : -v.w;
-              acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(f0, b.x, acc[t], 0, 0, 0);
-              acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(f1, b.y, acc[t], 0, 0, 0);
-              acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(f2, b.z, acc[t], 0, 0, 0);
-              acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(f3, b.w, acc[t], 0, 0, 0);
-            }
-        // the next tile of this term, or the first one of the next term
-        const bool more = t + 1 < MT && m + mstep < nM;
-        fill(more ? h : hn, more ? m + mstep : m0);
+            for (int u = 0; u < T64_RING; ++u)
+              if (s0 + u < Q4) {
+                const double4 v = ring[u];
+                ring[u] = ap[min(s0 + u + T64_RING, Q4 - 1) * 32];
+                const double4 b = bcol[s0 + u];
+                const double f0 = odd ? v.y : v.x, f1 = odd ? v.x : -v.y, f2 = odd ? v.w : v.z, f3 = odd ? v.z : -v.w;
+                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(f0, b.x, acc[t], 0, 0, 0);
+                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(f1, b.y, acc[t], 0, 0, 0);
+                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(f2, b.z, acc[t], 0, 0, 0);
+                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(f3, b.w, acc[t], 0, 0, 0);
+              }
+          // the next tile of this term, or the first one of the next term
+          const bool more = t + 1 < MT && m + mstep < nM;
+          fill(more || !Tn.any ? T : Tn, more ? m + mstep : m0);
+        }
       }
+      if (!Tn.any) break;
+      T = Tn;
+      Tn = Tnn;
     }
-    h = hn;
   }
   // (the accumulator layout of k_slot64)
-  const int out = a.dst[int64_t(g) * kTileCols + j];
+  const int out = list.out;
 #pragma unroll
   for (int t = 0; t < MT; ++t) {
     const int m = m0 + mstep * t;
@@ -459,9 +454,8 @@ void launch_slot64_t(const SlotGemm& S, const Slot64Args& a, int nrhs, double2* 
                      a, nrhs, Y);
 }
 
-// T: the tables for few right-hand sides, or null
-void launch_slot64(const SlotGemm& S, const SlotTiles* T, const double4* A0, const double2* X0, int KX0,
-                   const double4* A1, const double2* X1, int KX1, int nrhs, double2* Y, hipStream_t st) {
+void launch_slot64(const SlotGemm& S, const double4* A0, const double2* X0, int KX0, const double4* A1,
+                   const double2* X1, int KX1, int nrhs, double2* Y, hipStream_t st) {
   if (S.ngroups == 0) return;
   if (S.split2 || S.Kmax % 8 != 0) throw Error{DFMM_EUNSUPPORTED, "float64 slot GEMM: bad operator packing"};
   const int cpg = (nrhs + 15) / 16;
@@ -470,19 +464,22 @@ void launch_slot64(const SlotGemm& S, const SlotTiles* T, const double4* A0, con
   const int mt = slot64_mt(S);
   if (sizeof(double4) * 16 * size_t(a.S) > size_t(kLds64))
     throw Error{DFMM_EUNSUPPORTED, "skeleton rank too large for the float64 slot GEMM"};
-  if (T && T->ntiles > 0 && S.Kmax <= T64_MAXK) {
+  const int64_t ntiles = nrhs <= kTileRhs ? S.cut[nrhs].ntiles : 0;
+  if (ntiles > 0) {
     // one row tile per wave until the launch has two workgroups per CU, then two:
     // each slice stages the columns again
     const int nM = S.M / 8;
-    const bool two = T->ntiles * ((nM + 2 * T64_NW - 1) / (2 * T64_NW)) >= 512;
+    const bool two = ntiles * ((nM + 2 * T64_NW - 1) / (2 * T64_NW)) >= 512;
     const int per = (two ? 2 : 1) * T64_NW;
     // the slices first: workgroups go to the 8 XCDs in turn, so the tiles on one of
     // them read the same rows of every operator
     const int slices = (nM + per - 1) / per;
-    const Tile64Args t{T->t0, T->gm, T->head, T->vec, T->dst, A0, a.A1, X0, a.X1, KX0, a.KX1, S.M, a.S, slices};
+    const Tile64Args t{S.rec.as<int4>() + S.cut[nrhs].at, a.terms, A0, a.A1, X0, a.X1, KX0, a.KX1, S.M, a.S, nrhs,
+                       S.cut[nrhs].per, S.lead, slices};
     auto kern = two ? &k_tile64<2> : &k_tile64<1>;
     lds_limit64(reinterpret_cast<const void*>(kern));
-    hipLaunchKernelGGL(kern, dim3(unsigned(T->ntiles * slices)), dim3(64 * T64_NW), sizeof(double4) * 16 * size_t(a.S), st, t, Y);
+    hipLaunchKernelGGL(kern, dim3(unsigned(ntiles * slices)), dim3(64 * T64_NW),
+                       sizeof(double4) * kTileCols * size_t(a.S) + size_t(S.cut[nrhs].entries) * sizeof(int2), st, t, Y);
     return;
   }
   if (mt <= 2) launch_slot64_t<2>(S, a, nrhs, Y, st);
@@ -493,16 +490,7 @@ void launch_slot64(const SlotGemm& S, const SlotTiles* T, const double4* A0, con
 
 }  // namespace
 
-Tiles64::Tiles64(const dfmm_plan_s& P, int nrhs) : up(P.hf.size()), down(P.hf.size()) {
-  std::vector<TileJob> jobs{{&P.lf.down, P.lf.down.M / 8, nullptr, &lf}};
-  for (size_t e = 0; e < P.hf.size(); ++e) {
-    jobs.push_back({&P.hf[e].up, P.hf[e].up.M / 8, nullptr, &up[e]});
-    jobs.push_back({&P.hf[e].down, P.hf[e].down.M / 8, nullptr, &down[e]});
-  }
-  build_slot_tiles(jobs, nrhs, buf);
-}
-
-void run_apply64(dfmm_plan_s& P, const double2* f, double2* u, int nrhs, hipStream_t st, void* ws, const Tiles64* T) {
+void run_apply64(dfmm_plan_s& P, const double2* f, double2* u, int nrhs, hipStream_t st, void* ws) {
   const WsLayout L = ws_layout(ws_shape64(P), nrhs, false, 16);
   if (!ws) throw Error{DFMM_EINVAL, "no workspace"};
   char* b = static_cast<char*>(ws);
@@ -525,17 +513,17 @@ void run_apply64(dfmm_plan_s& P, const double2* f, double2* u, int nrhs, hipStre
   for (int e = 0; e <= e_top; ++e) {
     const double2* Fc = e == 0 ? flf : F[size_t(e - 1)];
     const int KC = e == 0 ? Rl : P.hf[size_t(e - 1)].R;
-    launch_slot64(P.hf[size_t(e)].up, T ? &T->up[size_t(e)] : nullptr, P.hf[size_t(e)].m2m.A.as<double4>(), Fc, KC, nullptr, nullptr, 0, nrhs,
+    launch_slot64(P.hf[size_t(e)].up, P.hf[size_t(e)].m2m.A.as<double4>(), Fc, KC, nullptr, nullptr, 0, nrhs,
                   F[size_t(e)], st);
   }
   for (int e = e_top; e >= 0; --e) {
     const HFLevel& H = P.hf[size_t(e)];
     const bool par = e < e_top;
-    launch_slot64(H.down, T ? &T->down[size_t(e)] : nullptr, H.m2l.A.as<double4>(), F[size_t(e)], H.R,
+    launch_slot64(H.down, H.m2l.A.as<double4>(), F[size_t(e)], H.R,
                   par ? P.hf[size_t(e + 1)].l2l.A.as<double4>() : nullptr, par ? U[size_t(e + 1)] : nullptr,
                   par ? P.hf[size_t(e + 1)].R : 0, nrhs, U[size_t(e)], st);
   }
-  launch_slot64(P.lf.down, T ? &T->lf : nullptr, P.lf.m2l.A.as<double4>(), flf, Rl, e_top >= 0 ? P.hf[0].l2l.A.as<double4>() : nullptr,
+  launch_slot64(P.lf.down, P.lf.m2l.A.as<double4>(), flf, Rl, e_top >= 0 ? P.hf[0].l2l.A.as<double4>() : nullptr,
                 e_top >= 0 ? U[0] : nullptr, e_top >= 0 ? P.hf[0].R : 0, nrhs, ulf, st);
   hipLaunchKernelGGL(k_l2t64, dim3(nblk(N * 16, L64_BS)), dim3(L64_BS), 0, st, P.lf.W.as<double2>(), ulf,
                      P.leaf_of.as<int>(), unear, P.perm_d.as<int>(), Rl, nrhs, N, u);

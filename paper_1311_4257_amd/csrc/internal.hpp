@@ -141,6 +141,8 @@ struct GGemm {
 struct SlotTerm {
   int32_t dst, op, src, kind;
 };
+constexpr int kTileCols = 16, kTileRhs = kTileCols / 2;
+constexpr int kTileMaxK = 128, kTile64MaxK = 256;  // columns of an operator in tiles (float32, float64)
 struct SlotGemm {
   int M = 0;                 // row stride of the output vectors (padded rank)
   int Kmax = 8;              // largest packed K of any term (LDS column length)
@@ -152,51 +154,38 @@ struct SlotGemm {
   DevBuf order;              // int32[ngroups]: launch order, groups with more terms first
   DevBuf t0;                 // int32[ngroups + 1]: term range of each group
   DevBuf gm;                 // int32[ngroups]: padded rows M_g of the group's operators
-  DevBuf terms;              // int32[nterms][4]: (operator float4 offset, source vector,
-                             //   packed K | split << 12 | kind << 14, 0)
-  // for build_slot_tiles: host copies of the term ranges and table, operator index of
-  // each term, padded rows and neighbourhood key of each group, the groups ordered by
-  // the two, and the kind that the groups' terms start with (-1: no common order)
-  std::vector<int32_t> t0_h, terms_h, op_h, gm_h, by_near_h;
-  std::vector<int64_t> near_h;
-  int lead = -1;
+  DevBuf terms;              // int32[nterms][4]: (operator float4 offset, packed K | kind << 14,
+                             //   source vector, with tiles the key (kind not lead) << 31 |
+                             //   offset | K / 8 - 1, which increases in a group)
+  // Up to kTileRhs right-hand sides (adaptive and float64 plans; TileTerms has the
+  // form): for each number of right-hand sides a cut of the groups into tiles of up to
+  // kTileCols / nrhs of one class and row count, the tiles with the most terms first.
+  DevBuf rec;                // int32[][4], per records a tile, one per group: (first term, end,
+                             //   output vector, padded rows | entries before its list in the tile << 12);
+                             //   output vector -1: no group
+  int lead = 0;              // the kind that the groups' terms start with
+  struct Cut {
+    int64_t at = 0, ntiles = 0;  // its first record, its tiles (none: the form above)
+    int per = 1;
+    int entries = 0;         // of a tile's term lists, each with an end mark, the largest
+  } cut[kTileRhs + 1];
 };
-// Slot-form tables for few right-hand sides: a tile holds 16 columns, one per
-// (group, rhs) of 16 / nrhs neighbouring groups, and walks the union of their
-// terms, so that an operator is read and multiplied once for all of its groups
-// that use it.  A column without the term has zeros there, which leave its sum as
-// it is: every column sums its own group's terms in their order.
-constexpr int kTileCols = 16;
-struct SlotTiles {
-  int64_t ntiles = 0;
-  // device tables (in the buffer of build_slot_tiles)
-  const int* t0 = nullptr;    // [ntiles + 1]: term range of each tile (longest first)
-  const int* gm = nullptr;    // [ntiles]: padded rows
-  const int4* head = nullptr; // [nterms]: (operator offset, K | kind << 14, 0, 0)
-  const int* vec = nullptr;   // [nterms][kTileCols]: source vector (slot nrhs + rhs) of each column, -1: none
-  const int* dst = nullptr;   // [ntiles][kTileCols]: output vector of each column, -1: none
-};
-// One launch's tables to make.  row_tiles: row tiles (waves) of a tile in the kernel
-// that uses them; gdst: output vector of each group (null: its own index).
-struct TileJob {
-  const SlotGemm* S;
-  int row_tiles;
-  const std::vector<int32_t>* gdst;
-  SlotTiles* out;
-};
-// Makes the tables of all jobs in one device buffer.  A job whose groups' terms have
-// no common order keeps ntiles = 0.
-void build_slot_tiles(const std::vector<TileJob>& jobs, int nrhs, DevBuf& buf);
+// A group's place among the tiles: its class (groups of one class have many
+// operators in common) << 32 | its order in it.
+using NearKey = int64_t;
 // Host view of one kind's operators: float4 offset and packed K (split doubling
 // included) of every operator index, and the split factor.
 struct SlotKind {
   const GGemm* G = nullptr;  // aoff_h, kpk_h and opflops of the operators (null: no terms of this kind)
   int split = 1;
 };
-// Term lists -> device tables; terms of a group keep the order given.
+// Term lists -> device tables; terms of a group keep the order given.  near: the
+// groups' keys (empty: no tiles); row_tiles, max_k: row tiles (waves) of a tile and
+// largest K in the kernel that uses them; gdst: output vector of each group (null: its own index).
 void build_slot_gemm(SlotGemm& S, int M, int64_t ngroups, const std::vector<int32_t>& gM,
                      const std::vector<SlotTerm>& terms, const SlotKind kinds[2], int kx_max,
-                     const std::vector<int64_t>& near);
+                     const std::vector<NearKey>& near, int row_tiles, int max_k,
+                     const std::vector<int32_t>* gdst = nullptr);
 
 // Pack an M x K complex matrix (row-major, interleaved float64) into the
 // fragment order of the float64 GEMM kernel
@@ -255,7 +244,6 @@ struct LFDeep {
   DevBuf red_start, red_idx; // pair-form CSR of the M2L (built with the operators, unused)
   SlotGemm up;               // LF-M2M: the split boxes of level l - 1 <- their children
   DevBuf up_dst;             // int32[nsplit]: LF vector index of each of those parents
-  std::vector<int32_t> up_dst_h;
   SlotGemm down;             // LF-M2L pairs + LF-L2L term of every box of this level
 };
 
@@ -361,16 +349,7 @@ size_t plan_device_bytes(const dfmm_plan_s& P);
 // float64 plans: the whole pass in complex128 on a caller-sized workspace
 // (ws_layout(ws_shape64(P), nrhs, false, 16))
 WsShape ws_shape64(const dfmm_plan_s& P);
-// The tables of a float64 apply with few right-hand sides (up to kTiles64Rhs; null:
-// the general form, with the same results bit for bit).
-constexpr int kTiles64Rhs = kTileCols / 2;
-struct Tiles64 {
-  std::vector<SlotTiles> up, down;  // per HF level
-  SlotTiles lf;
-  DevBuf buf;
-  Tiles64(const dfmm_plan_s& P, int nrhs);
-};
-void run_apply64(dfmm_plan_s& P, const double2* f, double2* u, int nrhs, hipStream_t st, void* ws, const Tiles64* T);
+void run_apply64(dfmm_plan_s& P, const double2* f, double2* u, int nrhs, hipStream_t st, void* ws);
 // S2M and L2T weights of every sorted point (float64, then stored in the plan's
 // precision).  DT holds D^T of each LF skeleton at R x R offsets, P.lf.a64 its
 // check points at R offsets; ra the skeletons' ranks, sk_of the skeleton of each leaf.

@@ -272,36 +272,116 @@ struct OpStore {
   }
 };
 
-namespace {
-inline int term_kind(const SlotGemm& S, int32_t i) { return (S.terms_h[size_t(4) * size_t(i) + 2] >> 14) & 1; }
-
-// The common order of the groups' terms: the kind that they start with, then the
-// operator index.  Returns that kind, -1 if there is none.
-int lead_kind(const SlotGemm& S) {
+// The cuts of a launch's groups into tiles (SlotGemm::rec): the groups in the order
+// of (padded rows, key), and for each number of right-hand sides runs of one class.
+// cnt: term ranges, tab: the term table, op: the operator of each term.
+static void build_cuts(SlotGemm& S, const std::vector<int32_t>& gM, const std::vector<int32_t>& cnt,
+                       std::vector<int32_t>& tab, const std::vector<int32_t>& op,
+                       const std::vector<NearKey>& near, int row_tiles, const std::vector<int32_t>* gdst) {
+  const int64_t n = S.ngroups;
+  // one order for all groups: the kind that they start with, then the operator
+  auto kind = [&](int32_t i) { return (tab[size_t(4) * size_t(i) + 1] >> 14) & 1; };
   int lead = -1;
-  for (int64_t g = 0; g < S.ngroups; ++g)
-    for (int32_t i = S.t0_h[size_t(g)] + 1; i < S.t0_h[size_t(g) + 1]; ++i) {
-      const int prev = term_kind(S, i - 1);
-      if (prev != term_kind(S, i)) {  // groups with both kinds decide it
-        if (lead >= 0 && lead != prev) return -1;
+  for (int64_t g = 0; g < n; ++g)
+    for (int32_t i = cnt[size_t(g)] + 1; i < cnt[size_t(g) + 1]; ++i) {
+      const int prev = kind(i - 1);
+      if (prev != kind(i)) {  // groups with both kinds decide it
+        if (lead >= 0 && lead != prev) return;
         lead = prev;
-      } else if (S.op_h[size_t(i)] <= S.op_h[size_t(i) - 1]) {
-        return -1;
+      } else if (op[size_t(i)] <= op[size_t(i) - 1]) {
+        return;
       }
     }
-  return std::max(lead, 0);
+  S.lead = std::max(lead, 0);
+  if (S.M >= 1 << 12) return;  // a record has 12 bits for the rows
+  for (size_t i = 0; i < op.size(); ++i) {
+    int32_t* e = &tab[4 * i];
+    const int32_t k8 = (e[1] & 0xFFF) / 8 - 1;
+    if (e[0] % 32 != 0 || k8 >= 32) return;  // (operators hold 64 complex entries at least, 32 float4)
+    e[3] = int32_t(uint32_t(kind(int32_t(i)) ^ S.lead) << 31 | uint32_t(e[0]) | uint32_t(k8));
+  }
+  if (n == 0) return;
+  std::vector<int32_t> by(static_cast<size_t>(n));
+  for (int64_t g = 0; g < n; ++g) by[size_t(g)] = int32_t(g);
+  std::stable_sort(by.begin(), by.end(), [&](int32_t a, int32_t b) {
+    if (gM[size_t(a)] != gM[size_t(b)]) return gM[size_t(a)] < gM[size_t(b)];
+    return near[size_t(a)] < near[size_t(b)];
+  });
+  auto same = [&](int64_t i, int64_t k) {
+    const size_t a = size_t(by[size_t(i)]), b = size_t(by[size_t(k)]);
+    return gM[a] == gM[b] && near[a] >> 32 == near[b] >> 32;
+  };
+  struct Tile {
+    int64_t first;
+    int32_t groups, terms;  // terms: of the union
+  };
+  auto cut = [&](int per, int& entries) {  // tiles of up to per groups; the longest lists of one
+    std::vector<Tile> ts;
+    entries = 0;
+    for (int64_t i = 0; i < n; i += ts.back().groups) {
+      int32_t k = 0, e = per;
+      for (; k < per && i + k < n && same(i, i + k); ++k) {
+        const size_t g = size_t(by[size_t(i + k)]);
+        e += cnt[g + 1] - cnt[g];
+      }
+      ts.push_back({i, k, 0});
+      entries = std::max(entries, e);
+    }
+    return ts;
+  };
+  std::vector<int32_t> seen;  // the last tile that held (operator, kind)
+  for (int32_t o : op) seen.resize(std::max(seen.size(), size_t(2) * size_t(o) + 2), -1);
+  int32_t mark = -1;
+  std::vector<int32_t> rec;
+  std::map<int, SlotGemm::Cut> made;  // by groups per tile
+  for (int nrhs = 1; nrhs <= kTileRhs; ++nrhs) {
+    // more groups of a tile share more operators (1.8 columns of a term in use with 4,
+    // 5 with 16), but leave fewer waves, one per row tile; as many as leave 1.5
+    // waves for each of the 1,024 SIMDs, and whose lists are 16 KB (float64: with 60 KB
+    // of columns two workgroups fit a CU; surfaces have 40 to 60 terms a group)
+    int per = kTileCols / nrhs;
+    while (per > 1 && (n + per - 1) / per * row_tiles < 1536) per /= 2;
+    SlotGemm::Cut c;
+    std::vector<Tile> ts = cut(per, c.entries);
+    for (; per > 1 && c.entries > 2048; ts = cut(per, c.entries)) per /= 2;
+    if (c.entries > 4096) continue;
+    if (made.count(per) == 0) {
+      for (Tile& t : ts) {
+        ++mark;
+        for (int32_t k = 0; k < t.groups; ++k) {
+          const size_t g = size_t(by[size_t(t.first + k)]);
+          for (int32_t x = cnt[g]; x < cnt[g + 1]; ++x) {
+            int32_t& at = seen[size_t(2) * size_t(op[size_t(x)]) + size_t(kind(x))];
+            t.terms += at != mark;
+            at = mark;
+          }
+        }
+      }
+      std::stable_sort(ts.begin(), ts.end(), [](const Tile& a, const Tile& b) { return a.terms > b.terms; });
+      c.at = int64_t(rec.size()) / 4;
+      c.ntiles = int64_t(ts.size());
+      c.per = per;
+      for (const Tile& t : ts) {
+        int32_t before = 0;
+        for (int32_t k = 0; k < per; ++k) {  // past the last group: empty lists
+          const bool has = k < t.groups;
+          const size_t g = size_t(by[size_t(t.first + (has ? k : 0))]);
+          const int32_t len = has ? cnt[g + 1] - cnt[g] : 0;
+          rec.insert(rec.end(), {cnt[g], cnt[g] + len, !has ? -1 : (gdst ? (*gdst)[g] : int32_t(g)),
+                                 gM[g] | before << 12});
+          before += len + 1;
+        }
+      }
+      made[per] = c;
+    }
+    S.cut[nrhs] = made[per];
+  }
+  S.rec.upload(rec);
 }
-
-struct HostTile {
-  std::vector<int32_t> g;  // its groups
-  std::vector<int32_t> at;  // where each of them stands in its terms
-  std::vector<int32_t> head, vec;
-};
-}  // namespace
 
 void build_slot_gemm(SlotGemm& S, int M, int64_t ngroups, const std::vector<int32_t>& gM,
                      const std::vector<SlotTerm>& terms, const SlotKind kinds[2], int kx_max,
-                     const std::vector<int64_t>& near) {
+                     const std::vector<NearKey>& near, int row_tiles, int max_k, const std::vector<int32_t>* gdst) {
   S.M = M;
   S.KXmax = kx_max;
   S.split2 = false;
@@ -328,8 +408,8 @@ void build_slot_gemm(SlotGemm& S, int M, int64_t ngroups, const std::vector<int3
     op[at] = t.op;
     int32_t* e = &tab[size_t(4) * at];
     e[0] = int32_t(aoff);
-    e[1] = t.src;
-    e[2] = kp | (k.split << 12) | (t.kind << 14);
+    e[1] = kp | (t.kind << 14);
+    e[2] = t.src;
     e[3] = 0;
     kmax = std::max(kmax, kp);
     S.split2 = S.split2 || k.split != 1;
@@ -348,132 +428,8 @@ void build_slot_gemm(SlotGemm& S, int M, int64_t ngroups, const std::vector<int3
   S.order.upload(order);
   S.t0.upload(cnt);
   S.gm.upload(gM);
+  if (!near.empty() && kmax <= max_k) build_cuts(S, gM, cnt, tab, op, near, row_tiles, gdst);
   S.terms.upload(tab);
-  S.t0_h = std::move(cnt);
-  S.terms_h = std::move(tab);
-  S.op_h = std::move(op);
-  S.gm_h = gM;
-  S.near_h = near;
-  S.by_near_h.resize(size_t(S.ngroups));
-  for (int64_t g = 0; g < S.ngroups; ++g) S.by_near_h[size_t(g)] = int32_t(g);
-  std::stable_sort(S.by_near_h.begin(), S.by_near_h.end(), [&](int32_t a, int32_t b) {
-    if (S.gm_h[size_t(a)] != S.gm_h[size_t(b)]) return S.gm_h[size_t(a)] < S.gm_h[size_t(b)];
-    return S.near_h[size_t(a)] < S.near_h[size_t(b)];
-  });
-  S.lead = lead_kind(S);
-}
-
-void build_slot_tiles(const std::vector<TileJob>& jobs, int nrhs, DevBuf& buf) {
-  std::vector<std::vector<HostTile>> all(jobs.size());
-  std::vector<std::pair<size_t, size_t>> work;  // (job, tile)
-  for (size_t q = 0; q < jobs.size(); ++q) {
-    const SlotGemm& S = *jobs[q].S;
-    jobs[q].out->ntiles = 0;
-    if (S.ngroups == 0 || S.lead < 0) continue;
-    // groups of a tile: more of them share more operators (about 1.8 columns of a
-    // term in use with 4, 5 with 16), but leave fewer waves, one per row tile; as
-    // many as leave 1.5 waves for each of the 1,024 SIMDs
-    int per = kTileCols / nrhs;
-    while (per > 1 && (S.ngroups + per - 1) / per * jobs[q].row_tiles < 1536) per /= 2;
-    const std::vector<int32_t>& gs = S.by_near_h;
-    for (size_t i = 0; i < gs.size();) {
-      HostTile t;
-      while (i < gs.size() && int(t.g.size()) < per &&
-             (t.g.empty() || (S.gm_h[size_t(gs[i])] == S.gm_h[size_t(t.g[0])] &&
-                              (S.near_h[size_t(gs[i])] >> 32) == (S.near_h[size_t(t.g[0])] >> 32))))
-        t.g.push_back(gs[i++]);
-      work.push_back({q, all[q].size()});
-      all[q].push_back(std::move(t));
-    }
-  }
-  // merge the term lists of each tile's groups
-  constexpr size_t kStep = 16;  // tiles per task
-  parallel_for(int64_t((work.size() + kStep - 1) / kStep), [&](int64_t w) {
-    for (size_t i = size_t(w) * kStep; i < std::min(work.size(), size_t(w + 1) * kStep); ++i) {
-      const SlotGemm& S = *jobs[work[i].first].S;
-      HostTile& t = all[work[i].first][work[i].second];
-      const size_t n = t.g.size();
-      std::vector<int64_t> key(n);
-      size_t most = 0;
-      auto look = [&](size_t c) {
-        const int32_t k = t.at[c];
-        key[c] = k >= S.t0_h[size_t(t.g[c]) + 1]
-                     ? INT64_MAX
-                     : (int64_t(term_kind(S, k) == S.lead ? 0 : 1) << 32 | S.op_h[size_t(k)]);
-      };
-      for (size_t c = 0; c < n; ++c) {
-        t.at.push_back(S.t0_h[size_t(t.g[c])]);
-        most += size_t(S.t0_h[size_t(t.g[c]) + 1] - t.at[c]);
-        look(c);
-      }
-      t.head.reserve(4 * most);
-      t.vec.reserve(kTileCols * most);
-      for (;;) {
-        const int64_t best = *std::min_element(key.begin(), key.end());
-        if (best == INT64_MAX) break;
-        const size_t v0 = t.vec.size(), h0 = t.head.size();
-        t.vec.resize(v0 + kTileCols, -1);
-        t.head.resize(h0 + 4, 0);
-        for (size_t c = 0; c < n; ++c) {
-          if (key[c] != best) continue;
-          const int32_t* e = &S.terms_h[size_t(4) * size_t(t.at[c]++)];
-          t.head[h0] = e[0];
-          t.head[h0 + 1] = e[2];
-          for (int k = 0; k < nrhs; ++k) t.vec[v0 + c * size_t(nrhs) + size_t(k)] = e[1] * nrhs + k;
-          look(c);
-        }
-      }
-    }
-  });
-  // one buffer for the tables of all jobs: the small ones of each, its heads, its
-  // vectors, each at a multiple of 16 bytes
-  struct At {
-    size_t t0, gm, dst, head, vec;
-  };
-  std::vector<At> at(jobs.size());
-  size_t words = 0;
-  for (size_t q = 0; q < jobs.size(); ++q) {
-    std::stable_sort(all[q].begin(), all[q].end(),
-                     [](const HostTile& a, const HostTile& b) { return a.head.size() > b.head.size(); });
-    const size_t n = all[q].size();
-    size_t nterms = 0;
-    for (const HostTile& t : all[q]) nterms += t.head.size() / 4;
-    at[q].t0 = words;
-    at[q].gm = at[q].t0 + (n + 4) / 4 * 4;
-    at[q].dst = at[q].gm + (n + 3) / 4 * 4;
-    at[q].head = at[q].dst + kTileCols * n;
-    at[q].vec = at[q].head + 4 * nterms;
-    words = at[q].vec + kTileCols * nterms;
-    if (nterms > size_t(INT32_MAX)) throw Error{DFMM_ENOMEM, "slot tile tables too large"};
-  }
-  const std::unique_ptr<int32_t[]> host(new int32_t[std::max<size_t>(words, 1)]);
-  for (size_t q = 0; q < jobs.size(); ++q) {
-    int32_t t0 = host[at[q].t0] = 0;
-    for (size_t i = 0; i < all[q].size(); ++i) host[at[q].t0 + i + 1] = t0 += int32_t(all[q][i].head.size() / 4);
-  }
-  parallel_for(int64_t((work.size() + kStep - 1) / kStep), [&](int64_t w) {
-    for (size_t i = size_t(w) * kStep; i < std::min(work.size(), size_t(w + 1) * kStep); ++i) {
-      const size_t q = work[i].first, ti = work[i].second;
-      const SlotGemm& S = *jobs[q].S;
-      const HostTile& t = all[q][ti];
-      host[at[q].gm + ti] = S.gm_h[size_t(t.g[0])];
-      int32_t* dst = &host[at[q].dst + kTileCols * ti];
-      std::fill(dst, dst + kTileCols, -1);
-      for (size_t c = 0; c < t.g.size(); ++c)
-        for (int k = 0; k < nrhs; ++k)
-          dst[c * size_t(nrhs) + size_t(k)] = (jobs[q].gdst ? (*jobs[q].gdst)[size_t(t.g[c])] : t.g[c]) * nrhs + k;
-      const size_t b = size_t(host[at[q].t0 + ti]);
-      std::copy(t.head.begin(), t.head.end(), &host[at[q].head + 4 * b]);
-      std::copy(t.vec.begin(), t.vec.end(), &host[at[q].vec + kTileCols * b]);
-    }
-  });
-  buf.alloc(words * sizeof(int32_t));
-  if (words > 0) DFMM_HIP(hipMemcpy(buf.p, host.get(), words * sizeof(int32_t), hipMemcpyHostToDevice));
-  const int* d = buf.as<int>();
-  for (size_t q = 0; q < jobs.size(); ++q)
-    if (!all[q].empty())
-      *jobs[q].out = SlotTiles{int64_t(all[q].size()), d + at[q].t0, d + at[q].gm,
-                               reinterpret_cast<const int4*>(d + at[q].head), d + at[q].vec, d + at[q].dst};
 }
 
 // Device bytes held by a plan (every table and operator array; the apply
@@ -481,7 +437,9 @@ void build_slot_tiles(const std::vector<TileJob>& jobs, int nrhs, DevBuf& buf) {
 static size_t gg_bytes(const GGemm& G) {
   return G.A.bytes + G.vsrc.bytes;
 }
-static size_t slot_bytes(const SlotGemm& S) { return S.order.bytes + S.t0.bytes + S.gm.bytes + S.terms.bytes; }
+static size_t slot_bytes(const SlotGemm& S) {
+  return S.order.bytes + S.t0.bytes + S.gm.bytes + S.terms.bytes + S.rec.bytes;
+}
 size_t plan_device_bytes(const dfmm_plan_s& P) {
   size_t b = P.pthi.bytes + P.ptlo.bytes + P.perm_d.bytes + P.iperm_d.bytes + P.leaf_start.bytes + P.leaf_of.bytes +
              P.leaf_center.bytes + P.near_start.bytes + P.near_src.bytes;
@@ -1217,13 +1175,20 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
         gm[size_t(i)] = pad8(ops.hf[e][(in ? IS[l] : OS[l]).list[size_t(i)].second].r);
       return gm;
     };
+    // tiles for few right-hand sides: a uniform float32 plan takes the pair form there
+    // unless DFMM_SLOT forces the slot form
+    const char* force = std::getenv("DFMM_SLOT");
+    const bool tiles = fp64 || adaptive || (force && force[0] == '1');
+    auto row_tiles = [&](int M) { return fp64 ? M / 8 : (M + 15) / 16; };
+    const int max_k = fp64 ? kTile64MaxK : kTileMaxK;
     // neighbourhood order of the slots of a level: by wedge, from width 1 down by
     // octant (boxes of one octant have the same candidate offsets), then Morton
     auto near_key = [&](int64_t cls, int l, int64_t b, bool octant) {
       return (cls * 8 + (octant ? T.lv[size_t(l)].octant[size_t(b)] : 0)) << 32 | b;
     };
     auto slot_near = [&](int l, const std::vector<std::pair<int64_t, int>>& list, bool in) {
-      std::vector<int64_t> v;
+      std::vector<NearKey> v;
+      if (!tiles) return v;
       for (const auto& s : list) v.push_back(near_key(s.second, l, s.first, in && l == D - 1));
       return v;
     };
@@ -1232,16 +1197,16 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
       const int l = H.l;
       SlotKind up[2] = {{&H.m2m, hf_split}, {nullptr, 1}};
       build_slot_gemm(H.up, H.R, H.nout, slot_m(l, H.nout, false), up_terms[size_t(e)], up,
-                      e == 0 ? Rlf : P.hf[size_t(e - 1)].R, slot_near(l, OS[l].list, false));
+                      e == 0 ? Rlf : P.hf[size_t(e - 1)].R, slot_near(l, OS[l].list, false), row_tiles(H.R), max_k);
       SlotKind dn[2] = {{&H.m2l, hf_split}, {e < e_top ? &P.hf[size_t(e + 1)].l2l : nullptr, hf_split}};
       build_slot_gemm(H.down, H.R, H.nin, slot_m(l, H.nin, true), down_terms[size_t(e)], dn,
-                      std::max(H.R, e < e_top ? P.hf[size_t(e + 1)].R : 0), slot_near(l, IS[l].list, true));
+                      std::max(H.R, e < e_top ? P.hf[size_t(e + 1)].R : 0), slot_near(l, IS[l].list, true), row_tiles(H.R), max_k);
     }
-    std::vector<int64_t> lf_near;
-    for (int64_t b = 0; b < nD; ++b) lf_near.push_back(near_key(0, D, b, true));
+    std::vector<NearKey> lf_near;
+    for (int64_t b = 0; tiles && b < nD; ++b) lf_near.push_back(near_key(0, D, b, true));
     SlotKind dn[2] = {{&P.lf.m2l, 1}, {e_top >= 0 ? &P.hf[0].l2l : nullptr, hf_split}};
     build_slot_gemm(P.lf.down, Rlf, nD, std::vector<int32_t>(size_t(nD), Rlf), lf_terms, dn,
-                    std::max(Rlf, e_top >= 0 ? P.hf[0].R : 0), lf_near);
+                    std::max(Rlf, e_top >= 0 ? P.hf[0].R : 0), lf_near, row_tiles(Rlf), max_k);
     // adaptive levels below D.  LF-M2M: a group per split box of level l - 1
     // (written at its LF vector through up_dst), a term per child.  Downward: a
     // group per box of level l: its M2L pairs (kind 0, sources at their LF
@@ -1251,7 +1216,7 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
       const auto& Lc = T.lv[size_t(D + k)];
       std::vector<SlotTerm> up_t;
       std::vector<int32_t> up_dst;
-      std::vector<int64_t> up_near, dn_near;
+      std::vector<NearKey> up_near, dn_near;
       for (size_t p = 0; p < AL.box[size_t(k - 1)].size(); ++p) {
         if (!AL.split[size_t(k - 1)][p]) continue;
         const int32_t g = int32_t(up_dst.size());
@@ -1264,9 +1229,8 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
       Q.nsplit = int64_t(up_dst.size());
       SlotKind uk[2] = {{&Q.m2m, 1}, {nullptr, 1}};
       build_slot_gemm(Q.up, Rlf, Q.nsplit, std::vector<int32_t>(up_dst.size(), pad8(lsk[size_t(k - 1)]->r)), up_t,
-                      uk, Rlf, up_near);
+                      uk, Rlf, up_near, row_tiles(Rlf), max_k, &up_dst);
       Q.up_dst.upload(up_dst);
-      Q.up_dst_h = up_dst;
       std::vector<SlotTerm> dn_t;
       for (const SlotTerm& t : deep_m2l_terms[size_t(k)])
         dn_t.push_back({t.dst, t.op, int32_t(Q.base + t.src), 0});
@@ -1275,7 +1239,8 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
                         int32_t(AL.base[size_t(k - 1)] + AL.par[size_t(k)][size_t(b)]), 1});
       SlotKind dk[2] = {{&Q.m2l, 1}, {&Q.l2l, 1}};
       for (int64_t b = 0; b < Q.nb; ++b) dn_near.push_back(near_key(0, D + k, AL.box[size_t(k)][size_t(b)], true));
-      build_slot_gemm(Q.down, Rlf, Q.nb, std::vector<int32_t>(size_t(Q.nb), pad8(Q.r)), dn_t, dk, Rlf, dn_near);
+      build_slot_gemm(Q.down, Rlf, Q.nb, std::vector<int32_t>(size_t(Q.nb), pad8(Q.r)), dn_t, dk, Rlf, dn_near,
+                      row_tiles(Rlf), max_k);
       for (const SlotTerm& t : up_t) info.flops_m2m += Q.m2m.opflops[size_t(t.op)];
       for (int64_t b = 0; b < Q.nb; ++b) info.flops_l2l += Q.l2l.opflops[0];
     }
