@@ -129,7 +129,9 @@ typedef struct {
 /* Arithmetic of the translation GEMMs (M2M, M2L, L2L) of a plan.  FP32: float32
  * products, each factor the exact sum of three bfloat16 parts and six products of
  * parts on the 16-bit MFMA (the dropped ones are below 2^-24 of the product), float32
- * accumulation.  FP16X3 / BF16X3: every operator entry a and vector entry x is split into
+ * accumulation.  The range stays float32's: a right-hand side whose densities are all
+ * below 2^-63 goes through the translations times 2^64 (in every float32 plan); only
+ * check potentials within 2^-9 of the largest float32 overflow earlier.  FP16X3 / BF16X3: every operator entry a and vector entry x is split into
  * a hi and a lo part of the 16-bit type (a = a_hi + a_lo to 22 resp. 16 bits)
  * and a x is formed as a_hi x_hi + a_hi x_lo + a_lo x_hi on the 16-bit MFMA with
  * float32 accumulation.  FP16X3 scales each operator (at plan time) and each
@@ -252,8 +254,8 @@ int dfmm_apply_ws(dfmm_plan_t plan, const void* f, void* u, int nrhs, void* ws, 
  * returns DFMM_EINVAL.  The launch shapes come from an earlier dfmm_apply (or
  * dfmm_apply_ws / dfmm_apply_batch) with the same nrhs on this plan; without one
  * the call returns DFMM_EINVAL.  Everything runs on `stream`.  Every call on one
- * GPU uses that GPU's array, which keeps the last call's contents (no apply
- * reads workspace memory it has not written): calls that overlap on one GPU --
+ * GPU uses that GPU's array, which keeps the last call's contents (no result
+ * depends on what a workspace held before): calls that overlap on one GPU --
  * on different streams, from different threads or plans -- race, so the caller
  * serializes them.  f, u, nrhs, layout and stream as for dfmm_apply. */
 #define DFMM_NOALLOC_MAX_BYTES (64u << 20)

@@ -78,14 +78,45 @@ __device__ __forceinline__ int req_of(const ReqTable& R, int k) {
   return r;
 }
 
+// ---- small densities ----------------------------------------------------------
+// The GEMMs hold a float32 as three bfloat16 parts, the last of which is a normal
+// number down to about 2^-102 only.  A right-hand side without a density from 2^-63
+// up (in |Re| or |Im|) goes through the translations times 2^64: S2M scales its check
+// potentials up and L2T the potentials down again, so that small densities keep the
+// bits that float32 products give them (without it: 2.9e-4 relative error at densities
+// of 2^-124, against 5.8e-7; 2.0e-6 at 2^-118 in a plan for 1e-6).  The near field is
+// not scaled.  The permutation marks the right-hand sides with an ordinary density in
+// `seen`; the first leaf's S2M hands what it found there to L2T in `lift`, and L2T clears
+// `seen` for the next apply.  Whatever a fresh workspace holds counts as not seen
+// (but for 64 bits that happen to be the mark).
+constexpr unsigned long long kSeen = 0x9E3779B97F4A7C15ull;
+struct LiftArgs {
+  unsigned long long* seen;
+  int* lift;
+};
+__device__ __forceinline__ bool ordinary(float2 v) {  // exponent field 64 or more, not finite ones too
+  return ((__float_as_uint(v.x) | __float_as_uint(v.y)) & 0x60000000u) != 0;
+}
+__device__ __forceinline__ float s2m_scale(const LiftArgs& a, int k) { return a.seen[k] == kSeen ? 1.0f : 0x1p64f; }
+__device__ __forceinline__ double l2t_scale(const LiftArgs& a, int k) { return a.lift[k] ? 0x1p-64 : 1.0; }
+// by all threads of the first workgroup of S2M / of L2T
+__device__ __forceinline__ void set_lift(const LiftArgs& a, int nrhs) {
+  for (int k = threadIdx.x; k < nrhs; k += blockDim.x) a.lift[k] = a.seen[k] != kSeen;
+}
+__device__ __forceinline__ void clear_seen(const LiftArgs& a, int nrhs) {
+  for (int k = threadIdx.x; k < nrhs; k += blockDim.x) a.seen[k] = 0;
+}
+
 __global__ void k_permute_in(const ReqTable R, float2* __restrict__ fs, const int* __restrict__ perm, int64_t N,
-                             int nrhs) {
+                             int nrhs, const LiftArgs la) {
   int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= N * nrhs) return;
   int64_t s = i / nrhs;
   int k = int(i % nrhs);
   const int r = req_of(R, k);
-  fs[i] = R.f[r][int64_t(k - R.k0[r]) * N + perm[s]];
+  const float2 v = R.f[r][int64_t(k - R.k0[r]) * N + perm[s]];
+  fs[i] = v;
+  if (ordinary(v)) la.seen[k] = kSeen;
 }
 
 // Many right-hand sides: the permutation through a tile in LDS of PT_P points,
@@ -95,7 +126,8 @@ __global__ void k_permute_in(const ReqTable R, float2* __restrict__ fs, const in
 // index to its tree position.
 constexpr int PT_P = 64, PT_C = 32, PT_BS = 256;
 __global__ void __launch_bounds__(PT_BS) k_permute_in_tile(const ReqTable R, float2* __restrict__ fs,
-                                                           const int* __restrict__ iperm, int64_t N, int nrhs) {
+                                                           const int* __restrict__ iperm, int64_t N, int nrhs,
+                                                           const LiftArgs la) {
   __shared__ float2 t[PT_C][PT_P + 1];
   const int64_t i0 = int64_t(blockIdx.x) * PT_P;
   const int c0 = int(blockIdx.y) * PT_C;
@@ -106,7 +138,9 @@ __global__ void __launch_bounds__(PT_BS) k_permute_in_tile(const ReqTable R, flo
     for (int c = int(threadIdx.x) / PT_P; c < nc; c += PT_BS / PT_P) {
       const int k = c0 + c;
       const int r = req_of(R, k);
-      t[c][p] = R.f[r][int64_t(k - R.k0[r]) * N + i0 + p];
+      const float2 v = R.f[r][int64_t(k - R.k0[r]) * N + i0 + p];
+      t[c][p] = v;
+      if (ordinary(v)) la.seen[k] = kSeen;
     }
   __syncthreads();
   for (int e = threadIdx.x; e < np * PT_C; e += PT_BS) {
@@ -205,7 +239,9 @@ constexpr int S2M_BS = 128;
 template <int RC>  // right-hand sides per pass
 __global__ void __launch_bounds__(S2M_BS) k_s2m(const int* __restrict__ lstart, const float2* __restrict__ V,
                                                  const float2* __restrict__ fs, int R, int nrhs,
-                                                 const int* __restrict__ gid, float2* __restrict__ clf) {
+                                                 const int* __restrict__ gid, const LiftArgs la,
+                                                 float2* __restrict__ clf) {
+  if (blockIdx.x == 0) set_lift(la, nrhs);
   constexpr int SU = RC <= 8 ? 4 : 1;  // sources per loaded batch
   const int b = blockIdx.x;
   const int bo = gid ? gid[b] : b;  // the leaf's LF vector (adaptive trees)
@@ -235,7 +271,10 @@ __global__ void __launch_bounds__(S2M_BS) k_s2m(const int* __restrict__ lstart, 
       }
 #pragma unroll
       for (int k = 0; k < RC; ++k)
-        if (k < nk) clf[(int64_t(bo) * nrhs + k0 + k) * R + p] = acc[k];
+        if (k < nk) {
+          const float sc = s2m_scale(la, k0 + k);
+          clf[(int64_t(bo) * nrhs + k0 + k) * R + p] = make_float2(acc[k].x * sc, acc[k].y * sc);
+        }
     }
   }
 }
@@ -254,9 +293,11 @@ template <int NCT>
 __global__ void __launch_bounds__(64 * S2M_MT_NW) k_s2m_mfma(const int* __restrict__ lstart,
                                                              const float2* __restrict__ V,
                                                              const float2* __restrict__ fs, int R, int nrhs,
-                                                             const int* __restrict__ gid, float2* __restrict__ clf) {
+                                                             const int* __restrict__ gid, const LiftArgs la,
+                                                             float2* __restrict__ clf) {
   constexpr int NCOL = 16 * NCT;
   extern __shared__ float2 fsh[];  // [point (even count)][NCOL]
+  if (blockIdx.x == 0 && blockIdx.y == 0) set_lift(la, nrhs);
   const int b = blockIdx.x;
   const int bo = gid ? gid[b] : b;  // the leaf's LF vector (adaptive trees)
   const int c0 = int(blockIdx.y) * NCOL;
@@ -277,6 +318,9 @@ __global__ void __launch_bounds__(64 * S2M_MT_NW) k_s2m_mfma(const int* __restri
   const int comp = (rodd ? 1 : 0) ^ kp;
   const unsigned neg = (!rodd && kp) ? 0x80000000u : 0u;
   const float* fb = reinterpret_cast<const float*>(fsh + (kr >> 1) * NCOL + jr) + kp;
+  float sc[NCT];
+#pragma unroll
+  for (int c = 0; c < NCT; ++c) sc[c] = c * 16 + jr < nc ? s2m_scale(la, c0 + c * 16 + jr) : 1.0f;
   for (int m = w; m < R / 8; m += S2M_MT_NW) {
     const int p = m * 8 + (jr >> 1);  // this lane's row (complex)
     v4f acc[NCT];
@@ -300,7 +344,8 @@ __global__ void __launch_bounds__(64 * S2M_MT_NW) k_s2m_mfma(const int* __restri
       if (col >= nc) continue;
 #pragma unroll
       for (int h = 0; h < 2; ++h)
-        clf[(int64_t(bo) * nrhs + c0 + col) * R + m * 8 + 2 * kr + h] = make_float2(acc[c][2 * h], acc[c][2 * h + 1]);
+        clf[(int64_t(bo) * nrhs + c0 + col) * R + m * 8 + 2 * kr + h] =
+            make_float2(acc[c][2 * h] * sc[c], acc[c][2 * h + 1] * sc[c]);
     }
   }
 }
@@ -1266,7 +1311,8 @@ constexpr int L2T_QMAX = 16;  // W values per lane: R <= 16 * L2T_QMAX
 __global__ void __launch_bounds__(L2T_BS) k_l2t(const float2* __restrict__ W, const float2* __restrict__ ulf,
                                                  const int* __restrict__ leaf_of, const double2* __restrict__ unear,
                                                  const int* __restrict__ perm, int R, int nrhs, int64_t N,
-                                                 const ReqTable Q) {
+                                                 const LiftArgs la, const ReqTable Q) {
+  if (blockIdx.x == 0) clear_seen(la, nrhs);
   const int64_t t = (int64_t(blockIdx.x) * L2T_BS + threadIdx.x) >> 4;
   const int l = threadIdx.x & 15;
   const bool act = t < N;
@@ -1292,7 +1338,9 @@ __global__ void __launch_bounds__(L2T_BS) k_l2t(const float2* __restrict__ W, co
     if (act && l == 0) {
       const double2 nf = unear[int64_t(k) * N + tt];
       const int r = req_of(Q, k);
-      Q.u[r][int64_t(k - Q.k0[r]) * N + o] = make_float2(float(double(acc.x) + nf.x), float(double(acc.y) + nf.y));
+      const double sc = l2t_scale(la, k);
+      Q.u[r][int64_t(k - Q.k0[r]) * N + o] =
+          make_float2(float(double(acc.x) * sc + nf.x), float(double(acc.y) * sc + nf.y));
     }
   }
 }
@@ -1305,8 +1353,9 @@ __global__ void __launch_bounds__(L2T_BS) k_l2t_leaf(const float2* __restrict__ 
                                                       const int* __restrict__ lstart, const int* __restrict__ gid,
                                                       const double2* __restrict__ unear,
                                                       const int* __restrict__ perm, int R, int nrhs, int kc,
-                                                      int64_t N, const ReqTable Q) {
+                                                      int64_t N, const LiftArgs la, const ReqTable Q) {
   extern __shared__ float2 us[];  // [kc][R]
+  if (blockIdx.x == 0) clear_seen(la, nrhs);
   const int b = blockIdx.x;
   const int bo = gid ? gid[b] : b;  // the leaf's LF vector (adaptive trees)
   const int s0 = lstart[b], s1 = lstart[b + 1];
@@ -1339,7 +1388,9 @@ __global__ void __launch_bounds__(L2T_BS) k_l2t_leaf(const float2* __restrict__ 
           const int kk = k0 + k;
           const double2 nf = unear[int64_t(kk) * N + t];
           const int r = req_of(Q, kk);
-          Q.u[r][int64_t(kk - Q.k0[r]) * N + o] = make_float2(float(double(acc.x) + nf.x), float(double(acc.y) + nf.y));
+          const double sc = l2t_scale(la, kk);
+          Q.u[r][int64_t(kk - Q.k0[r]) * N + o] =
+              make_float2(float(double(acc.x) * sc + nf.x), float(double(acc.y) * sc + nf.y));
         }
       }
     }
@@ -1367,9 +1418,11 @@ __global__ void __launch_bounds__(64 * L2T_MT_NW) k_l2t_mfma(const float2* __res
                                                              const int* __restrict__ lstart,
                                                              const int* __restrict__ gid,
                                                              const double2* __restrict__ unear, int R, int RS,
-                                                             int nrhs, int64_t N, float2* __restrict__ ut) {
+                                                             int nrhs, int64_t N, const LiftArgs la,
+                                                             float2* __restrict__ ut) {
   constexpr int NCOL = 16 * NCT;
   extern __shared__ float2 us[];  // [NCOL][RS]: the leaf's incoming potentials of this block's columns
+  if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) clear_seen(la, nrhs);
   const int b = blockIdx.x;
   const int bo = gid ? gid[b] : b;  // the leaf's LF vector (adaptive trees)
   const int c0 = int(blockIdx.y) * NCOL;
@@ -1414,13 +1467,14 @@ __global__ void __launch_bounds__(64 * L2T_MT_NW) k_l2t_mfma(const float2* __res
     for (int c = 0; c < NCT; ++c) {
       const int col = c0 + c * 16 + j;
       if (col >= nrhs) continue;
+      const double sc = l2t_scale(la, col);
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const int tt = s0 + rt * 8 + 2 * kr + h;
         if (tt < s1) {
           const double2 nf = unear[int64_t(col) * N + tt];
           ut[int64_t(tt) * nrhs + col] =
-              make_float2(float(double(acc[c][2 * h]) + nf.x), float(double(acc[c][2 * h + 1]) + nf.y));
+              make_float2(float(double(acc[c][2 * h]) * sc + nf.x), float(double(acc[c][2 * h + 1]) * sc + nf.y));
         }
       }
     }
@@ -1537,7 +1591,7 @@ struct WsPtr {
 };
 // The buffers of one apply, carved out of a workspace by ws_layout.
 struct Ws {
-  WsPtr fs, unear, flf, ulf, Y;
+  WsPtr fs, unear, flf, ulf, Y, seen, lift;
   std::vector<WsPtr> F, U;  // per HF level
 };
 
@@ -1943,6 +1997,8 @@ static Ws carve(const WsLayout& L, void* base) {
   W.flf.p = b + L.flf;
   W.ulf.p = b + L.ulf;
   W.Y.p = b + L.Y;
+  W.seen.p = b + L.seen;
+  W.lift.p = b + L.lift;
   for (size_t o : L.F) W.F.push_back(WsPtr{b + o});
   for (size_t o : L.U) W.U.push_back(WsPtr{b + o});
   return W;
@@ -2231,15 +2287,16 @@ void run_apply(dfmm_plan_s& P, const ReqTable& R, int nrhs, hipStream_t st, void
   auto mark = [&](int stage) {
     if (tm) tm->mark(stage, st);
   };
+  const LiftArgs la{S.seen.as<unsigned long long>(), S.lift.as<int>()};
   // the tiled permutations pay from 16 rhs; the L2T of as many writes tree order
   const bool tiled = nrhs >= 16;
   const dim3 pt_grid(nblocks(N, PT_P), unsigned((nrhs + PT_C - 1) / PT_C));
   if (tiled)
     hipLaunchKernelGGL(k_permute_in_tile, pt_grid, dim3(PT_BS), 0, st, R, S.fs.as<float2>(), P.iperm_d.as<int>(), N,
-                       nrhs);
+                       nrhs, la);
   else
     hipLaunchKernelGGL(k_permute_in, dim3(nblocks(N * nrhs, 256)), dim3(256), 0, st, R, S.fs.as<float2>(),
-                       P.perm_d.as<int>(), N, nrhs);
+                       P.perm_d.as<int>(), N, nrhs, la);
   mark(ST_PERMUTE);
   // the near field needs only the permuted densities: it runs on the plan's
   // second stream while the far-field passes run on st (on st itself when the
@@ -2285,19 +2342,19 @@ void run_apply(dfmm_plan_s& P, const ReqTable& R, int nrhs, hipStream_t st, void
   }
   if (nrhs == 1)
     hipLaunchKernelGGL(k_s2m<1>, dim3(unsigned(nleaf)), dim3(S2M_BS), 0, st, P.leaf_start.as<int>(),
-                       P.lf.V.as<float2>(), S.fs.as<float2>(), Rl, nrhs, gid, S.flf.as<float2>());
+                       P.lf.V.as<float2>(), S.fs.as<float2>(), Rl, nrhs, gid, la, S.flf.as<float2>());
   else if (nrhs < 24)
     hipLaunchKernelGGL(k_s2m<8>, dim3(unsigned(nleaf)), dim3(S2M_BS), 0, st, P.leaf_start.as<int>(),
-                       P.lf.V.as<float2>(), S.fs.as<float2>(), Rl, nrhs, gid, S.flf.as<float2>());
+                       P.lf.V.as<float2>(), S.fs.as<float2>(), Rl, nrhs, gid, la, S.flf.as<float2>());
   else if (size_t(P.max_leaf_pts + 1) * 32 * sizeof(float2) > size_t(kGgDynLds) || Rl % 8 != 0)
     // one pass over the weights for up to 32 right-hand sides
     hipLaunchKernelGGL(k_s2m<32>, dim3(unsigned(nleaf)), dim3(S2M_BS), 0, st, P.leaf_start.as<int>(),
-                       P.lf.V.as<float2>(), S.fs.as<float2>(), Rl, nrhs, gid, S.flf.as<float2>());
+                       P.lf.V.as<float2>(), S.fs.as<float2>(), Rl, nrhs, gid, la, S.flf.as<float2>());
   else {  // k_s2m_mfma: the leaf's densities of 32 columns in LDS
     const size_t lds = sizeof(float2) * size_t(32) * size_t((P.max_leaf_pts + 1) & ~1);
     ensure_lds_limit(reinterpret_cast<const void*>(&k_s2m_mfma<2>));
     hipLaunchKernelGGL(k_s2m_mfma<2>, dim3(unsigned(nleaf), unsigned((nrhs + 31) / 32)), dim3(64 * S2M_MT_NW),
-                       lds, st, P.leaf_start.as<int>(), P.lf.V.as<float2>(), S.fs.as<float2>(), Rl, nrhs, gid,
+                       lds, st, P.leaf_start.as<int>(), P.lf.V.as<float2>(), S.fs.as<float2>(), Rl, nrhs, gid, la,
                        S.flf.as<float2>());
   }
   mark(ST_S2M);
@@ -2445,18 +2502,19 @@ void run_apply(dfmm_plan_s& P, const ReqTable& R, int nrhs, hipStream_t st, void
     // the potentials in tree order go to fs: the densities there are dead once
     // S2M and the near field (joined above) have run
     hipLaunchKernelGGL(kern, grid, dim3(64 * L2T_MT_NW), lds, st, P.lf.W.as<float2>(), S.ulf.as<float2>(),
-                       P.leaf_start.as<int>(), gid, S.unear.as<double2>(), Rl, RS, nrhs, N, S.fs.as<float2>());
+                       P.leaf_start.as<int>(), gid, S.unear.as<double2>(), Rl, RS, nrhs, N, la,
+                       S.fs.as<float2>());
     hipLaunchKernelGGL(k_permute_out_tile, pt_grid, dim3(PT_BS), 0, st, R, S.fs.as<const float2>(),
                        P.iperm_d.as<int>(), N, nrhs);
   } else if (nrhs >= 4) {
     const int kc = std::min(nrhs, std::max(1, int((48 << 10) / (sizeof(float2) * Rl))));
     hipLaunchKernelGGL(k_l2t_leaf, dim3(unsigned(nleaf)), dim3(L2T_BS), sizeof(float2) * size_t(kc) * Rl, st,
                        P.lf.W.as<float2>(), S.ulf.as<float2>(), P.leaf_start.as<int>(), gid, S.unear.as<double2>(),
-                       P.perm_d.as<int>(), Rl, nrhs, kc, N, R);
+                       P.perm_d.as<int>(), Rl, nrhs, kc, N, la, R);
   } else {
     hipLaunchKernelGGL(k_l2t, dim3(nblocks(N * 16, L2T_BS)), dim3(L2T_BS), 0, st, P.lf.W.as<float2>(),
                        S.ulf.as<float2>(), P.leaf_of.as<int>(), S.unear.as<double2>(), P.perm_d.as<int>(), Rl, nrhs,
-                       N, R);
+                       N, la, R);
   }
   mark(ST_LEAF);
   DFMM_HIP(hipGetLastError());

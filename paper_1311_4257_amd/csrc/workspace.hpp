@@ -29,8 +29,11 @@ struct WsShape {
 //   F[e]   complex [nout][nrhs][R]    HF outgoing check potentials of level e
 //   U[e]   complex [nin][nrhs][R]     HF incoming check potentials of level e
 //   Y      complex64 [pair_rows][nrhs]   pair outputs (pair form only; else empty)
+//   seen   uint64 [nrhs]              float32 plans: right-hand sides with a density of
+//                                     ordinary size
+//   lift   int32 [nrhs]               float32 plans: right-hand sides scaled up
 struct WsLayout {
-  size_t fs = 0, unear = 0, flf = 0, ulf = 0, Y = 0;
+  size_t fs = 0, unear = 0, flf = 0, ulf = 0, Y = 0, seen = 0, lift = 0;
   std::vector<size_t> F, U;
   size_t total = 0;
 };
@@ -73,6 +76,10 @@ inline WsLayout ws_layout(const WsShape& s, int nrhs, bool pair_form, int csize 
     L.U.push_back(take(ws_mul(r, size_t(s.nin[e] > 0 ? s.nin[e] : 1))));
   }
   L.Y = take(pair_form ? ws_mul(ws_mul(8, size_t(s.pair_rows > 0 ? s.pair_rows : 1)), k) : 0);
+  if (csize == 8) {
+    L.seen = take(ws_mul(12, k));
+    L.lift = L.seen + 8 * k;
+  }
   L.total = off > 0 ? off : kWsAlign;
   return L;
 }
