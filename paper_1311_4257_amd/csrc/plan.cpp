@@ -2,17 +2,16 @@
 // translation tables (Section 2.2, Algorithm 1), resident on the device.
 #include <algorithm>
 #include <array>
-#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstring>
 #include <map>
 #include <set>
-#include <thread>
 #include <tuple>
 
 #include "geometry.hpp"
 #include "internal.hpp"
+#include "parallel.hpp"
 
 namespace dfmm {
 
@@ -20,24 +19,6 @@ void build_tree_device(dfmm_plan_s& P, const double* points, int64_t N, double K
                        int extra);
 
 namespace {
-
-template <class F>
-void parallel_for(int64_t n, F&& fn) {
-  unsigned hc = std::thread::hardware_concurrency();
-  int64_t nt = std::max<int64_t>(1, std::min<int64_t>(hc ? hc : 1, 16));
-  nt = std::min<int64_t>(nt, n);
-  if (nt <= 1) {
-    for (int64_t i = 0; i < n; ++i) fn(i);
-    return;
-  }
-  std::atomic<int64_t> next{0};
-  std::vector<std::thread> th;
-  for (int64_t t = 0; t < nt; ++t)
-    th.emplace_back([&]() {
-      for (int64_t i = next++; i < n; i = next++) fn(i);
-    });
-  for (auto& x : th) x.join();
-}
 
 // G(x, y) in float64 (zero at coincidence).
 inline void green64(double dx, double dy, double dz, double* re, double* im) {

@@ -20,16 +20,15 @@
 // boxes plus the shifted check points of the six width-1 wedges.  Widths are
 // built from w_hi downwards.
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <string>
-#include <thread>
 #include <vector>
 
 #include "geometry.hpp"
 #include "internal.hpp"
+#include "parallel.hpp"
 
 namespace dfmm {
 
@@ -413,20 +412,6 @@ void add_inherited(const Skel& parent, double w, std::vector<double>& out) {
     for (int p = 0; p < parent.r; ++p)
       for (int t = 0; t < 3; ++t) out.push_back(parent.a[3 * p + t] - d[t]);
   }
-}
-
-template <class F>
-void parallel_for(int n, F&& fn) {
-  unsigned hc = std::thread::hardware_concurrency();
-  int nt = int(std::max(1u, std::min(hc ? hc : 1u, 16u)));
-  nt = std::min(nt, n);
-  std::atomic<int> next{0};
-  std::vector<std::thread> th;
-  for (int t = 0; t < nt; ++t)
-    th.emplace_back([&]() {
-      for (int i = next++; i < n; i = next++) fn(i);
-    });
-  for (auto& x : th) x.join();
 }
 
 }  // namespace
