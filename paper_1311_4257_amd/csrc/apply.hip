@@ -1769,7 +1769,7 @@ static bool prepare_slot(SlotLaunch& L, const SlotGemm& S, int nrhs, int nt) {
   const int nMall = std::max(1, (S.M + 15) / 16);
   L.slices = (nMall + SLOT_MAXW - 1) / SLOT_MAXW;
   L.waves = (nMall + L.slices - 1) / L.slices;
-  return !S.split2 && slot_lds_bytes(S, nt) <= size_t(kGgDynLds);
+  return slot_lds_bytes(S, nt) <= size_t(kGgDynLds);
 }
 
 // The slot form serves fast float32 plans where it pays (DFMM_SLOT=0 forces the

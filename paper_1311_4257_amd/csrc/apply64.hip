@@ -457,7 +457,7 @@ void launch_slot64_t(const SlotGemm& S, const Slot64Args& a, int nrhs, double2* 
 void launch_slot64(const SlotGemm& S, const double4* A0, const double2* X0, int KX0, const double4* A1,
                    const double2* X1, int KX1, int nrhs, double2* Y, hipStream_t st) {
   if (S.ngroups == 0) return;
-  if (S.split2 || S.Kmax % 8 != 0) throw Error{DFMM_EUNSUPPORTED, "float64 slot GEMM: bad operator packing"};
+  if (S.Kmax % 8 != 0) throw Error{DFMM_EUNSUPPORTED, "float64 slot GEMM: bad operator packing"};
   const int cpg = (nrhs + 15) / 16;
   Slot64Args a{S.order.as<int>(), S.t0.as<int>(), S.gm.as<int>(), S.terms.as<int4>(), A0, A1 ? A1 : A0, X0,
                X1 ? X1 : X0, KX0, X1 ? KX1 : KX0, S.M, cpg, S.Kmax / 2 + 1};

@@ -146,11 +146,8 @@ constexpr int kTileMaxK = 128, kTile64MaxK = 256;  // columns of an operator in 
 struct SlotGemm {
   int M = 0;                 // row stride of the output vectors (padded rank)
   int Kmax = 8;              // largest packed K of any term (LDS column length)
-  int KXmax = 8;             // largest row stride of the source vectors (set by the plan)
-  bool split2 = false;       // some term has split operators (not handled by the slot kernel)
   int64_t ngroups = 0, nterms = 0;
   int max_terms = 0;
-  double flops[2] = {0, 0};  // 8 r_dst r_src per term and rhs by kind (unpadded ranks)
   DevBuf order;              // int32[ngroups]: launch order, groups with more terms first
   DevBuf t0;                 // int32[ngroups + 1]: term range of each group
   DevBuf gm;                 // int32[ngroups]: padded rows M_g of the group's operators
@@ -173,17 +170,13 @@ struct SlotGemm {
 // A group's place among the tiles: its class (groups of one class have many
 // operators in common) << 32 | its order in it.
 using NearKey = int64_t;
-// Host view of one kind's operators: float4 offset and packed K (split doubling
-// included) of every operator index, and the split factor.
-struct SlotKind {
-  const GGemm* G = nullptr;  // aoff_h, kpk_h and opflops of the operators (null: no terms of this kind)
-  int split = 1;
-};
-// Term lists -> device tables; terms of a group keep the order given.  near: the
+// Term lists -> device tables; terms of a group keep the order given.  kinds: the
+// operators of each kind (null: no terms of it; one plane set, split = 1).  near: the
 // groups' keys (empty: no tiles); row_tiles, max_k: row tiles (waves) of a tile and
-// largest K in the kernel that uses them; gdst: output vector of each group (null: its own index).
+// largest K in the kernel that uses them; gdst: output vector of each group (null: its
+// own index).
 void build_slot_gemm(SlotGemm& S, int M, int64_t ngroups, const std::vector<int32_t>& gM,
-                     const std::vector<SlotTerm>& terms, const SlotKind kinds[2], int kx_max,
+                     const std::vector<SlotTerm>& terms, const GGemm* const kinds[2],
                      const std::vector<NearKey>& near, int row_tiles, int max_k,
                      const std::vector<int32_t>* gdst = nullptr);
 
@@ -241,7 +234,6 @@ struct LFDeep {
   GGemm m2l;                 // LF-M2L operators, one per offset
   GGemm m2m;                 // 8 octant operators G(a_P - delta_o, b_C) D_C: parent <- child
   GGemm l2l;                 // 8 octant operators G(b_C + delta_o, a_P) D_P^T: child <- parent
-  DevBuf red_start, red_idx; // pair-form CSR of the M2L (built with the operators, unused)
   SlotGemm up;               // LF-M2M: the split boxes of level l - 1 <- their children
   DevBuf up_dst;             // int32[nsplit]: LF vector index of each of those parents
   SlotGemm down;             // LF-M2L pairs + LF-L2L term of every box of this level

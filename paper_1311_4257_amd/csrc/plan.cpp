@@ -361,14 +361,11 @@ static void build_cuts(SlotGemm& S, const std::vector<int32_t>& gM, const std::v
 }
 
 void build_slot_gemm(SlotGemm& S, int M, int64_t ngroups, const std::vector<int32_t>& gM,
-                     const std::vector<SlotTerm>& terms, const SlotKind kinds[2], int kx_max,
+                     const std::vector<SlotTerm>& terms, const GGemm* const kinds[2],
                      const std::vector<NearKey>& near, int row_tiles, int max_k, const std::vector<int32_t>* gdst) {
   S.M = M;
-  S.KXmax = kx_max;
-  S.split2 = false;
   S.ngroups = ngroups;
   S.nterms = int64_t(terms.size());
-  S.flops[0] = S.flops[1] = 0.0;
   // terms grouped by destination, each group in the order given
   std::vector<int32_t> cnt(size_t(ngroups) + 1, 0);
   for (const SlotTerm& t : terms) {
@@ -379,11 +376,11 @@ void build_slot_gemm(SlotGemm& S, int M, int64_t ngroups, const std::vector<int3
   std::vector<int32_t> pos(cnt.begin(), cnt.end() - 1), tab(size_t(4) * terms.size()), op(terms.size());
   int kmax = 8;
   for (const SlotTerm& t : terms) {
-    const SlotKind& k = kinds[t.kind];
-    if (!k.G) throw Error{DFMM_EINVAL, "slot term of a kind without operators"};
-    const int64_t aoff = k.G->aoff_h[size_t(t.op)];
-    const int kp = k.G->kpk_h[size_t(t.op)];
-    if (aoff > INT32_MAX || kp >= (1 << 12) || kp < 8 || kp % 8 != 0 || k.split > 3)
+    const GGemm* k = kinds[t.kind];
+    if (!k) throw Error{DFMM_EINVAL, "slot term of a kind without operators"};
+    const int64_t aoff = k->aoff_h[size_t(t.op)];
+    const int kp = k->kpk_h[size_t(t.op)];
+    if (aoff > INT32_MAX || kp >= (1 << 12) || kp < 8 || kp % 8 != 0)
       throw Error{DFMM_EUNSUPPORTED, "operator table too large for the slot-form GEMM"};
     const size_t at = size_t(pos[size_t(t.dst)]++);
     op[at] = t.op;
@@ -393,8 +390,6 @@ void build_slot_gemm(SlotGemm& S, int M, int64_t ngroups, const std::vector<int3
     e[2] = t.src;
     e[3] = 0;
     kmax = std::max(kmax, kp);
-    S.split2 = S.split2 || k.split != 1;
-    S.flops[t.kind] += k.G->opflops[size_t(t.op)];
   }
   S.Kmax = kmax;
   S.max_terms = 0;
@@ -431,8 +426,7 @@ size_t plan_device_bytes(const dfmm_plan_s& P) {
          H.l2l_ri.bytes + H.red_start.bytes + H.red_idx.bytes + slot_bytes(H.up) + slot_bytes(H.down);
   b += P.leaf_gid.bytes;
   for (const LFDeep& Q : P.lfd)
-    b += gg_bytes(Q.m2l) + gg_bytes(Q.m2m) + gg_bytes(Q.l2l) + Q.red_start.bytes + Q.red_idx.bytes +
-         slot_bytes(Q.up) + slot_bytes(Q.down) + Q.up_dst.bytes;
+    b += gg_bytes(Q.m2l) + gg_bytes(Q.m2m) + gg_bytes(Q.l2l) + slot_bytes(Q.up) + slot_bytes(Q.down) + Q.up_dst.bytes;
   return b;
 }
 
@@ -726,7 +720,7 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
   // incoming check potentials of B); the pair outputs are summed per in-slot.
   auto build_m2l = [&](const std::vector<PairRec>& pr, double w, int R,
                        const std::vector<const Skel*>& skin, const SlotIndex* osl, const SlotIndex* isl,
-                       int64_t nin, GGemm& G, DevBuf& rs, DevBuf& ri, int64_t& ngroups, double& flops,
+                       int64_t nin, GGemm& G, DevBuf* rs, DevBuf* ri, int64_t& ngroups, double& flops,
                        int split, std::vector<SlotTerm>& sterms) {
     // algorithmic bytes: each group's operator once (complex64, unpadded), each
     // source slot read once and each target slot read and written once, per rhs
@@ -830,8 +824,8 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
       const PairRec& r = pr[rep[gi]];
       G.opflops[size_t(gi)] = 8.0 * skin[r.din < 0 ? 0 : r.din]->r * skin[r.dout < 0 ? 0 : r.dout]->r;
     }
-    rs.upload(rstart);
-    ri.upload(ridx);
+    if (rs) rs->upload(rstart);
+    if (ri) ri->upload(ridx);
   };
 
   // slot-form term lists: M2L pairs and L2L terms of the leaves and of every HF level
@@ -840,7 +834,7 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
   {
     std::vector<const Skel*> s1{&sl};
     P.lf.npairs = int64_t(pairs[D].size());
-    build_m2l(pairs[D], 0.5, Rlf, s1, nullptr, nullptr, nD, P.lf.m2l, P.lf.red_start, P.lf.red_idx,
+    build_m2l(pairs[D], 0.5, Rlf, s1, nullptr, nullptr, nD, P.lf.m2l, &P.lf.red_start, &P.lf.red_idx,
               P.lf.ngroups, P.lf.flops, 1, lf_terms);
     info.flops_m2l_lf = P.lf.flops;
     info.flops_m2l_level[D] = P.lf.flops;
@@ -1051,7 +1045,7 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
     // M2L
     std::vector<const Skel*> sp;
     for (auto& s : sk) sp.push_back(&s);
-    build_m2l(pairs[l], double(w), H.R, sp, &OS[l], &IS[l], H.nin, H.m2l, H.red_start, H.red_idx, H.ngroups,
+    build_m2l(pairs[l], double(w), H.R, sp, &OS[l], &IS[l], H.nin, H.m2l, &H.red_start, &H.red_idx, H.ngroups,
               H.flops, hf_split, down_terms[size_t(e)]);
     info.flops_m2l_hf += H.flops;
     info.flops_m2l_level[l] = H.flops;
@@ -1140,14 +1134,14 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
     Q.base = AL.base[size_t(k)];
     Q.npairs = int64_t(dpairs[size_t(k)].size());
     std::vector<const Skel*> s1{&sc};
-    build_m2l(dpairs[size_t(k)], w, Rlf, s1, nullptr, nullptr, Q.nb, Q.m2l, Q.red_start, Q.red_idx, Q.ngroups,
+    build_m2l(dpairs[size_t(k)], w, Rlf, s1, nullptr, nullptr, Q.nb, Q.m2l, nullptr, nullptr, Q.ngroups,
               Q.flops, 1, deep_m2l_terms[size_t(k)]);
     info.flops_m2l_lf += Q.flops;
     if (l < 32) info.flops_m2l_level[l] = Q.flops;
     build_lf_transfer(*lsk[size_t(k - 1)], sc, w, Q.m2m, Q.l2l);
   }
 
-  // ---- slot-form tables (fast float32 plans; used from 16 right-hand sides) -------
+  // ---- slot-form tables (fast float32 plans, float64 plans) --------------------
   if ((!P.precise && P.prec == DFMM_PREC_FP32) || fp64) {
     auto slot_m = [&](int l, int64_t n, bool in) {  // padded rows of each slot's skeleton
       std::vector<int32_t> gm(static_cast<size_t>(n));
@@ -1176,18 +1170,18 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
     for (int e = 0; e <= e_top; ++e) {
       HFLevel& H = P.hf[size_t(e)];
       const int l = H.l;
-      SlotKind up[2] = {{&H.m2m, hf_split}, {nullptr, 1}};
+      const GGemm* up[2] = {&H.m2m, nullptr};
       build_slot_gemm(H.up, H.R, H.nout, slot_m(l, H.nout, false), up_terms[size_t(e)], up,
-                      e == 0 ? Rlf : P.hf[size_t(e - 1)].R, slot_near(l, OS[l].list, false), row_tiles(H.R), max_k);
-      SlotKind dn[2] = {{&H.m2l, hf_split}, {e < e_top ? &P.hf[size_t(e + 1)].l2l : nullptr, hf_split}};
+                      slot_near(l, OS[l].list, false), row_tiles(H.R), max_k);
+      const GGemm* dn[2] = {&H.m2l, e < e_top ? &P.hf[size_t(e + 1)].l2l : nullptr};
       build_slot_gemm(H.down, H.R, H.nin, slot_m(l, H.nin, true), down_terms[size_t(e)], dn,
-                      std::max(H.R, e < e_top ? P.hf[size_t(e + 1)].R : 0), slot_near(l, IS[l].list, true), row_tiles(H.R), max_k);
+                      slot_near(l, IS[l].list, true), row_tiles(H.R), max_k);
     }
     std::vector<NearKey> lf_near;
     for (int64_t b = 0; tiles && b < nD; ++b) lf_near.push_back(near_key(0, D, b, true));
-    SlotKind dn[2] = {{&P.lf.m2l, 1}, {e_top >= 0 ? &P.hf[0].l2l : nullptr, hf_split}};
+    const GGemm* dn[2] = {&P.lf.m2l, e_top >= 0 ? &P.hf[0].l2l : nullptr};
     build_slot_gemm(P.lf.down, Rlf, nD, std::vector<int32_t>(size_t(nD), Rlf), lf_terms, dn,
-                    std::max(Rlf, e_top >= 0 ? P.hf[0].R : 0), lf_near, row_tiles(Rlf), max_k);
+                    lf_near, row_tiles(Rlf), max_k);
     // adaptive levels below D.  LF-M2M: a group per split box of level l - 1
     // (written at its LF vector through up_dst), a term per child.  Downward: a
     // group per box of level l: its M2L pairs (kind 0, sources at their LF
@@ -1208,9 +1202,9 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
                           int32_t(Q.base + c), 0});
       }
       Q.nsplit = int64_t(up_dst.size());
-      SlotKind uk[2] = {{&Q.m2m, 1}, {nullptr, 1}};
+      const GGemm* uk[2] = {&Q.m2m, nullptr};
       build_slot_gemm(Q.up, Rlf, Q.nsplit, std::vector<int32_t>(up_dst.size(), pad8(lsk[size_t(k - 1)]->r)), up_t,
-                      uk, Rlf, up_near, row_tiles(Rlf), max_k, &up_dst);
+                      uk, up_near, row_tiles(Rlf), max_k, &up_dst);
       Q.up_dst.upload(up_dst);
       std::vector<SlotTerm> dn_t;
       for (const SlotTerm& t : deep_m2l_terms[size_t(k)])
@@ -1218,9 +1212,9 @@ void build_plan(dfmm_plan_s& P, const double* points, int64_t N, double K,
       for (int64_t b = 0; b < Q.nb; ++b)
         dn_t.push_back({int32_t(b), int32_t(Lc.octant[size_t(AL.box[size_t(k)][size_t(b)])]),
                         int32_t(AL.base[size_t(k - 1)] + AL.par[size_t(k)][size_t(b)]), 1});
-      SlotKind dk[2] = {{&Q.m2l, 1}, {&Q.l2l, 1}};
+      const GGemm* dk[2] = {&Q.m2l, &Q.l2l};
       for (int64_t b = 0; b < Q.nb; ++b) dn_near.push_back(near_key(0, D + k, AL.box[size_t(k)][size_t(b)], true));
-      build_slot_gemm(Q.down, Rlf, Q.nb, std::vector<int32_t>(size_t(Q.nb), pad8(Q.r)), dn_t, dk, Rlf, dn_near,
+      build_slot_gemm(Q.down, Rlf, Q.nb, std::vector<int32_t>(size_t(Q.nb), pad8(Q.r)), dn_t, dk, dn_near,
                       row_tiles(Rlf), max_k);
       for (const SlotTerm& t : up_t) info.flops_m2m += Q.m2m.opflops[size_t(t.op)];
       for (int64_t b = 0; b < Q.nb; ++b) info.flops_l2l += Q.l2l.opflops[0];
