@@ -53,7 +53,7 @@ PEAK_HBM_GBS = 8000.0
 CACHE_DIR = os.path.join(ROOT, ".dfmm_cache")
 # the M2L launch is defined by the tile engine and the operator layout built at plan time
 GEMM_SOURCES = ["paper_1311_4257_amd/csrc/apply.hip", "paper_1311_4257_amd/csrc/plan.cpp",
-                "paper_1311_4257_amd/csrc/split_mfma.hpp"]
+                "paper_1311_4257_amd/csrc/slot_merge.hpp", "paper_1311_4257_amd/csrc/split_mfma.hpp"]
 CALIB_BYTES = 256 << 20
 # --precision -> (dfmm_options.precision, the dtype reported)
 PRECISIONS = {"fp32": (0, "f32"), "fp16x3": (1, "f16x3 (hi/lo f16 products, f32 sums)"),

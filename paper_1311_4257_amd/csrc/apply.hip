@@ -524,7 +524,8 @@ __device__ __forceinline__ void ggemm_tile(const GgArgs& a, const GgChunk& ch, i
 // The same tile engine under two names, so that kernel traces separate the
 // translations (M2L of Algorithm 1) from the pair-form tree transfers (M2M and L2L).
 constexpr int GG_MINW = 2, GG_MAXW = 8;  // waves per workgroup
-// Waves per SIMD that the registers have to allow: 4 for up to 32 columns.
+// Waves per SIMD that the registers have to allow: 4, with float64 sums 2.  (At 64
+// columns the float32 form keeps two of its 128 registers in scratch.)
 #define DFMM_GG_BOUNDS(NT, OP) __launch_bounds__(64 * GG_MAXW, OP == OP_P4 ? 2 : 4)
 template <int NT, bool ACC64, int OP>
 __global__ void DFMM_GG_BOUNDS(NT, (ACC64 ? OP_P4 : OP)) k_m2l(const GgArgs a, const GgChunk* __restrict__ chunks,
@@ -1655,7 +1656,7 @@ static void prepare_cfg(Launch& L, const GGemm& G, int nrhs, int nt, int slices,
 }
 
 // dynamic LDS limit of the GEMM kernels: 160 KB less 1 KB for their static LDS
-// (the column source table)
+// (the FP16X3 column exponents)
 constexpr int kGgDynLds = 159 * 1024;
 
 // operand form of a launch, and its LDS: nt 16-column tiles in their 16-bit planes
@@ -1668,7 +1669,7 @@ static size_t gg_lds(const GGemm& G, int nt) {
   const int pb = gg_form(G) == OP_F32 || gg_form(G) == OP_P4 ? 3 : 2;
   return size_t(16) * size_t(nt * 16) * size_t(col_units(G.K, pb));
 }
-// 16 columns do not fit LDS (float32 ranks past 846): 8 per chunk
+// 16 columns do not fit LDS (ranks past 832 in three planes): 8 per chunk
 static bool gg_half(const GGemm& G) { return gg_lds(G, 1) > size_t(kGgDynLds); }
 static size_t gg_lds_used(const GGemm& G, int nt) { return nt == 1 && gg_half(G) ? gg_lds(G, 1) / 2 : gg_lds(G, nt); }
 static bool gg_fits(const GGemm& G, int nt) { return gg_lds_used(G, nt) <= size_t(kGgDynLds); }
