@@ -97,8 +97,16 @@ struct LiftArgs {
 __device__ __forceinline__ bool ordinary(float2 v) {  // exponent field 64 or more, not finite ones too
   return ((__float_as_uint(v.x) | __float_as_uint(v.y)) & 0x60000000u) != 0;
 }
-__device__ __forceinline__ float s2m_scale(const LiftArgs& a, int k) { return a.seen[k] == kSeen ? 1.0f : 0x1p64f; }
-__device__ __forceinline__ double l2t_scale(const LiftArgs& a, int k) { return a.lift[k] ? 0x1p-64 : 1.0; }
+// S2M and L2T load the marks first and look at them after their sums: a launch of few
+// leaves is one chain of loads, to which a look at the end adds 1 to 3 us.  (The asm
+// keeps the compiler from looking, and waiting, where it loads.)
+template <class T>
+__device__ __forceinline__ T late(T v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+__device__ __forceinline__ float s2m_scale(unsigned long long seen) { return seen == kSeen ? 1.0f : 0x1p64f; }
+__device__ __forceinline__ double l2t_scale(int lift) { return lift ? 0x1p-64 : 1.0; }
 // by all threads of the first workgroup of S2M / of L2T
 __device__ __forceinline__ void set_lift(const LiftArgs& a, int nrhs) {
   for (int k = threadIdx.x; k < nrhs; k += blockDim.x) a.lift[k] = a.seen[k] != kSeen;
@@ -248,6 +256,10 @@ __global__ void __launch_bounds__(S2M_BS) k_s2m(const int* __restrict__ lstart, 
   const int s0 = lstart[b], s1 = lstart[b + 1];
   for (int k0 = 0; k0 < nrhs; k0 += RC) {
     const int nk = min(RC, nrhs - k0);
+    // marks of the pass, in every RC lanes (R is a multiple of 8: the first 8 of a wave
+    // are at work whenever it is); in passes of 32 one per output
+    const int km = k0 + int(threadIdx.x) % RC;
+    const unsigned long long mark = RC <= 8 && km < nrhs ? la.seen[km] : kSeen;
     for (int p = threadIdx.x; p < R; p += S2M_BS) {
       float2 acc[RC];
 #pragma unroll
@@ -269,10 +281,11 @@ __global__ void __launch_bounds__(S2M_BS) k_s2m(const int* __restrict__ lstart, 
         for (int k = 0; k < RC; ++k)
           if (k < nk) cfma(acc[k], v, fs[int64_t(j) * nrhs + k0 + k]);
       }
+      const unsigned up = unsigned(__ballot(late(mark) != kSeen));
 #pragma unroll
       for (int k = 0; k < RC; ++k)
         if (k < nk) {
-          const float sc = s2m_scale(la, k0 + k);
+          const float sc = RC <= 8 ? (up >> k & 1 ? 0x1p64f : 1.0f) : s2m_scale(la.seen[k0 + k]);
           clf[(int64_t(bo) * nrhs + k0 + k) * R + p] = make_float2(acc[k].x * sc, acc[k].y * sc);
         }
     }
@@ -304,6 +317,12 @@ __global__ void __launch_bounds__(64 * S2M_MT_NW) k_s2m_mfma(const int* __restri
   const int s0 = lstart[b], s1 = lstart[b + 1];
   const int np = s1 - s0, np2 = (np + 1) & ~1;
   const int nc = min(NCOL, nrhs - c0);
+  unsigned long long mark[NCT];  // of the columns that this lane writes
+#pragma unroll
+  for (int c = 0; c < NCT; ++c) {
+    const int col = c * 16 + int(threadIdx.x & 15);
+    mark[c] = col < nc ? la.seen[c0 + col] : kSeen;
+  }
   for (int e = threadIdx.x; e < np2 * NCOL; e += 64 * S2M_MT_NW) {
     const int j = e / NCOL, c = e - j * NCOL;
     fsh[e] = (j < np && c < nc) ? fs[int64_t(s0 + j) * nrhs + c0 + c] : make_float2(0.f, 0.f);
@@ -320,7 +339,7 @@ __global__ void __launch_bounds__(64 * S2M_MT_NW) k_s2m_mfma(const int* __restri
   const float* fb = reinterpret_cast<const float*>(fsh + (kr >> 1) * NCOL + jr) + kp;
   float sc[NCT];
 #pragma unroll
-  for (int c = 0; c < NCT; ++c) sc[c] = c * 16 + jr < nc ? s2m_scale(la, c0 + c * 16 + jr) : 1.0f;
+  for (int c = 0; c < NCT; ++c) sc[c] = s2m_scale(late(mark[c]));
   for (int m = w; m < R / 8; m += S2M_MT_NW) {
     const int p = m * 8 + (jr >> 1);  // this lane's row (complex)
     v4f acc[NCT];
@@ -1325,6 +1344,7 @@ __global__ void __launch_bounds__(L2T_BS) k_l2t(const float2* __restrict__ W, co
   for (int i = 0; i < L2T_QMAX; ++i)
     if (i < nq) w[i] = W[tt * R + l + 16 * i];
   const int64_t o = act ? perm[tt] : 0;
+  const int lift = l < nrhs ? la.lift[l] : 0;  // (fewer than 16 right-hand sides)
   for (int k = 0; k < nrhs; ++k) {
     const float2* ur = ulf + (int64_t(leaf) * nrhs + k) * R;
     float2 acc = make_float2(0.f, 0.f);
@@ -1336,10 +1356,11 @@ __global__ void __launch_bounds__(L2T_BS) k_l2t(const float2* __restrict__ W, co
       acc.x += __shfl_xor(acc.x, m, 16);
       acc.y += __shfl_xor(acc.y, m, 16);
     }
+    const unsigned up = unsigned(__ballot(late(lift) != 0));
     if (act && l == 0) {
       const double2 nf = unear[int64_t(k) * N + tt];
       const int r = req_of(Q, k);
-      const double sc = l2t_scale(la, k);
+      const double sc = up >> k & 1 ? 0x1p-64 : 1.0;
       Q.u[r][int64_t(k - Q.k0[r]) * N + o] =
           make_float2(float(double(acc.x) * sc + nf.x), float(double(acc.y) * sc + nf.y));
     }
@@ -1362,12 +1383,14 @@ __global__ void __launch_bounds__(L2T_BS) k_l2t_leaf(const float2* __restrict__ 
   const int s0 = lstart[b], s1 = lstart[b + 1];
   const int g = threadIdx.x >> 4, l = threadIdx.x & 15;
   const int nq = (R - l + 15) / 16;
+  const int lift = l < nrhs ? la.lift[l] : 0;  // (fewer than 16 right-hand sides)
   for (int k0 = 0; k0 < nrhs; k0 += kc) {
     const int nk = min(kc, nrhs - k0);
     __syncthreads();  // the previous rows are consumed
     const float2* src = ulf + (int64_t(bo) * nrhs + k0) * R;
     for (int i = threadIdx.x; i < nk * R; i += L2T_BS) us[i] = src[i];
     __syncthreads();
+    const unsigned up = unsigned(__ballot(late(lift) != 0));
     for (int t = s0 + g; t < s1; t += L2T_BS / 16) {
       float2 w[L2T_QMAX];
 #pragma unroll
@@ -1389,7 +1412,7 @@ __global__ void __launch_bounds__(L2T_BS) k_l2t_leaf(const float2* __restrict__ 
           const int kk = k0 + k;
           const double2 nf = unear[int64_t(kk) * N + t];
           const int r = req_of(Q, kk);
-          const double sc = l2t_scale(la, kk);
+          const double sc = up >> kk & 1 ? 0x1p-64 : 1.0;
           Q.u[r][int64_t(kk - Q.k0[r]) * N + o] =
               make_float2(float(double(acc.x) * sc + nf.x), float(double(acc.y) * sc + nf.y));
         }
@@ -1433,6 +1456,12 @@ __global__ void __launch_bounds__(64 * L2T_MT_NW) k_l2t_mfma(const float2* __res
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const int nc = min(NCOL, nrhs - c0);
+  int lift[NCT];  // of the columns that this lane writes
+#pragma unroll
+  for (int c = 0; c < NCT; ++c) {
+    const int col = c * 16 + int(threadIdx.x & 15);
+    lift[c] = col < nc ? la.lift[c0 + col] : 0;
+  }
   for (int e = threadIdx.x; e < NCOL * R; e += 64 * L2T_MT_NW) {
     const int c = e / R, q = e - c * R;
     us[c * RS + q] = c < nc ? ulf[(int64_t(bo) * nrhs + c0 + c) * R + q] : make_float2(0.f, 0.f);
@@ -1468,7 +1497,7 @@ __global__ void __launch_bounds__(64 * L2T_MT_NW) k_l2t_mfma(const float2* __res
     for (int c = 0; c < NCT; ++c) {
       const int col = c0 + c * 16 + j;
       if (col >= nrhs) continue;
-      const double sc = l2t_scale(la, col);
+      const double sc = l2t_scale(late(lift[c]));
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const int tt = s0 + rt * 8 + 2 * kr + h;
@@ -2290,7 +2319,8 @@ void run_apply(dfmm_plan_s& P, const ReqTable& R, int nrhs, hipStream_t st, void
   };
   const LiftArgs la{S.seen.as<unsigned long long>(), S.lift.as<int>()};
   // the tiled permutations pay from 16 rhs; the L2T of as many writes tree order
-  const bool tiled = nrhs >= 16;
+  constexpr int kTiledRhs = 16;
+  const bool tiled = nrhs >= kTiledRhs;
   const dim3 pt_grid(nblocks(N, PT_P), unsigned((nrhs + PT_C - 1) / PT_C));
   if (tiled)
     hipLaunchKernelGGL(k_permute_in_tile, pt_grid, dim3(PT_BS), 0, st, R, S.fs.as<float2>(), P.iperm_d.as<int>(), N,
@@ -2489,6 +2519,7 @@ void run_apply(dfmm_plan_s& P, const ReqTable& R, int nrhs, hipStream_t st, void
     }
   }
   if (own) DFMM_HIP(hipStreamWaitEvent(st, AS.join, 0));
+  static_assert(kTiledRhs <= 16, "k_l2t and k_l2t_leaf hold the marks of their right-hand sides in 16 lanes");
   if (Rl > 16 * L2T_QMAX || Rl % 2 != 0) throw Error{DFMM_EUNSUPPORTED, "leaf skeleton rank unsupported by L2T"};
   if (tiled) {
     // k_l2t_mfma: the staged column stride RS is odd (in float2), which spreads
