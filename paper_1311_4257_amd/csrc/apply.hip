@@ -712,9 +712,9 @@ __device__ __forceinline__ void slot_gemm(const SlotArgs& a, int nrhs, float2* _
 // are (group, rhs) of neighbouring groups, and columns without a term are zeros
 // there, which leave their sums as they are.  With one group per workgroup a single
 // right-hand side multiplies 15 columns of padding and reads and splits an operator
-// for every term of every slot; here 1.8 to 5 of 16 columns of a term are in use
-// (tiles of 4 to 16 groups).  A column's products and sums are those of the form
-// above, so the two give the same bits.
+// for every term of every slot; here 1.8 to 2.9 of 16 columns of an M2L term
+// are in use (K = 8 sphere, tiles of 4 and 8 groups).  A column's products and sums
+// are those of the form above, so the two give the same bits.
 struct SlotTileArgs {
   const int4* rec;    // SlotGemm: the cut's records, terms
   const int4* terms;  // (operator float4 offset, K | kind << 14, source vector, key)

@@ -266,8 +266,8 @@ __global__ void __launch_bounds__(256) k_slot64(const Slot64Args a, int nrhs, do
 // The same for few right-hand sides (TileTerms): the 16 columns of a workgroup are
 // (group, rhs) of neighbouring groups, and columns without a term are zeros there.
 // At one right-hand side the form above multiplies 15 columns of padding and reads
-// an operator (0.8 MB at rank 232) for every term of every slot; here 1.8 to 5 of
-// 16 columns of a term are in use (tiles of 4 to 16 groups).  A column's products
+// an operator (0.8 MB at rank 232) for every term of every slot; here 4.4 of 16
+// columns of an M2L term are in use (K = 8 sphere, 16 groups).  A column's products
 // and their order are those of the form above, so the two give the same bits.  A
 // wave takes MT row tiles of the slice, with the operator rows of T64_RING steps in
 // flight (a step is 256 matrix-core cycles; 12 steps measured the same).  Eight

@@ -317,9 +317,10 @@ static void build_cuts(SlotGemm& S, const std::vector<int32_t>& gM, const std::v
   std::map<int, SlotGemm::Cut> made;  // by groups per tile
   for (int nrhs = 1; nrhs <= kTileRhs; ++nrhs) {
     // more groups of a tile share more operators (1.8 columns of a term in use with 4,
-    // 5 with 16), but leave fewer waves, one per row tile; as many as leave 1.5
-    // waves for each of the 1,024 SIMDs, and whose lists are 16 KB (float64: with 60 KB
-    // of columns two workgroups fit a CU; surfaces have 40 to 60 terms a group)
+    // 2.9 with 8, 4.4 with 16 on the K = 8 sphere), but leave fewer waves, one per row
+    // tile; as many as leave 1.5 waves for each of the 1,024 SIMDs, and whose lists are
+    // 16 KB (float64: with 60 KB of columns two workgroups fit a CU; surfaces have 40
+    // to 60 terms a group)
     int per = kTileCols / nrhs;
     while (per > 1 && (n + per - 1) / per * row_tiles < 1536) per /= 2;
     SlotGemm::Cut c;
